@@ -104,17 +104,50 @@ static int check_block(const sparc_op *op, const void *p, int64_t ld, int ns, co
     return SPARC_OK;
 }
 
+int append_units(const int n[3], int64_t nd, const int lo[3], const int ext[3], std::vector<int> &units,
+                 std::vector<int> &pos)
+{
+    int cnt = 0;
+    size_t loc = pos.size();
+    pos.resize(loc + (size_t)ext[0] * ext[1] * ext[2]);
+    for (int i = 0; i < ext[0]; ++i)
+        for (int j = 0; j < ext[1]; ++j) {
+            const int64_t row = (int64_t)n[2] * ((lo[1] + j) + (int64_t)n[1] * (lo[0] + i));
+            const int z0 = lo[2], z1 = lo[2] + ext[2];
+            for (int s = z0 / 4 * 4; s < z1; s += 4) {
+                // the last unit of the grid starts 4 nodes before its end
+                const int64_t first = std::max<int64_t>(0, std::min<int64_t>(row + s, nd - 4));
+                int mask = 0;
+                for (int z = std::max(s, z0); z < std::min(s + 4, z1); ++z, ++loc) {
+                    const int b = (int)(row + z - first);
+                    mask |= 1 << b;
+                    pos[loc] = 4 * cnt + b;
+                }
+                units.push_back((int)first);
+                units.push_back(mask);
+                ++cnt;
+            }
+        }
+    return cnt;
+}
+
 int launch_h_step(const sparc_op *op, int dtype, const void *yk, int64_t ldk, const void *yprev, int64_t ldp,
                   void *out, int64_t ldo, int ns, void *part, const StepCoef &c, const StepLaunch &L,
                   hipStream_t stream, const FLaunch *V)
 {
     int st;
+    const int nparts = op->natoms > 0 && dtype == SPARC_F32 && gather_wide(op, ns) ? 1 : kGatherSplit;
+    void *tail = part;
+    if (part && nparts == 1) {
+        if ((st = launch_gather(op, dtype, yk, ldk, ns, part, nparts, stream))) return st;
+        tail = nullptr;
+    }
     if (V && V->plan >= 0)
-        st = launch_fstep(op, dtype, *V, yk, ldk, yprev, ldp, out, ldo, ns, part, c, stream);
+        st = launch_fstep(op, dtype, *V, yk, ldk, yprev, ldp, out, ldo, ns, tail, c, stream);
     else
-        st = launch_step_gather(op, dtype, yk, ldk, yprev, ldp, out, ldo, ns, part, c, L, stream);
+        st = launch_step_gather(op, dtype, yk, ldk, yprev, ldp, out, ldo, ns, tail, c, L, stream);
     if (st) return st;
-    return launch_scatter(op, dtype, out, ldo, ns, part, c.alpha, stream);
+    return launch_scatter(op, dtype, out, ldo, ns, part, nparts, c.alpha, stream);
 }
 
 }  // namespace sparc
@@ -231,7 +264,8 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
 
     // atoms
     op->natoms = natoms;
-    int64_t chi_total = 0, box_total = 0;
+    int64_t chi_total = 0, box_total = 0, chiu_total = 0;
+    std::vector<int> units, upos;
     for (int J = 0; J < natoms; ++J) {
         const sparc_atom &A = atoms[J];
         if (A.nproj < 1 || A.nproj > kMaxProj || !A.chi || !A.gamma)
@@ -248,8 +282,12 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
         a.proj0 = op->nproj_total;
         a.chi0 = chi_total;
         const int64_t nbox = (int64_t)A.ext[0] * A.ext[1] * A.ext[2];
-        a.box0 = (int)box_total;
         box_total += nbox;
+        // the gather's unit table and chi in its layout
+        a.unit0 = (int)(units.size() / 2);
+        a.nunits = append_units(op->n, op->nd, a.lo, a.ext, units, upos);
+        a.chiu0 = chiu_total;
+        chiu_total += (int64_t)4 * a.nunits * A.nproj;
         chi_total += nbox * A.nproj;
         op->nproj_total += A.nproj;
         op->max_nproj = std::max(op->max_nproj, A.nproj);
@@ -282,6 +320,8 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
         if (hipMalloc(&op->d_atoms, natoms * sizeof(AtomDev)) != hipSuccess ||
             hipMalloc(&op->d_chi64, chi_total * sizeof(double)) != hipSuccess ||
             hipMalloc(&op->d_chi32, chi_total * sizeof(float)) != hipSuccess ||
+            hipMalloc(&op->d_chiu64, chiu_total * sizeof(double)) != hipSuccess ||
+            hipMalloc(&op->d_chiu32, chiu_total * sizeof(float)) != hipSuccess ||
             hipMalloc(&op->d_hg64, op->nproj_total * sizeof(double)) != hipSuccess ||
             hipMalloc(&op->d_hg32, op->nproj_total * sizeof(float)) != hipSuccess)
             return cleanup(fail(SPARC_E_NOMEM, "device allocation of projector data failed"));
@@ -291,12 +331,13 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
             hipMemcpy(op->d_hg64, hg64.data(), op->nproj_total * sizeof(double), hipMemcpyHostToDevice) ||
             hipMemcpy(op->d_hg32, hg32.data(), op->nproj_total * sizeof(float), hipMemcpyHostToDevice))
             return cleanup(fail(SPARC_E_HIP, "copy of projector data failed"));
+        int st;
+        if ((st = build_unit_chi(op, upos, chiu_total))) return cleanup(st);
     }
 
-    // cube-point grid offsets and the unique covered nodes with their (atom, cube index) entries
+    // the unique covered nodes with their (atom, cube index) entries
     if (natoms > 0) {
         if (box_total > 0x7fffffffLL) return cleanup(fail(SPARC_E_SHAPE, "projector cubes too large"));
-        std::vector<int> boff(box_total);
         std::vector<std::pair<int64_t, std::pair<int, int>>> cover;
         cover.reserve(box_total);
         for (int J = 0; J < natoms; ++J) {
@@ -306,7 +347,6 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
                 for (int j = 0; j < a.ext[1]; ++j)
                     for (int k = 0; k < a.ext[2]; ++k, ++loc) {
                         const int64_t g = (int64_t)(a.lo[2] + k) + (int64_t)op->n[2] * ((a.lo[1] + j) + (int64_t)op->n[1] * (a.lo[0] + i));
-                        boff[a.box0 + loc] = (int)g;
                         cover.push_back({g, {J, loc}});
                     }
         }
@@ -368,7 +408,7 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
             if (hipMalloc(dst, std::max<size_t>(1, v.size()) * sizeof(int)) != hipSuccess) return false;
             return v.empty() || hipMemcpy(*dst, v.data(), v.size() * sizeof(int), hipMemcpyHostToDevice) == hipSuccess;
         };
-        if (!up(&op->d_box_off, boff) || !up(&op->d_nl_pts, pts) || !up(&op->d_nl_off, off) || !up(&op->d_nl_ent, ent) ||
+        if (!up(&op->d_units, units) || !up(&op->d_nl_pts, pts) || !up(&op->d_nl_off, off) || !up(&op->d_nl_ent, ent) ||
             !up(&op->d_nl_blk_pt, blk_pt) || !up(&op->d_nl_blk_at, blk_at) || !up(&op->d_nl_blk_atoms, blk_atoms))
             return cleanup(fail(SPARC_E_NOMEM, "device allocation of projector tables failed"));
     }
@@ -386,7 +426,9 @@ int sparc_op_destroy(sparc_op *op)
     (void)hipFree(op->d_chi32);
     (void)hipFree(op->d_hg64);
     (void)hipFree(op->d_hg32);
-    (void)hipFree(op->d_box_off);
+    (void)hipFree(op->d_units);
+    (void)hipFree(op->d_chiu64);
+    (void)hipFree(op->d_chiu32);
     (void)hipFree(op->d_nl_pts);
     (void)hipFree(op->d_nl_off);
     (void)hipFree(op->d_nl_ent);
@@ -394,7 +436,7 @@ int sparc_op_destroy(sparc_op *op)
     (void)hipFree(op->d_nl_blk_at);
     (void)hipFree(op->d_nl_blk_atoms);
     (void)hipFree(op->d_fatoms);
-    (void)hipFree(op->d_fbox_off);
+    (void)hipFree(op->d_funits);
     (void)hipFree(op->d_ffun);
     (void)hipFree(op->d_fgamma);
     delete op;

@@ -49,7 +49,9 @@ struct BatchClusterDev {
     const void *chi;
     const void *hg;
     const AtomDev *atoms;
-    const int *box_off;
+    const int2 *units;
+    const void *chiu;
+    int small;
     const int *blk_pt, *blk_at, *blk_atoms, *pts, *ent_off;
     const int4 *ent;
     int natoms, nproj_total, nl_nblk;
@@ -137,8 +139,9 @@ __device__ __forceinline__ void do_gather(const BatchClusterDev &c, int k, int l
     g.ns = c.ns;
     g.nproj_total = c.nproj_total;
     g.atoms = c.atoms;
-    g.box_off = c.box_off;
-    g.chi = (const T *)c.chi;
+    g.small = c.small;
+    g.units = c.units;
+    g.chi = (const T *)c.chiu;
     g.part = (T *)c.G;
     const int atom = local / kGatherSplit, ks = local % kGatherSplit;
 #pragma unroll 1
@@ -210,6 +213,7 @@ __device__ __forceinline__ void do_scatter(const BatchClusterDev &c, int k, int 
     sa.chi = (const T *)c.chi;
     sa.hg = (const T *)c.hg;
     sa.part = (const T *)c.G;
+    sa.nparts = kGatherSplit;
     sa.alpha = (T)c.coef[3 * k];
 #pragma unroll 1
     for (int cg = 0; cg < c.ncg; ++cg) {
@@ -478,7 +482,9 @@ int sparc_batch_create(const sparc_batch_job *jobs, int32_t njobs, int32_t mode,
         c.chi = f64 ? (const void *)op->d_chi64 : (const void *)op->d_chi32;
         c.hg = f64 ? (const void *)op->d_hg64 : (const void *)op->d_hg32;
         c.atoms = op->d_atoms;
-        c.box_off = op->d_box_off;
+        c.units = (const int2 *)op->d_units;
+        c.chiu = f64 ? (const void *)op->d_chiu64 : (const void *)op->d_chiu32;
+        c.small = op->nd < kUnit;
         c.blk_pt = op->d_nl_blk_pt;
         c.blk_at = op->d_nl_blk_at;
         c.blk_atoms = op->d_nl_blk_atoms;

@@ -49,7 +49,7 @@ int build_force_tables(const sparc_op *op)
     SPARC_HIP(hipMemcpy(chi.data(), op->d_chi64, chi_total * sizeof(double), hipMemcpyDeviceToHost));
 
     std::vector<AtomDev> rec;
-    std::vector<int> boff;
+    std::vector<int> boff, upos;
     std::vector<double> fun;
     rec.reserve(4 * natoms);
     for (int J = 0; J < natoms; ++J) {
@@ -71,15 +71,13 @@ int build_force_tables(const sparc_op *op)
             }
             F.proj0 = 4 * A.proj0 + r * A.nproj;
             if (boff.size() > 0x7fffffffULL) return fail(SPARC_E_SHAPE, "force tables too large");
-            F.box0 = (int)boff.size();
-            F.chi0 = (long long)fun.size();
-            const int nb = F.ext[0] * F.ext[1] * F.ext[2];
-            for (int i = 0; i < F.ext[0]; ++i)
-                for (int j = 0; j < F.ext[1]; ++j)
-                    for (int k = 0; k < F.ext[2]; ++k)
-                        boff.push_back(((F.lo[0] + i) * op->n[1] + (F.lo[1] + j)) * op->n[2] + (F.lo[2] + k));
-            fun.resize(fun.size() + (size_t)nb * A.nproj);
-            double *out = fun.data() + F.chi0;
+            F.unit0 = (int)(boff.size() / 2);
+            F.chiu0 = (long long)fun.size();
+            upos.clear();
+            F.nunits = append_units(op->n, op->nd, F.lo, F.ext, boff, upos);
+            const int nb = 4 * F.nunits;
+            fun.resize(fun.size() + (size_t)nb * A.nproj, 0.0);
+            double *out = fun.data() + F.chiu0;
             for (int p = 0; p < A.nproj; ++p) {
                 int t = 0;
                 for (int i = 0; i < F.ext[0]; ++i)
@@ -99,7 +97,7 @@ int build_force_tables(const sparc_op *op)
                                     v += w[q] * (chi_at(p, zm) - chi_at(p, zp));
                                 }
                             }
-                            out[(size_t)p * nb + t] = v;
+                            out[(size_t)p * nb + upos[t]] = v;
                         }
             }
             rec.push_back(F);
@@ -107,10 +105,10 @@ int build_force_tables(const sparc_op *op)
     }
     std::vector<double> gam(op->gamma.begin(), op->gamma.end());
     if (hipMalloc(&op->d_fatoms, rec.size() * sizeof(AtomDev)) != hipSuccess ||
-        hipMalloc(&op->d_fbox_off, boff.size() * sizeof(int)) != hipSuccess ||
+        hipMalloc(&op->d_funits, boff.size() * sizeof(int)) != hipSuccess ||
         hipMalloc(&op->d_ffun, fun.size() * sizeof(double)) != hipSuccess ||
         hipMalloc(&op->d_fgamma, gam.size() * sizeof(double)) != hipSuccess) {
-        for (void **p : {(void **)&op->d_fatoms, (void **)&op->d_fbox_off, (void **)&op->d_ffun,
+        for (void **p : {(void **)&op->d_fatoms, (void **)&op->d_funits, (void **)&op->d_ffun,
                          (void **)&op->d_fgamma}) {
             (void)hipFree(*p);
             *p = nullptr;
@@ -118,7 +116,7 @@ int build_force_tables(const sparc_op *op)
         return fail(SPARC_E_NOMEM, "allocation of the force tables failed");
     }
     SPARC_HIP(hipMemcpy(op->d_fatoms, rec.data(), rec.size() * sizeof(AtomDev), hipMemcpyHostToDevice));
-    SPARC_HIP(hipMemcpy(op->d_fbox_off, boff.data(), boff.size() * sizeof(int), hipMemcpyHostToDevice));
+    SPARC_HIP(hipMemcpy(op->d_funits, boff.data(), boff.size() * sizeof(int), hipMemcpyHostToDevice));
     SPARC_HIP(hipMemcpy(op->d_ffun, fun.data(), fun.size() * sizeof(double), hipMemcpyHostToDevice));
     SPARC_HIP(hipMemcpy(op->d_fgamma, gam.data(), gam.size() * sizeof(double), hipMemcpyHostToDevice));
     op->force_ready = true;
@@ -223,11 +221,13 @@ extern "C" int sparc_nonlocal_force(const sparc_op *op, int32_t dtype, const voi
     const double h3 = op->h * op->h * op->h;
     ProfScope prof(5, s);
     if (dtype == SPARC_F64) {
-        GatherArgs<double, double> a{(const double *)psi, ld, ns, 4 * op->nproj_total, op->d_fatoms, op->d_fbox_off,
+        GatherArgs<double, double> a{(const double *)psi, ld, ns, 4 * op->nproj_total, op->nd < kUnit, op->d_fatoms,
+                                     (const int2 *)op->d_funits,
                                      op->d_ffun, (double *)ws};
         hipLaunchKernelGGL(force_gather_kernel<double>, grid, dim3(256), 0, s, a);
     } else {
-        GatherArgs<double, float> a{(const float *)psi, ld, ns, 4 * op->nproj_total, op->d_fatoms, op->d_fbox_off,
+        GatherArgs<double, float> a{(const float *)psi, ld, ns, 4 * op->nproj_total, op->nd < kUnit, op->d_fatoms,
+                                     (const int2 *)op->d_funits,
                                     op->d_ffun, (double *)ws};
         hipLaunchKernelGGL(force_gather_kernel<float>, grid, dim3(256), 0, s, a);
     }

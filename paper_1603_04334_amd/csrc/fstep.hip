@@ -161,7 +161,7 @@ static int launch_fstep_t(const sparc_op *op, const FLaunch &L, const void *yk, 
             // the patch is too small to host gather items: a launch of its own
             int st;
             if ((st = launch_gather(op, std::is_same<T, double>::value ? SPARC_F64 : SPARC_F32, yk, ldk, ns, part,
-                                    stream)))
+                                    kGatherSplit, stream)))
                 return st;
         } else {
             g.Y = (const T *)yk;
@@ -169,8 +169,9 @@ static int launch_fstep_t(const sparc_op *op, const FLaunch &L, const void *yk, 
             g.ns = ns;
             g.nproj_total = op->nproj_total;
             g.atoms = op->d_atoms;
-            g.box_off = op->d_box_off;
-            g.chi = std::is_same<T, double>::value ? (const T *)op->d_chi64 : (const T *)op->d_chi32;
+            g.small = op->nd < kUnit;
+            g.units = (const int2 *)op->d_units;
+            g.chi = std::is_same<T, double>::value ? (const T *)op->d_chiu64 : (const T *)op->d_chiu32;
             g.part = (T *)part;
             ncb = (ns + 15) / 16;
             nitems = op->natoms * ncb * kGatherSplit;

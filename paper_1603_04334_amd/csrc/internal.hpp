@@ -26,7 +26,8 @@ struct AtomDev {
     int ext[3];
     int nproj;
     int proj0;        // index of the atom's first projector in the global projector list
-    int box0;         // offset of the atom's cube in the cube-point offset table
+    int unit0, nunits;  // the atom's units in the gather's unit table
+    long long chiu0;    // offset of its chi in unit layout (nproj * nunits units)
     long long chi0;   // offset of the atom's chi block (nproj * nbox values)
 };
 
@@ -69,7 +70,9 @@ struct sparc_op {
     float *d_chi32 = nullptr;
     double *d_hg64 = nullptr;  // h^3 gamma per global projector
     float *d_hg32 = nullptr;
-    int *d_box_off = nullptr;  // grid index of every cube point (atoms back to back)
+    int *d_units = nullptr;  // int2 records of the gather's units (atoms back to back)
+    double *d_chiu64 = nullptr;  // chi in unit layout
+    float *d_chiu32 = nullptr;
     // unique nodes covered by at least one projector cube, their entries
     // (chi index of projector 0, cube size, block slot, nproj) and the
     // scatter blocks (node ranges and the atoms each touches)
@@ -95,7 +98,7 @@ struct sparc_op {
     mutable std::mutex force_mu;
     mutable bool force_ready = false;
     mutable sparc::AtomDev *d_fatoms = nullptr;
-    mutable int *d_fbox_off = nullptr;
+    mutable int *d_funits = nullptr;
     mutable double *d_ffun = nullptr;
     mutable double *d_fgamma = nullptr;
 };
@@ -164,13 +167,30 @@ FLaunch vec_launch_plan(const sparc_op *op, int dtype, int ns, int plan);
 int launch_fstep(const sparc_op *op, int dtype, const FLaunch &L, const void *yk, int64_t ldk, const void *yprev,
                  int64_t ldp, void *out, int64_t ldo, int ns, void *part, const StepCoef &c, hipStream_t stream);
 
-// enqueue the projector gather: split partial sums of chi_Jp^T Y(:,c) per atom
-int launch_gather(const sparc_op *op, int dtype, const void *Y, int64_t ldy, int ns, void *part,
+// The gather's units of the cube (lo, ext) appended to units (see
+// nonlocal_kernel.hpp); per cube node (x, y, z fastest) its place 4 u + j among
+// the cube's units is appended to pos.  Returns the number of units.
+int append_units(const int n[3], int64_t nd, const int lo[3], const int ext[3], std::vector<int> &units,
+                 std::vector<int> &pos);
+
+// chi in unit layout (op->d_chiu64, d_chiu32: total values) from op->d_chi64
+// and the places of the cube nodes, atoms back to back.  Synchronous.
+int build_unit_chi(sparc_op *op, const std::vector<int> &pos, int64_t total);
+
+// A gather whose (atom, 16 columns) pairs alone fill the chip takes one
+// workgroup per pair, which finishes the projections (1 part); a smaller one
+// is spread over kGatherSplit workgroups per pair, which leave as many partial
+// sums, or over the last workgroups of a step launch.
+bool gather_wide(const sparc_op *op, int ns);
+
+// enqueue the projector gather of chi_Jp^T Y(:,c) per atom (FP32: nparts = 1 or
+// kGatherSplit; FP64: kGatherSplit)
+int launch_gather(const sparc_op *op, int dtype, const void *Y, int64_t ldy, int ns, void *part, int nparts,
                   hipStream_t stream);
 
 // enqueue the projector scatter: out += alpha * V_nl Y from the gathered partials
-int launch_scatter(const sparc_op *op, int dtype, void *out, int64_t ldo, int ns, const void *part, double alpha,
-                   hipStream_t stream);
+int launch_scatter(const sparc_op *op, int dtype, void *out, int64_t ldo, int ns, const void *part, int nparts,
+                   double alpha, hipStream_t stream);
 
 // enqueue one fused stencil / potential / recurrence step (local part of H)
 int launch_step(const sparc_op *op, int dtype, const void *yk, int64_t ldk, const void *yprev, int64_t ldp,
@@ -178,7 +198,7 @@ int launch_step(const sparc_op *op, int dtype, const void *yk, int64_t ldk, cons
 
 // H applied in FP64 to an FP32 block (values widened on load): the
 // projector gather and the local step of the Rayleigh-Ritz product H Y
-int launch_gather_f32_to_f64(const sparc_op *op, const float *Y, int64_t ldy, int ns, double *part,
+int launch_gather_f32_to_f64(const sparc_op *op, const float *Y, int64_t ldy, int ns, double *part, int nparts,
                              hipStream_t stream);
 int launch_step_f32_to_f64(const sparc_op *op, const float *yk, int64_t ldk, double *out, int64_t ldo, int ns,
                            const StepCoef &c, const StepLaunch &L, hipStream_t stream);

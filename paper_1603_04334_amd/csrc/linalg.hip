@@ -816,7 +816,7 @@ int sparc_lanczos(const sparc_op *op, int32_t k, const double *v0, double *alpha
         double *vj = V + (long long)j * n;
         // w = H v_j, with the two parts of alpha_j = v_j^T H v_j left as partials
         if ((st = launch_lanczos_h_f64(op, vj, w, dotp, G, s))) return st;
-        if ((st = launch_scatter(op, SPARC_F64, w, n, 1, G, 1.0, s))) return st;
+        if ((st = launch_scatter(op, SPARC_F64, w, n, 1, G, kGatherSplit, 1.0, s))) return st;
         if (j + 1 == k) {
             hipLaunchKernelGGL(alpha_finish, dim3(1), tb, 0, s, (const double *)dotp, ndot, (const double *)G,
                                (const double *)op->d_hg64, nproj, d_alpha + j);
@@ -934,9 +934,10 @@ int sparc_rayleigh_ritz(const sparc_op *op, int32_t dtype, const void *Y, int64_
     } else {
         // H in FP64 on the FP32 values, widened as they are loaded
         const float *Yf = (const float *)Y;
-        if ((st = launch_gather_f32_to_f64(op, Yf, ldy, ns, G, s))) return st;
+        const int nparts = op->natoms > 0 && gather_wide(op, ns) ? 1 : kGatherSplit;
+        if ((st = launch_gather_f32_to_f64(op, Yf, ldy, ns, G, nparts, s))) return st;
         if ((st = launch_step_f32_to_f64(op, Yf, ldy, HY, nd, ns, hc, choose_mixed_launch(op, ns), s))) return st;
-        if ((st = launch_scatter(op, SPARC_F64, HY, nd, ns, G, 1.0, s))) return st;
+        if ((st = launch_scatter(op, SPARC_F64, HY, nd, ns, G, nparts, 1.0, s))) return st;
         hipLaunchKernelGGL(rr_project_kernel<float>, pg, dim3(256), 0, s, Yf, (long long)ldy, (const double *)HY, nd,
                            nd, ns, kc, partial);
     }

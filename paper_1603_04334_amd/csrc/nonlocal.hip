@@ -5,10 +5,18 @@
 //  * gather: per atom J, the projections S_Jp(c) = sum_{x in cube_J} chi_Jp(x) y(x,c)
 //    as a small dense GEMM on the matrix cores, S_J^T (ns x nproj) =
 //    Y_cube^T (ns x nbox) * chi_J (nbox x nproj), using
-//    v_mfma_f64_16x16x4f64 (FP64) or v_mfma_f32_16x16x4f32 (FP32).  The
-//    cube's points (the K dimension) are split over kGatherSplit workgroups;
-//    each writes its partial 16 x nproj tile.  No atomics: the partials are
-//    summed in split order by the consumer.
+//    v_mfma_f64_16x16x4f64 (FP64) or v_mfma_f32_16x16x4f32 (FP32).  The cube is
+//    read as units of 4 nodes along z, 16 bytes of FP32 per lane, four matrix
+//    instructions per load; the units (the K dimension) are cut into 4
+//    kGatherSplit segments of one wave each.  Either kGatherSplit workgroups
+//    share an atom and 16 columns and leave partial 16 x nproj tiles that the
+//    consumer sums in split order, or one workgroup sums them itself in the
+//    same order; no atomics, the same bits either way.
+//    What bounds it: the cube rows are short (14 to 15 nodes), so each costs
+//    1.5 lines of 128 bytes per column, 3.3 GB at 160^3 x 600 with 128 cubes.
+//    Node by node (4 bytes per lane, a table entry and a chi value per matrix
+//    instruction) the gather took 948 us there, by units of 4 nodes 676 us
+//    (4.9 TB/s of those lines); the FP64 gathers of the force 5.2 -> 4.2 ms.
 //  * scatter: out(x,c) += alpha * sum_{J: x in cube_J} sum_p chi_Jp(x) h^3 gamma_Jp S_Jp(c)
 //    over the unique nodes covered by at least one cube, grouped in blocks of
 //    at most 256 nodes that touch at most kScatterSlots atoms (tables built at
@@ -39,6 +47,13 @@ __global__ void __launch_bounds__(256) gather_kernel(const GatherArgs<T, TI> g)
     gather_item<T, TI>(g, blockIdx.x, blockIdx.y, blockIdx.z, tile, threadIdx.x);
 }
 
+template <typename T, typename TI>
+__global__ void __launch_bounds__(256) gather_whole_kernel(const GatherArgs<T, TI> g)
+{
+    __shared__ T tile[4][4][16][16];
+    gather_whole<T, TI>(g, blockIdx.y, blockIdx.x, tile);
+}
+
 // table in dynamic LDS: [block's atoms][npm][NC]
 template <typename T, int NC>
 __global__ void __launch_bounds__(256) scatter_kernel(const ScatterArgs<T> s, int npm)
@@ -47,43 +62,98 @@ __global__ void __launch_bounds__(256) scatter_kernel(const ScatterArgs<T> s, in
     scatter_item<T, NC>(s, blockIdx.x, blockIdx.y, (T *)scatter_lds, npm);
 }
 
+// blockIdx.x: atom; its nodes' places from pos + (cube nodes of the atoms before it)
+__global__ void __launch_bounds__(256) unit_chi_kernel(const AtomDev *atoms, const double *chi, const int *pos,
+                                                       double *chiu64, float *chiu32)
+{
+    const AtomDev A = atoms[blockIdx.x];
+    long long p0 = 0;
+    for (int J = 0; J < (int)blockIdx.x; ++J) p0 += (long long)atoms[J].ext[0] * atoms[J].ext[1] * atoms[J].ext[2];
+    const int nbox = A.ext[0] * A.ext[1] * A.ext[2];
+    for (int t = blockIdx.y * 256 + threadIdx.x; t < nbox; t += gridDim.y * 256) {
+        const int d = pos[p0 + t];
+        for (int p = 0; p < A.nproj; ++p) {
+            const double v = chi[A.chi0 + (long long)p * nbox + t];
+            const long long o = A.chiu0 + (long long)p * A.nunits * kUnit + d;
+            chiu64[o] = v;
+            chiu32[o] = (float)v;
+        }
+    }
+}
+
+int build_unit_chi(sparc_op *op, const std::vector<int> &pos, int64_t total)
+{
+    int *d_pos = nullptr;
+    if (hipMalloc(&d_pos, pos.size() * sizeof(int)) != hipSuccess)
+        return fail(SPARC_E_NOMEM, "device allocation of projector tables failed");
+    hipError_t e = hipMemcpy(d_pos, pos.data(), pos.size() * sizeof(int), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemset(op->d_chiu64, 0, total * sizeof(double));
+    if (e == hipSuccess) e = hipMemset(op->d_chiu32, 0, total * sizeof(float));
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(unit_chi_kernel, dim3(op->natoms, 4), dim3(256), 0, 0, op->d_atoms, op->d_chi64, d_pos,
+                           op->d_chiu64, op->d_chiu32);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(0);
+    (void)hipFree(d_pos);
+    return e == hipSuccess ? SPARC_OK : fail(SPARC_E_HIP, std::string("projector tables: ") + hipGetErrorString(e));
+}
+
+bool gather_wide(const sparc_op *op, int ns)
+{
+    // measured (FP32 filters): 128 atoms x 600 columns (4864 pairs) 1.3 %
+    // faster per step on its own than in the step's tail, 40 atoms x 128
+    // columns (320 pairs) 0.5 % slower
+    return (long long)op->natoms * ((ns + 15) / 16) >= 2048;
+}
+
 template <typename T, typename TI = T>
-static int launch_gather_t(const sparc_op *op, const void *Y, int64_t ldy, int ns, void *part, hipStream_t stream,
-                           const T *chi)
+static int launch_gather_t(const sparc_op *op, const void *Y, int64_t ldy, int ns, void *part, int nparts,
+                           hipStream_t stream, const T *chi)
 {
     GatherArgs<T, TI> a;
     a.Y = (const TI *)Y;
     a.ldy = ldy;
     a.ns = ns;
     a.nproj_total = op->nproj_total;
+    a.small = op->nd < kUnit;
     a.atoms = op->d_atoms;
-    a.box_off = op->d_box_off;
+    a.units = (const int2 *)op->d_units;
     a.chi = chi;
     a.part = (T *)part;
-    dim3 grid(op->natoms, (ns + 15) / 16, kGatherSplit);
+    const unsigned ncb = (unsigned)(ns + 15) / 16;
     ProfScope prof(1, stream);
-    hipLaunchKernelGGL((gather_kernel<T, TI>), grid, dim3(256), 0, stream, a);
+    if constexpr (sizeof(TI) == 4) {
+        if (nparts == 1) {
+            hipLaunchKernelGGL((gather_whole_kernel<T, TI>), dim3(ncb, op->natoms), dim3(256), 0, stream, a);
+            SPARC_HIP(hipGetLastError());
+            return SPARC_OK;
+        }
+    }
+    hipLaunchKernelGGL((gather_kernel<T, TI>), dim3(op->natoms, ncb, kGatherSplit), dim3(256), 0, stream, a);
     SPARC_HIP(hipGetLastError());
     return SPARC_OK;
 }
 
-int launch_gather_f32_to_f64(const sparc_op *op, const float *Y, int64_t ldy, int ns, double *part, hipStream_t stream)
+int launch_gather_f32_to_f64(const sparc_op *op, const float *Y, int64_t ldy, int ns, double *part, int nparts,
+                             hipStream_t stream)
 {
     if (op->natoms == 0) return SPARC_OK;
     if ((long long)(ns + 15) / 16 > 65535) return fail(SPARC_E_SHAPE, "too many columns for one gather launch");
-    return launch_gather_t<double, float>(op, Y, ldy, ns, part, stream, op->d_chi64);
+    return launch_gather_t<double, float>(op, Y, ldy, ns, part, nparts, stream, op->d_chiu64);
 }
 
-int launch_gather(const sparc_op *op, int dtype, const void *Y, int64_t ldy, int ns, void *part, hipStream_t stream)
+int launch_gather(const sparc_op *op, int dtype, const void *Y, int64_t ldy, int ns, void *part, int nparts,
+                  hipStream_t stream)
 {
     if (op->natoms == 0) return SPARC_OK;
     if ((long long)(ns + 15) / 16 > 65535) return fail(SPARC_E_SHAPE, "too many columns for one gather launch");
-    if (dtype == SPARC_F64) return launch_gather_t<double>(op, Y, ldy, ns, part, stream, op->d_chi64);
-    return launch_gather_t<float>(op, Y, ldy, ns, part, stream, op->d_chi32);
+    if (dtype == SPARC_F64) return launch_gather_t<double>(op, Y, ldy, ns, part, nparts, stream, op->d_chiu64);
+    return launch_gather_t<float>(op, Y, ldy, ns, part, nparts, stream, op->d_chiu32);
 }
 
 template <typename T>
-static int launch_scatter_t(const sparc_op *op, void *out, int64_t ldo, int ns, const void *part, double alpha,
+static int launch_scatter_t(const sparc_op *op, void *out, int64_t ldo, int ns, const void *part, int nparts, double alpha,
                             hipStream_t stream, const T *chi, const T *hg)
 {
     ScatterArgs<T> a;
@@ -101,6 +171,7 @@ static int launch_scatter_t(const sparc_op *op, void *out, int64_t ldo, int ns, 
     a.chi = chi;
     a.hg = hg;
     a.part = (const T *)part;
+    a.nparts = nparts;
     a.alpha = (T)alpha;
     // columns per workgroup: FP32 blocks take 32 when the table fits in 32
     // KiB of LDS (a quarter of the chi and table reads of 8 columns, same
@@ -121,12 +192,12 @@ static int launch_scatter_t(const sparc_op *op, void *out, int64_t ldo, int ns, 
     return SPARC_OK;
 }
 
-int launch_scatter(const sparc_op *op, int dtype, void *out, int64_t ldo, int ns, const void *part, double alpha,
-                   hipStream_t stream)
+int launch_scatter(const sparc_op *op, int dtype, void *out, int64_t ldo, int ns, const void *part, int nparts,
+                   double alpha, hipStream_t stream)
 {
     if (op->natoms == 0) return SPARC_OK;
-    if (dtype == SPARC_F64) return launch_scatter_t<double>(op, out, ldo, ns, part, alpha, stream, op->d_chi64, op->d_hg64);
-    return launch_scatter_t<float>(op, out, ldo, ns, part, alpha, stream, op->d_chi32, op->d_hg32);
+    if (dtype == SPARC_F64) return launch_scatter_t<double>(op, out, ldo, ns, part, nparts, alpha, stream, op->d_chi64, op->d_hg64);
+    return launch_scatter_t<float>(op, out, ldo, ns, part, nparts, alpha, stream, op->d_chi32, op->d_hg32);
 }
 
 }  // namespace sparc

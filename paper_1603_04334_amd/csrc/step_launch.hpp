@@ -152,7 +152,8 @@ int launch_step_t(const sparc_op *op, const void *yk, int64_t ldk, const void *y
         gp.g.ns = ns;
         gp.g.nproj_total = op->nproj_total;
         gp.g.atoms = op->d_atoms;
-        gp.g.box_off = op->d_box_off;
+        gp.g.small = op->nd < kUnit;
+        gp.g.units = (const int2 *)op->d_units;
         gp.g.chi = chi;
         gp.g.part = (T *)part;
         gp.natoms = op->natoms;
