@@ -484,8 +484,8 @@ int sparc_step_config(const sparc_op *op, int32_t dtype, int32_t ns, int32_t *ti
     if (!op || ns < 1 || (dtype != SPARC_F64 && dtype != SPARC_F32)) return fail(SPARC_E_ARG, "null op, ns < 1 or bad dtype");
     const FLaunch V = choose_vec_launch(op, dtype, ns, {});
     if (V.plan >= 0) {
-        if (tile_z) *tile_z = kPlanTZ[V.plan];
-        if (tile_y) *tile_y = kPlanTY[V.plan];
+        if (tile_z) *tile_z = V.plan == kRowPair ? V.tz : kPlanTZ[V.plan];
+        if (tile_y) *tile_y = V.plan == kRowPair ? V.ty : kPlanTY[V.plan];
         if (chunk_x) *chunk_x = V.chunk_x;
         if (col_group) *col_group = std::min(V.cgroup, (ns + V.cblk - 1) / V.cblk);
         if (col_block) *col_block = V.cblk;

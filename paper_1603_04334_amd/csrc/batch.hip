@@ -512,11 +512,11 @@ int sparc_batch_create(const sparc_batch_job *jobs, int32_t njobs, int32_t mode,
         // stencil geometry: the dtype's 256-thread vector patch and the
         // standalone filter's x split for it
         if (mode != 3 && mode != 5) {
-            const FLaunch V = choose_vec_launch(op, j.dtype, j.ns, {j.ldx, j.ldy, op->nd});
-            if (V.plan < 0)
+            if (!vec_grid(op, j.dtype, {j.ldx, j.ldy, op->nd}))
                 return cleanup(fail(SPARC_E_SHAPE, "job " + std::to_string(i) +
                                                        ": batched modes need the vector step kernels (z extent and "
                                                        "leading dimensions multiples of 4 FP32 / 2 FP64 values)"));
+            const FLaunch V = choose_vec_launch(op, j.dtype, j.ns, {j.ldx, j.ldy, op->nd});
             const FLaunch B = V.plan == kBatchPlan[j.dtype] ? V : vec_launch_plan(op, j.dtype, j.ns, kBatchPlan[j.dtype]);
             const int ty = kPlanTY[B.plan];
             c.tiles_y = (c.n2 + ty - 1) / ty;

@@ -40,6 +40,7 @@
 #include <type_traits>
 
 #include "fstep_launch.hpp"
+#include "rstep_launch.hpp"
 
 namespace sparc {
 
@@ -77,6 +78,15 @@ static int vec_default_chunks(const sparc_op *op, int dtype, int plan, int ns)
     return (int)nch;
 }
 
+bool vec_grid(const sparc_op *op, int dtype, std::initializer_list<int64_t> lds)
+{
+    const int vz = vec_width(dtype);
+    if (op->n[2] % vz != 0) return false;
+    for (int64_t ld : lds)
+        if (ld % vz != 0) return false;
+    return true;
+}
+
 static void set_chunks(const sparc_op *op, int nch, FLaunch &L)
 {
     nch = std::max(1, std::min(nch, std::min(kMaxChunks, op->n[0])));
@@ -84,15 +94,118 @@ static void set_chunks(const sparc_op *op, int nch, FLaunch &L)
     L.nchunks = (op->n[0] + L.chunk_x - 1) / L.chunk_x;
 }
 
+// ---------------------------------------------------------------- row-pair launches
+
+
+// LDS row pitch of a patch tz nodes wide: the narrowest of the two compiled
+static int rstep_pitch(int dtype, int tz)
+{
+    const int need = tz + 2 * (dtype == SPARC_F64 ? 6 : 8);
+    if (dtype == SPARC_F64) return need <= 44 ? 44 : need <= 108 ? 108 : 0;
+    return need <= 112 ? 112 : need <= 176 ? 176 : 0;
+}
+
+// threads of a patch (whole waves; 0: the patch does not fit a workgroup)
+static int rstep_threads(const sparc_op *op, int dtype, int tz, int ty, int &nh)
+{
+    const int vz = vec_width(dtype), lpr = tz / vz;
+    const int pitch = rstep_pitch(dtype, tz);
+    const int nt = (lpr * (ty / 2) + 63) / 64 * 64;
+    if (!pitch || nt > kRThreads) return 0;
+    if (2 * (size_t)(ty + 2 * kMaxRadius) * pitch * elem_size(dtype) > 65536) return 0;
+    const int zu = dtype == SPARC_F64 ? 3 : 2;
+    const int nhalo = 2 * kMaxRadius * lpr + (tz < op->n[2] ? ty * 2 * zu : 0);
+    nh = (nhalo + nt - 1) / nt;
+    return nh <= 2 ? nt : 0;
+}
+
+// Patch and x split of the row-pair kernels for ns columns (L.plan stays -1
+// when no patch fits).  A workgroup holds its CU's SIMDs with up to 8 waves of
+// 256 registers, so small launches run in a few rounds of workgroups and what
+// decides is how full the last round is against the 12 planes every workgroup
+// reads before its first output (worth about 10 planes).  The estimate is
+//   (rounds + 1/2) x waves per CU x (planes + 10) x (1 + 4 / patch rows),
+// the last factor the y halo.  Measured per step, FP32: 128^3 x 128 in 1, 2, 4
+// x-chunks 733, 666, 688 us; 75 x 83 x 91 x 64 in 2, 4, 5 chunks 95, 101, 113
+// us; 96^3 x 64 in 1, 4, 8 chunks 137, 138, 160 us.  Patches are as wide as the
+// grid row where it fits (no z halo): 160^3 x 600 24 x 160 5.81 ms, 24 x 80
+// 6.76 ms.
+static void choose_rstep(const sparc_op *op, int dtype, int ns, FLaunch &L)
+{
+    const int vz = vec_width(dtype), maxtz = dtype == SPARC_F64 ? 96 : 160;
+    const int kz = (op->n[2] + maxtz - 1) / maxtz;
+    const int tz = ((op->n[2] + kz - 1) / kz + vz - 1) / vz * vz;
+    const int tiles_z = (op->n[2] + tz - 1) / tz;
+    double best = 0;
+    for (int ky = 1; ky <= op->n[1]; ++ky) {
+        const int ty = ((op->n[1] + ky - 1) / ky + 1) / 2 * 2;
+        if (ty < 12 && ky > 1) break;
+        int nh = 0;
+        const int nt = rstep_threads(op, dtype, tz, ty, nh);
+        // patches below 256 threads cannot host gather items (40 x 32 x 32 x
+        // 503: 128 threads and a gather launch 57 us per step, 32 x 32 patches
+        // of the other kernels 55 us)
+        if (!nt || (nt < 256 && op->natoms > 0)) continue;
+        const int w = nt / 64;
+        // workgroups of about 10 planes: too few leave CUs idle (118 x 149 x 129
+        // x 3: 177 of them, 40 us per step against the scalar kernels' 37.6 us)
+        if ((double)ns * ky * tiles_z * op->n[0] < 4000.0) continue;
+        const size_t lds = 2 * (size_t)(ty + 2 * kMaxRadius) * rstep_pitch(dtype, tz) * elem_size(dtype);
+        const int percu = std::max(1, std::min(8 / w, (int)(163840 / lds)));
+        const int full = std::max(6, percu * w);  // fewer waves than that leave a CU waiting
+        for (int nch = 1; nch <= kMaxChunks && (nch == 1 || op->n[0] / nch >= 8); ++nch) {
+            const int cx = (op->n[0] + nch - 1) / nch, chunks = (op->n[0] + cx - 1) / cx;
+            const long long wgs = (long long)ns * ((op->n[1] + ty - 1) / ty) * tiles_z * chunks;
+            const long long slots = 256LL * percu, rem = wgs % slots;
+            double rounds = (double)(wgs / slots) * full + 0.5 * full;
+            if (rem) rounds += std::max<long long>(6, (rem + 255) / 256 * w);
+            const double cost = rounds * (cx + 10) * (1.0 + 4.0 / ty);
+            if (L.plan < 0 || cost < best) {
+                best = cost;
+                L.plan = kRowPair;
+                L.tz = tz;
+                L.ty = ty;
+                L.chunk_x = cx;
+                L.nchunks = chunks;
+                L.cgroup = L.cblk = 1;
+            }
+        }
+    }
+}
+
+// Whether the library's own choice is the row-pair kernels.  aligned: the
+// 16-byte-unit kernels of this file take the grid too.
+//  * FP32 from 4e6 values per block: 160^3 x 600 7.75 -> 6.84 ms per step
+//    launch, 128^3 x 128 827 -> 666 us, 96^3 x 64 178 -> 137 us, 64^3 x 64 49 ->
+//    44 us; below (32^3 x 64) 12 -> 15 us.
+//  * FP64, whose step is bound by memory already: only where the 16 x 32 patches
+//    of the other kernels reach 15 % past the grid (75 x 83 x 92 x 37 151 -> 131
+//    us; 96^3 x 64, no overhang, 300 -> 322 us).
+//  * Rows of broken units, which only the scalar kernels take otherwise:
+//    75 x 83 x 91, FP64 x 37 171 -> 135 us, FP32 x 64 191 -> 95 us.
+static bool take_rstep(const sparc_op *op, int dtype, int ns, bool aligned)
+{
+    if ((double)op->nd * ns < 4e6 || op->n[2] < vec_width(dtype)) return false;
+    if (!aligned || dtype == SPARC_F32) return true;
+    const double pad = (double)((op->n[1] + 15) / 16 * 16) * ((op->n[2] + 31) / 32 * 32);
+    return pad >= 1.15 * op->n[1] * op->n[2];
+}
+
 FLaunch choose_vec_launch(const sparc_op *op, int dtype, int ns, std::initializer_list<int64_t> lds)
 {
     FLaunch L;
-    const int vz = vec_width(dtype);
-    if (op->n[2] % vz != 0) return L;
-    for (int64_t ld : lds)
-        if (ld % vz != 0) return L;
-    int plan = vec_default_plan(dtype);
+    const bool aligned = vec_grid(op, dtype, lds);
     const bool tuned = tune_applies(op, dtype, ns);
+    if (tuned && op->tune_shape[dtype] == kRowPair) {
+        choose_rstep(op, dtype, ns, L);
+        if (L.plan >= 0 && op->tune_chunk[dtype] > 0) set_chunks(op, (op->n[0] + op->tune_chunk[dtype] - 1) / op->tune_chunk[dtype], L);
+        if (L.plan >= 0) return L;
+    }
+    const bool forced = tuned && (op->tune_shape[dtype] >= 0 || op->tune_chunk[dtype] > 0 || op->tune_group[dtype] > 0 ||
+                                  op->tune_cblk[dtype] > 0);
+    if (!(aligned && forced) && take_rstep(op, dtype, ns, aligned)) choose_rstep(op, dtype, ns, L);
+    if (L.plan >= 0 || !aligned) return L;
+    int plan = vec_default_plan(dtype);
     if (tuned && op->tune_shape[dtype] >= 0 && vec_plan_valid(dtype, op->tune_shape[dtype]))
         plan = op->tune_shape[dtype];
     int nch = vec_default_chunks(op, dtype, plan, ns);
@@ -110,6 +223,93 @@ FLaunch vec_launch_plan(const sparc_op *op, int dtype, int ns, int plan)
     L.plan = plan;
     set_chunks(op, vec_default_chunks(op, dtype, plan, ns), L);
     return L;
+}
+
+template <typename T>
+static int launch_rstep_t(const sparc_op *op, const FLaunch &L, const void *yk, int64_t ldk, const void *yprev,
+                          int64_t ldp, void *out, int64_t ldo, int ns, void *part, const StepCoef &c,
+                          hipStream_t stream)
+{
+    constexpr int dtype = std::is_same<T, double>::value ? SPARC_F64 : SPARC_F32;
+    int nh = 0;
+    const int nt = rstep_threads(op, dtype, L.tz, L.ty, nh);
+    if (!nt) return fail(SPARC_E_ARG, "row-pair patch does not fit a workgroup");
+    RStepArgs<T> a;
+    std::memset(&a, 0, sizeof(a));
+    a.yk = (const T *)yk;
+    a.yprev = (const T *)yprev;
+    a.out = (T *)out;
+    a.veff = std::is_same<T, double>::value ? (const T *)op->d_veff64 : (const T *)op->d_veff32;
+    a.ldk = ldk;
+    a.ldp = ldp;
+    a.ldo = ldo;
+    a.n1 = op->n[0];
+    a.n2 = op->n[1];
+    a.n3 = op->n[2];
+    a.tz = L.tz;
+    a.ty = L.ty;
+    a.lpr = L.tz / VecTraits<T>::N;
+    a.tiles_y = (op->n[1] + L.ty - 1) / L.ty;
+    a.tiles_z = (op->n[2] + L.tz - 1) / L.tz;
+    a.zhalo = L.tz < op->n[2] ? 1 : 0;
+    a.chunk_x = L.chunk_x;
+    a.nchunks = L.nchunks;
+    const int G = std::max(1, std::min(L.cgroup, ns));
+    const long long nb = (long long)(ns + G - 1) / G * G * L.nchunks * a.tiles_y * a.tiles_z;
+    if (nb > 0x7fffffffLL) return fail(SPARC_E_SHAPE, "too many workgroups for one launch");
+    a.nblocks = (int)nb;
+    a.ns = ns;
+    a.cgroup = G;
+    a.c0 = (T)(-3.0 * op->w[0]);
+    for (int p = 1; p <= kMaxRadius; ++p) a.cp[p - 1] = (T)(-0.5 * op->w[p]);
+    a.alpha = (T)c.alpha;
+    a.beta = (T)c.beta;
+    a.shift = (T)c.shift;
+    const bool prev = c.has_prev && yprev != nullptr;
+    const bool strm = (double)op->nd * ns * 3 * sizeof(T) > kStreamBytes;
+    GatherArgs<T, T> g;
+    std::memset(&g, 0, sizeof(g));
+    int ncb = 0, nitems = 0, ngb = 0;
+    if (part && op->natoms > 0) {
+        if ((long long)(ns + 15) / 16 > 65535) return fail(SPARC_E_SHAPE, "too many columns for one gather launch");
+        if (nt < 256) {
+            // the patch is too small to host gather items: a launch of its own
+            int st;
+            if ((st = launch_gather(op, dtype, yk, ldk, ns, part, kGatherSplit, stream))) return st;
+        } else {
+            g.Y = (const T *)yk;
+            g.ldy = ldk;
+            g.ns = ns;
+            g.nproj_total = op->nproj_total;
+            g.atoms = op->d_atoms;
+            g.small = op->nd < kUnit;
+            g.units = (const int2 *)op->d_units;
+            g.chi = std::is_same<T, double>::value ? (const T *)op->d_chiu64 : (const T *)op->d_chiu32;
+            g.part = (T *)part;
+            ncb = (ns + 15) / 16;
+            nitems = op->natoms * ncb * kGatherSplit;
+            const int per = nt / 256;
+            ngb = (nitems + per - 1) / per;
+            if ((long long)a.nblocks + ngb > 0x7fffffffLL) return fail(SPARC_E_SHAPE, "too many workgroups for one launch");
+        }
+    }
+    ProfScope prof(prev ? 0 : 3, stream);
+    const int natoms = std::max(op->natoms, 1);
+    const int rag = (VecTraits<T>::N - op->n[2] % VecTraits<T>::N) % VecTraits<T>::N;
+    const bool wide = rstep_pitch(dtype, L.tz) == (dtype == SPARC_F64 ? 108 : 176);
+#define SPARC_RSTEP(name) name(a, g, natoms, ncb, nitems, ngb, nt, nh, prev, strm, stream)
+    if constexpr (std::is_same<T, float>::value) {
+        switch (rag) {
+            case 0: return wide ? SPARC_RSTEP(rstep_f32_p176) : SPARC_RSTEP(rstep_f32_p112);
+            case 1: return wide ? SPARC_RSTEP(rstep_f32_p176_r1) : SPARC_RSTEP(rstep_f32_p112_r1);
+            case 2: return wide ? SPARC_RSTEP(rstep_f32_p176_r2) : SPARC_RSTEP(rstep_f32_p112_r2);
+            default: return wide ? SPARC_RSTEP(rstep_f32_p176_r3) : SPARC_RSTEP(rstep_f32_p112_r3);
+        }
+    } else {
+        if (rag) return wide ? SPARC_RSTEP(rstep_f64_p108_r1) : SPARC_RSTEP(rstep_f64_p44_r1);
+        return wide ? SPARC_RSTEP(rstep_f64_p108) : SPARC_RSTEP(rstep_f64_p44);
+    }
+#undef SPARC_RSTEP
 }
 
 template <typename T>
@@ -221,6 +421,11 @@ int launch_fstep(const sparc_op *op, int dtype, const FLaunch &L, const void *yk
                  int64_t ldp, void *out, int64_t ldo, int ns, void *part, const StepCoef &c, hipStream_t stream)
 {
     if (L.plan < 0) return fail(SPARC_E_ARG, "vector step not available");
+    if (L.plan == kRowPair) {
+        if (dtype == SPARC_F64)
+            return launch_rstep_t<double>(op, L, yk, ldk, yprev, ldp, out, ldo, ns, part, c, stream);
+        return launch_rstep_t<float>(op, L, yk, ldk, yprev, ldp, out, ldo, ns, part, c, stream);
+    }
     if (dtype == SPARC_F64)
         return launch_fstep_t<double>(op, L, yk, ldk, yprev, ldp, out, ldo, ns, part, c, stream);
     return launch_fstep_t<float>(op, L, yk, ldk, yprev, ldp, out, ldo, ns, part, c, stream);

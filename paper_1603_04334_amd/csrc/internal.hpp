@@ -152,12 +152,16 @@ struct FLaunch {
     int chunk_x = 0, nchunks = 0;
     int cgroup = 1;  // column blocks of one patch on consecutive workgroups
     int cblk = 1;    // columns per workgroup (1 or 2: orbital blocking)
+    int tz = 0, ty = 0;  // patch extents of the row-pair kernels (plan kRowPair)
 };
+constexpr int kRowPair = kNumPlans;  // FLaunch::plan of the row-pair kernels (rstep_kernel.hpp)
 constexpr int kMaxChunks = 16;  // most x-chunks of a vector step launch
 
 // is plan a patch height offered for dtype
 bool vec_plan_valid(int dtype, int plan);
 int vec_max_cblk(int dtype, int plan);  // columns per workgroup the plan's patch can hold (1 or 2)
+// rows and columns of whole 16-byte units (what the kernels of fstep.hip need)
+bool vec_grid(const sparc_op *op, int dtype, std::initializer_list<int64_t> lds);
 // vector launch for a block of ns columns whose leading dimensions are lds
 FLaunch choose_vec_launch(const sparc_op *op, int dtype, int ns, std::initializer_list<int64_t> lds);
 // the default x split of patch height `plan` (no tuning applied)

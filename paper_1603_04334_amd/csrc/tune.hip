@@ -39,7 +39,7 @@ void load_cache()
     double us;
     while (std::fscanf(f, "%d %d %d %d %d %d %d %d %d %d %d %lf", &n1, &n2, &n3, &na, &np, &ns, &dt, &pl, &ch, &gr, &cb,
                        &us) == 12)
-        if (pl >= 0 && pl < kNumPlans && ch > 0 && gr > 0 && (cb == 1 || cb == 2))
+        if (pl >= 0 && pl <= kRowPair && ch > 0 && gr > 0 && (cb == 1 || cb == 2))
             g_tune[Key(n1, n2, n3, na, np, ns, dt)] = {pl, ch, gr, cb, us};
     std::fclose(f);
 }
@@ -86,7 +86,7 @@ extern "C" int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *str
 {
     if (!op || ns < 1 || (dtype != SPARC_F64 && dtype != SPARC_F32)) return fail(SPARC_E_ARG, "bad arguments");
     hipStream_t s = (hipStream_t)stream;
-    if (choose_vec_launch(op, dtype, ns, {}).plan < 0)
+    if (!vec_grid(op, dtype, {}))
         return fail(SPARC_E_SHAPE, "the vector step kernels cannot take this grid (nothing to tune)");
     const Key key(op->n[0], op->n[1], op->n[2], op->natoms, op->nproj_total, ns, dtype);
     Choice best{-1, 0, 1, 1, 1e30};
@@ -114,6 +114,8 @@ extern "C" int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *str
             (void)hipFree(G);
             return fail(SPARC_E_NOMEM, "autotune scratch allocation failed");
         }
+        op->tune_shape[dtype] = -1;
+        op->tune_chunk[dtype] = op->tune_group[dtype] = op->tune_cblk[dtype] = 0;
         op->tune_ns[dtype] = ns;
         fill_scratch(dtype, X, blk, 0x9e3779b9u, s);
         fill_scratch(dtype, Pv, blk, 0x7f4a7c15u, s);
@@ -125,14 +127,18 @@ extern "C" int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *str
         const StepLaunch Ls = choose_step_launch(op, dtype, ns);
         int st = SPARC_OK;
         const int groups[] = {1, 4, 8, 16};
-        for (int p = 0; p < kNumPlans && st == SPARC_OK; ++p) {
-            if (!vec_plan_valid(dtype, p)) continue;
+        // the row-pair kernels (last plan) with their own patch, where they are
+        // the library's choice, beside every offered patch
+        const bool pairs = choose_vec_launch(op, dtype, ns, {}).plan == kRowPair;
+        for (int p = 0; p < kNumPlans + (pairs ? 1 : 0) && st == SPARC_OK; ++p) {
+            if (p < kNumPlans && !vec_plan_valid(dtype, p)) continue;
             for (int ci = 0; ci < 5 && st == SPARC_OK; ++ci) {
                 if (chunks[ci] > 0 && chunks[ci] < 4) continue;
                 for (int cb = 1; cb <= 2 && st == SPARC_OK; ++cb) {
                 for (int gi = 0; gi < 4 && st == SPARC_OK; ++gi) {
                     if (groups[gi] * cb > ns && gi > 0) continue;
-                    if (cb == 2 && (ns < 2 || vec_max_cblk(dtype, p) < 2)) continue;
+                    if (cb == 2 && (ns < 2 || p == kRowPair || vec_max_cblk(dtype, p) < 2)) continue;
+                    if (p == kRowPair && gi > 0) continue;
                     op->tune_shape[dtype] = p;
                     op->tune_chunk[dtype] = chunks[ci];
                     op->tune_group[dtype] = groups[gi];
@@ -178,8 +184,9 @@ extern "C" int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *str
     op->tune_group[dtype] = best.group;
     op->tune_cblk[dtype] = best.cblk;
     op->tune_ns[dtype] = ns;  // the choice holds for this block width only
-    if (tile_z) *tile_z = kPlanTZ[best.plan];
-    if (tile_y) *tile_y = kPlanTY[best.plan];
+    const FLaunch L = choose_vec_launch(op, dtype, ns, {});
+    if (tile_z) *tile_z = L.plan == kRowPair ? L.tz : kPlanTZ[best.plan];
+    if (tile_y) *tile_y = L.plan == kRowPair ? L.ty : kPlanTY[best.plan];
     if (chunk_x) *chunk_x = best.chunk;
     if (col_group) *col_group = best.group;
     if (col_block) *col_block = best.cblk;
