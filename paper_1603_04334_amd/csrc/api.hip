@@ -282,6 +282,7 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
         a.proj0 = op->nproj_total;
         a.chi0 = chi_total;
         const int64_t nbox = (int64_t)A.ext[0] * A.ext[1] * A.ext[2];
+        a.box0 = (int)box_total;
         box_total += nbox;
         // the gather's unit table and chi in its layout
         a.unit0 = (int)(units.size() / 2);
@@ -335,9 +336,10 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
         if ((st = build_unit_chi(op, upos, chiu_total))) return cleanup(st);
     }
 
-    // the unique covered nodes with their (atom, cube index) entries
+    // cube-node grid offsets and the unique covered nodes with their (atom, cube index) entries
     if (natoms > 0) {
         if (box_total > 0x7fffffffLL) return cleanup(fail(SPARC_E_SHAPE, "projector cubes too large"));
+        std::vector<int> boff(box_total);
         std::vector<std::pair<int64_t, std::pair<int, int>>> cover;
         cover.reserve(box_total);
         for (int J = 0; J < natoms; ++J) {
@@ -347,6 +349,7 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
                 for (int j = 0; j < a.ext[1]; ++j)
                     for (int k = 0; k < a.ext[2]; ++k, ++loc) {
                         const int64_t g = (int64_t)(a.lo[2] + k) + (int64_t)op->n[2] * ((a.lo[1] + j) + (int64_t)op->n[1] * (a.lo[0] + i));
+                        boff[a.box0 + loc] = (int)g;
                         cover.push_back({g, {J, loc}});
                     }
         }
@@ -408,7 +411,7 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
             if (hipMalloc(dst, std::max<size_t>(1, v.size()) * sizeof(int)) != hipSuccess) return false;
             return v.empty() || hipMemcpy(*dst, v.data(), v.size() * sizeof(int), hipMemcpyHostToDevice) == hipSuccess;
         };
-        if (!up(&op->d_units, units) || !up(&op->d_nl_pts, pts) || !up(&op->d_nl_off, off) || !up(&op->d_nl_ent, ent) ||
+        if (!up(&op->d_box_off, boff) || !up(&op->d_units, units) || !up(&op->d_nl_pts, pts) || !up(&op->d_nl_off, off) || !up(&op->d_nl_ent, ent) ||
             !up(&op->d_nl_blk_pt, blk_pt) || !up(&op->d_nl_blk_at, blk_at) || !up(&op->d_nl_blk_atoms, blk_atoms))
             return cleanup(fail(SPARC_E_NOMEM, "device allocation of projector tables failed"));
     }
@@ -426,6 +429,7 @@ int sparc_op_destroy(sparc_op *op)
     (void)hipFree(op->d_chi32);
     (void)hipFree(op->d_hg64);
     (void)hipFree(op->d_hg32);
+    (void)hipFree(op->d_box_off);
     (void)hipFree(op->d_units);
     (void)hipFree(op->d_chiu64);
     (void)hipFree(op->d_chiu32);

@@ -50,6 +50,7 @@ struct BatchClusterDev {
     const void *hg;
     const AtomDev *atoms;
     const int2 *units;
+    const int *box_off;
     const void *chiu;
     int small;
     const int *blk_pt, *blk_at, *blk_atoms, *pts, *ent_off;
@@ -141,7 +142,9 @@ __device__ __forceinline__ void do_gather(const BatchClusterDev &c, int k, int l
     g.atoms = c.atoms;
     g.small = c.small;
     g.units = c.units;
-    g.chi = (const T *)c.chiu;
+    g.chiu = (const T *)c.chiu;
+    g.box_off = c.box_off;
+    g.chi = (const T *)c.chi;
     g.part = (T *)c.G;
     const int atom = local / kGatherSplit, ks = local % kGatherSplit;
 #pragma unroll 1
@@ -213,7 +216,6 @@ __device__ __forceinline__ void do_scatter(const BatchClusterDev &c, int k, int 
     sa.chi = (const T *)c.chi;
     sa.hg = (const T *)c.hg;
     sa.part = (const T *)c.G;
-    sa.nparts = kGatherSplit;
     sa.alpha = (T)c.coef[3 * k];
 #pragma unroll 1
     for (int cg = 0; cg < c.ncg; ++cg) {
@@ -483,6 +485,7 @@ int sparc_batch_create(const sparc_batch_job *jobs, int32_t njobs, int32_t mode,
         c.hg = f64 ? (const void *)op->d_hg64 : (const void *)op->d_hg32;
         c.atoms = op->d_atoms;
         c.units = (const int2 *)op->d_units;
+        c.box_off = op->d_box_off;
         c.chiu = f64 ? (const void *)op->d_chiu64 : (const void *)op->d_chiu32;
         c.small = op->nd < kUnit;
         c.blk_pt = op->d_nl_blk_pt;

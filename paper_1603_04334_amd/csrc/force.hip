@@ -127,7 +127,7 @@ template <typename TI>
 __global__ void __launch_bounds__(256) force_gather_kernel(const GatherArgs<double, TI> g)
 {
     __shared__ double tile[4][16][16];
-    gather_item<double, TI>(g, blockIdx.x, blockIdx.y, blockIdx.z, tile, threadIdx.x);
+    gather_units<double, TI>(g, blockIdx.x, blockIdx.y, blockIdx.z, tile, threadIdx.x);
 }
 
 // one workgroup per atom: f[3J + d] = scale * sum_n occ[n] sum_p gamma_p S_0p(n) S_dp(n),
@@ -223,12 +223,12 @@ extern "C" int sparc_nonlocal_force(const sparc_op *op, int32_t dtype, const voi
     if (dtype == SPARC_F64) {
         GatherArgs<double, double> a{(const double *)psi, ld, ns, 4 * op->nproj_total, op->nd < kUnit, op->d_fatoms,
                                      (const int2 *)op->d_funits,
-                                     op->d_ffun, (double *)ws};
+                                     op->d_ffun, nullptr, nullptr, (double *)ws};
         hipLaunchKernelGGL(force_gather_kernel<double>, grid, dim3(256), 0, s, a);
     } else {
         GatherArgs<double, float> a{(const float *)psi, ld, ns, 4 * op->nproj_total, op->nd < kUnit, op->d_fatoms,
                                      (const int2 *)op->d_funits,
-                                    op->d_ffun, (double *)ws};
+                                    op->d_ffun, nullptr, nullptr, (double *)ws};
         hipLaunchKernelGGL(force_gather_kernel<float>, grid, dim3(256), 0, s, a);
     }
     hipLaunchKernelGGL(force_finish_kernel, dim3(op->natoms), dim3(256), 0, s, (const double *)ws,

@@ -284,7 +284,9 @@ static int launch_rstep_t(const sparc_op *op, const FLaunch &L, const void *yk, 
             g.atoms = op->d_atoms;
             g.small = op->nd < kUnit;
             g.units = (const int2 *)op->d_units;
-            g.chi = std::is_same<T, double>::value ? (const T *)op->d_chiu64 : (const T *)op->d_chiu32;
+            g.chiu = std::is_same<T, double>::value ? (const T *)op->d_chiu64 : (const T *)op->d_chiu32;
+            g.box_off = op->d_box_off;
+            g.chi = std::is_same<T, double>::value ? (const T *)op->d_chi64 : (const T *)op->d_chi32;
             g.part = (T *)part;
             ncb = (ns + 15) / 16;
             nitems = op->natoms * ncb * kGatherSplit;
@@ -371,7 +373,9 @@ static int launch_fstep_t(const sparc_op *op, const FLaunch &L, const void *yk, 
             g.atoms = op->d_atoms;
             g.small = op->nd < kUnit;
             g.units = (const int2 *)op->d_units;
-            g.chi = std::is_same<T, double>::value ? (const T *)op->d_chiu64 : (const T *)op->d_chiu32;
+            g.chiu = std::is_same<T, double>::value ? (const T *)op->d_chiu64 : (const T *)op->d_chiu32;
+            g.box_off = op->d_box_off;
+            g.chi = std::is_same<T, double>::value ? (const T *)op->d_chi64 : (const T *)op->d_chi32;
             g.part = (T *)part;
             ncb = (ns + 15) / 16;
             nitems = op->natoms * ncb * kGatherSplit;

@@ -26,6 +26,7 @@ struct AtomDev {
     int ext[3];
     int nproj;
     int proj0;        // index of the atom's first projector in the global projector list
+    int box0;         // offset of the atom's cube in the cube-node offset table
     int unit0, nunits;  // the atom's units in the gather's unit table
     long long chiu0;    // offset of its chi in unit layout (nproj * nunits units)
     long long chi0;   // offset of the atom's chi block (nproj * nbox values)
@@ -70,6 +71,7 @@ struct sparc_op {
     float *d_chi32 = nullptr;
     double *d_hg64 = nullptr;  // h^3 gamma per global projector
     float *d_hg32 = nullptr;
+    int *d_box_off = nullptr;  // grid index of every cube node (atoms back to back)
     int *d_units = nullptr;  // int2 records of the gather's units (atoms back to back)
     double *d_chiu64 = nullptr;  // chi in unit layout
     float *d_chiu32 = nullptr;

@@ -6,8 +6,8 @@
 //    as a small dense GEMM on the matrix cores, S_J^T (ns x nproj) =
 //    Y_cube^T (ns x nbox) * chi_J (nbox x nproj), using
 //    v_mfma_f64_16x16x4f64 (FP64) or v_mfma_f32_16x16x4f32 (FP32).  The cube is
-//    read as units of 4 nodes along z, 16 bytes of FP32 per lane, four matrix
-//    instructions per load; the units (the K dimension) are cut into 4
+//    read (for FP32 blocks) as units of 4 nodes along z, 16 bytes per lane, four
+//    matrix instructions per load; the units (the K dimension) are cut into 4
 //    kGatherSplit segments of one wave each.  Either kGatherSplit workgroups
 //    share an atom and 16 columns and leave partial 16 x nproj tiles that the
 //    consumer sums in split order, or one workgroup sums them itself in the
@@ -55,11 +55,11 @@ __global__ void __launch_bounds__(256) gather_whole_kernel(const GatherArgs<T, T
 }
 
 // table in dynamic LDS: [block's atoms][npm][NC]
-template <typename T, int NC>
+template <typename T, int NC, int NP>
 __global__ void __launch_bounds__(256) scatter_kernel(const ScatterArgs<T> s, int npm)
 {
     extern __shared__ __align__(16) char scatter_lds[];
-    scatter_item<T, NC>(s, blockIdx.x, blockIdx.y, (T *)scatter_lds, npm);
+    scatter_item<T, NC, NP>(s, blockIdx.x, blockIdx.y, (T *)scatter_lds, npm);
 }
 
 // blockIdx.x: atom; its nodes' places from pos + (cube nodes of the atoms before it)
@@ -109,7 +109,7 @@ bool gather_wide(const sparc_op *op, int ns)
 
 template <typename T, typename TI = T>
 static int launch_gather_t(const sparc_op *op, const void *Y, int64_t ldy, int ns, void *part, int nparts,
-                           hipStream_t stream, const T *chi)
+                           hipStream_t stream, const T *chi, const T *chiu)
 {
     GatherArgs<T, TI> a;
     a.Y = (const TI *)Y;
@@ -119,6 +119,8 @@ static int launch_gather_t(const sparc_op *op, const void *Y, int64_t ldy, int n
     a.small = op->nd < kUnit;
     a.atoms = op->d_atoms;
     a.units = (const int2 *)op->d_units;
+    a.chiu = chiu;
+    a.box_off = op->d_box_off;
     a.chi = chi;
     a.part = (T *)part;
     const unsigned ncb = (unsigned)(ns + 15) / 16;
@@ -140,7 +142,7 @@ int launch_gather_f32_to_f64(const sparc_op *op, const float *Y, int64_t ldy, in
 {
     if (op->natoms == 0) return SPARC_OK;
     if ((long long)(ns + 15) / 16 > 65535) return fail(SPARC_E_SHAPE, "too many columns for one gather launch");
-    return launch_gather_t<double, float>(op, Y, ldy, ns, part, nparts, stream, op->d_chiu64);
+    return launch_gather_t<double, float>(op, Y, ldy, ns, part, nparts, stream, op->d_chi64, op->d_chiu64);
 }
 
 int launch_gather(const sparc_op *op, int dtype, const void *Y, int64_t ldy, int ns, void *part, int nparts,
@@ -148,8 +150,8 @@ int launch_gather(const sparc_op *op, int dtype, const void *Y, int64_t ldy, int
 {
     if (op->natoms == 0) return SPARC_OK;
     if ((long long)(ns + 15) / 16 > 65535) return fail(SPARC_E_SHAPE, "too many columns for one gather launch");
-    if (dtype == SPARC_F64) return launch_gather_t<double>(op, Y, ldy, ns, part, nparts, stream, op->d_chiu64);
-    return launch_gather_t<float>(op, Y, ldy, ns, part, nparts, stream, op->d_chiu32);
+    if (dtype == SPARC_F64) return launch_gather_t<double>(op, Y, ldy, ns, part, nparts, stream, op->d_chi64, op->d_chiu64);
+    return launch_gather_t<float>(op, Y, ldy, ns, part, nparts, stream, op->d_chi32, op->d_chiu32);
 }
 
 template <typename T>
@@ -171,7 +173,6 @@ static int launch_scatter_t(const sparc_op *op, void *out, int64_t ldo, int ns, 
     a.chi = chi;
     a.hg = hg;
     a.part = (const T *)part;
-    a.nparts = nparts;
     a.alpha = (T)alpha;
     // columns per workgroup: FP32 blocks take 32 when the table fits in 32
     // KiB of LDS (a quarter of the chi and table reads of 8 columns, same
@@ -184,10 +185,19 @@ static int launch_scatter_t(const sparc_op *op, void *out, int64_t ldo, int ns, 
     if ((ns + nc - 1) / nc > 65535) return fail(SPARC_E_SHAPE, "too many columns for one scatter launch");
     dim3 grid(op->nl_nblk, (ns + nc - 1) / nc);
     ProfScope prof(2, stream);
-    if (wide && NW != kScatterCols)
-        hipLaunchKernelGGL((scatter_kernel<T, NW>), grid, dim3(256), row * NW, stream, a, npm);
-    else
-        hipLaunchKernelGGL((scatter_kernel<T, kScatterCols>), grid, dim3(256), row * kScatterCols, stream, a, npm);
+    const size_t lds = row * nc;
+    if constexpr (NW != kScatterCols) {
+        if (wide && nparts == 1)
+            hipLaunchKernelGGL((scatter_kernel<T, NW, 1>), grid, dim3(256), lds, stream, a, npm);
+        else if (wide)
+            hipLaunchKernelGGL((scatter_kernel<T, NW, kGatherSplit>), grid, dim3(256), lds, stream, a, npm);
+    }
+    if (NW == kScatterCols || !wide) {
+        if (nparts == 1)
+            hipLaunchKernelGGL((scatter_kernel<T, kScatterCols, 1>), grid, dim3(256), lds, stream, a, npm);
+        else
+            hipLaunchKernelGGL((scatter_kernel<T, kScatterCols, kGatherSplit>), grid, dim3(256), lds, stream, a, npm);
+    }
     SPARC_HIP(hipGetLastError());
     return SPARC_OK;
 }

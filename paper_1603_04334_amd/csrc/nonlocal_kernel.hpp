@@ -22,7 +22,9 @@ struct GatherArgs {
     int small;           // fewer than kUnit grid nodes: Y is read node by node
     const AtomDev *atoms;
     const int2 *units;   // per atom from atom.unit0
-    const T *chi;        // per atom from atom.chiu0: [projector][unit][kUnit], zero off the cube
+    const T *chiu;       // per atom from atom.chiu0: [projector][unit][kUnit], zero off the cube
+    const int *box_off;  // grid index of every cube node, per atom from atom.box0
+    const T *chi;        // per atom from atom.chi0: [projector][cube node]
     T *part;             // [kGatherSplit (1: gather_whole_kernel)][nproj_total][ns] projections
 };
 
@@ -112,7 +114,7 @@ __device__ __forceinline__ void gather_accum(const GatherArgs<T, TI> &g, const T
 // together (more take registers, so waves in flight: 96^3 x 64 FP64 with 16
 // cubes 13.0 us with 2, 14.4 with 4, 16.0 with 8; FP32 9.8, 10.7, 11.2)
 template <typename T, typename TI = T>
-__device__ __forceinline__ void gather_item(const GatherArgs<T, TI> &g, int atom, int cb, int ks, T (*tile)[16][16],
+__device__ __forceinline__ void gather_units(const GatherArgs<T, TI> &g, int atom, int cb, int ks, T (*tile)[16][16],
                                             int tid)
 {
     const int c0 = cb * 16;
@@ -126,7 +128,7 @@ __device__ __forceinline__ void gather_item(const GatherArgs<T, TI> &g, int atom
     const int u0 = min(A.nunits, (4 * ks + wave) * seg), u1 = min(A.nunits, u0 + seg);
     T acc[4] = {T(0), T(0), T(0), T(0)};
     gather_accum<T, TI, 2>(g, g.Y + (long long)(col_ok ? col : 0) * g.ldy,
-                           g.chi + A.chiu0 + (long long)(i < A.nproj ? i : 0) * A.nunits * kUnit, g.units + A.unit0, u0,
+                           g.chiu + A.chiu0 + (long long)(i < A.nproj ? i : 0) * A.nunits * kUnit, g.units + A.unit0, u0,
                            u1, col_ok, lane >> 4, acc);
 #pragma unroll
     for (int r = 0; r < 4; ++r) tile[wave][acc_row<T>(lane, r)][lane & 15] = acc[r];
@@ -137,6 +139,82 @@ __device__ __forceinline__ void gather_item(const GatherArgs<T, TI> &g, int atom
         const T s = ((tile[0][row][pj] + tile[1][row][pj]) + tile[2][row][pj]) + tile[3][row][pj];
         g.part[((long long)ks * g.nproj_total + A.proj0 + pj) * g.ns + cc] = s;
     }
+}
+
+constexpr int kGatherUnroll = 8;  // groups of 4 points per wave per batch
+
+// One split of an atom's cube node by node (FP64 blocks).  An FP64 node is half
+// of a 16-byte load already, and units of 4 would pad the rows of 14 to 15
+// nodes by a quarter more matrix instructions, which are on the critical path
+// of the small FP64 launches: by units a filter step of 48^3 x 11 took 17.7
+// instead of 17.0 us, H of one 148 x 132 x 145 column 32.6 instead of 31.1 us;
+// 96^3 x 64 the same 13 us.
+// tid: this thread's index within the 256 threads (4 waves) that run the
+// item; the item has one workgroup barrier
+template <typename T, typename TI = T>
+__device__ __forceinline__ void gather_nodes(const GatherArgs<T, TI> &g, int atom, int cb, int ks, T (*tile)[16][16],
+                                            int tid)
+{
+    const int c0 = cb * 16;
+    const AtomDev A = g.atoms[atom];
+    const int nbox = A.ext[0] * A.ext[1] * A.ext[2];
+    const int chunk = (nbox + kGatherSplit - 1) / kGatherSplit;
+    const int k0 = min(nbox, ks * chunk);
+    const int k1 = min(nbox, k0 + chunk);
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int i = lane & 15;
+    const int k = lane >> 4;
+    const int col = c0 + i;
+    const bool col_ok = col < g.ns;
+    const bool proj_ok = i < A.nproj;
+    const TI *y = g.Y + (long long)(col_ok ? col : 0) * g.ldy;
+    const T *ch = g.chi + A.chi0 + (long long)(proj_ok ? i : 0) * nbox;
+    const int *boff = g.box_off + A.box0;
+
+    T acc[4] = {T(0), T(0), T(0), T(0)};
+    constexpr int BATCH = 4 * kGatherUnroll;
+    for (int base = k0 + wave * BATCH; base < k1; base += 4 * BATCH) {
+        int off[kGatherUnroll];
+        T av[kGatherUnroll], bv[kGatherUnroll];
+#pragma unroll
+        for (int u = 0; u < kGatherUnroll; ++u) {
+            const int pt = base + 4 * u + k;
+            off[u] = boff[pt < k1 ? pt : k0];
+        }
+#pragma unroll
+        for (int u = 0; u < kGatherUnroll; ++u) {
+            const int pt = base + 4 * u + k;
+            const bool ok = pt < k1;
+            const T yv = (T)y[off[u]];
+            const T cv = ch[ok ? pt : k0];
+            av[u] = (ok && col_ok) ? yv : T(0);
+            bv[u] = (ok && proj_ok) ? cv : T(0);
+        }
+#pragma unroll
+        for (int u = 0; u < kGatherUnroll; ++u) mfma_16x16x4(av[u], bv[u], acc);
+    }
+
+#pragma unroll
+    for (int r = 0; r < 4; ++r) tile[wave][acc_row<T>(lane, r)][lane & 15] = acc[r];
+    __syncthreads();
+    const int row = tid >> 4, pj = tid & 15;
+    const int cc = c0 + row;
+    if (cc < g.ns && pj < A.nproj) {
+        const T s = ((tile[0][row][pj] + tile[1][row][pj]) + tile[2][row][pj]) + tile[3][row][pj];
+        g.part[((long long)ks * g.nproj_total + A.proj0 + pj) * g.ns + cc] = s;
+    }
+}
+
+// one item of the gather: FP32 storage by units, FP64 node by node
+template <typename T, typename TI = T>
+__device__ __forceinline__ void gather_item(const GatherArgs<T, TI> &g, int atom, int cb, int ks, T (*tile)[16][16],
+                                            int tid)
+{
+    if constexpr (sizeof(TI) == 4)
+        gather_units<T, TI>(g, atom, cb, ks, tile, tid);
+    else
+        gather_nodes<T, TI>(g, atom, cb, ks, tile, tid);
 }
 
 // all kGatherSplit items of (atom, cb) in one 256-thread workgroup, their
@@ -153,7 +231,7 @@ __device__ __forceinline__ void gather_whole(const GatherArgs<T, TI> &g, int ato
     const int col = c0 + i;
     const bool col_ok = col < g.ns;
     const TI *y = g.Y + (long long)(col_ok ? col : 0) * g.ldy;
-    const T *ch = g.chi + A.chiu0 + (long long)(i < A.nproj ? i : 0) * A.nunits * kUnit;
+    const T *ch = g.chiu + A.chiu0 + (long long)(i < A.nproj ? i : 0) * A.nunits * kUnit;
     const int row = tid >> 4, pj = tid & 15;
     T s = T(0);
 #pragma unroll 1
@@ -192,18 +270,18 @@ struct ScatterArgs {
     const AtomDev *atoms;
     const T *chi;
     const T *hg;           // h^3 gamma per global projector
-    const T *part;         // [nparts][nproj_total][ns]
-    int nparts;            // kGatherSplit, or 1: finished projections
+    const T *part;         // [NP][nproj_total][ns]
     T alpha;
 };
 
-// One node block b (at most 256 nodes) and NC columns from cg * NC.  gl: the
+// One node block b (at most 256 nodes) and NC columns from cg * NC.  NP: parts
+// of the projections (kGatherSplit, or 1: finished).  gl: the
 // block's table h^3 gamma S, [slot][npm][NC] (npm >= every atom's projector
 // count).  The out values of all NC columns are requested before the table
 // is built, so their latency overlaps it.  Per node and column the sum runs
 // over the node's entries and projectors in table order whatever NC is, so
 // every column count gives the same bits.
-template <typename T, int NC>
+template <typename T, int NC, int NP = kGatherSplit>
 __device__ __forceinline__ void scatter_item(const ScatterArgs<T> &s, int b, int cg, T *gl, int npm)
 {
     const int c0 = cg * NC;
@@ -233,12 +311,8 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs<T> &s, int b, int
         if (p < A.nproj && c0 + cc < s.ns) {
             const long long pg = A.proj0 + p;
             T sum = T(0);
-            if (s.nparts == 1) {
-                sum = s.part[pg * s.ns + c0 + cc];
-            } else {
 #pragma unroll
-                for (int q = 0; q < kGatherSplit; ++q) sum += s.part[q * split + pg * s.ns + c0 + cc];
-            }
+            for (int q = 0; q < NP; ++q) sum += s.part[q * split + pg * s.ns + c0 + cc];
             v = s.hg[pg] * sum;
         }
         gl[idx] = v;

@@ -196,7 +196,9 @@ int launch_lanczos_h_f64(const sparc_op *op, const double *v, double *out, doubl
     g.atoms = op->d_atoms;
     g.small = op->nd < kUnit;
     g.units = (const int2 *)op->d_units;
-    g.chi = op->d_chiu64;
+    g.chiu = op->d_chiu64;
+    g.box_off = op->d_box_off;
+    g.chi = op->d_chi64;
     g.part = part;
     const int ngather = op->natoms * kGatherSplit;
     ProfScope prof(3, stream);

@@ -113,7 +113,7 @@ inline int launch_typed(const StepArgs<T, TI> &a, bool prev, bool strm, hipStrea
 template <typename T, typename TI = T>
 int launch_step_t(const sparc_op *op, const void *yk, int64_t ldk, const void *yprev, int64_t ldp,
                          void *out, int64_t ldo, int ns, const StepCoef &c, const StepLaunch &L,
-                         hipStream_t stream, const T *veff, void *part = nullptr, const T *chi = nullptr)
+                         hipStream_t stream, const T *veff, void *part = nullptr, const T *chi = nullptr, const T *chiu = nullptr)
 {
     const TileShape &s = kShapes[L.shape];
     StepArgs<T, TI> a;
@@ -154,6 +154,8 @@ int launch_step_t(const sparc_op *op, const void *yk, int64_t ldk, const void *y
         gp.g.atoms = op->d_atoms;
         gp.g.small = op->nd < kUnit;
         gp.g.units = (const int2 *)op->d_units;
+        gp.g.box_off = op->d_box_off;
+        gp.g.chiu = chiu;
         gp.g.chi = chi;
         gp.g.part = (T *)part;
         gp.natoms = op->natoms;
