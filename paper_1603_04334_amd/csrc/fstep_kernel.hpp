@@ -54,9 +54,31 @@ struct FStepArgs {
     T alpha, beta, shift;
 };
 
+// the unit as loaded, at its place: a unit cut RAG nodes short by the end of
+// its row (c) was loaded from RAG nodes further back and is moved up, zeros
+// past the row end
+template <typename T, int RAG>
+__device__ __forceinline__ typename VecTraits<T>::V place_unit(const typename VecTraits<T>::V &v, bool c)
+{
+    constexpr int VZ = VecTraits<T>::N;
+    if constexpr (RAG == 0) return v;
+    typename VecTraits<T>::V r;
+#pragma unroll
+    for (int j = 0; j < VZ; ++j) {
+        T m = T(0);
+        if constexpr (RAG > 0)
+            if (j + RAG < VZ) m = v[(j + RAG) % VZ];
+        r[j] = c ? m : v[j];
+    }
+    return r;
+}
+
+// POT = false: no potential (V_eff = shift = 0).  DOT: each lane sums yk(x)
+// out(x) over its nodes (dacc).  RAG: see place_unit (one column only).
 // B: columns per workgroup.  With B = 2 the two columns of one patch share
 // the V_eff loads, the halo offsets and the plane loop (orbital blocking).
-template <typename T, int TY, bool PREV, bool STREAM, int B = 1, int TZ = kFTZ>
+template <typename T, int TY, bool PREV, bool STREAM, int B = 1, int TZ = kFTZ, bool POT = true, bool DOT = false,
+          int RAG = 0>
 struct FStep {
     static constexpr int R = kMaxRadius;
     static constexpr int VZ = VecTraits<T>::N;
@@ -78,6 +100,7 @@ struct FStep {
     static_assert(VZ == 1 || ((PADZ - R) % (VZ / 2) == 0 && (PADZ + VZ + R) % (VZ / 2) == 0),
                   "z window edges must fall on half units");
     static_assert(B == 1 || B == 2, "one or two columns per workgroup");
+    static_assert(RAG == 0 || (B == 1 && !PREV), "cut rows: one column without Y_{k-1}");
 
     struct Shared {
         T plane[2][B][SY * SZ];
@@ -93,6 +116,8 @@ struct FStep {
     unsigned sofs[B];   // store offset per column (kOutside for a column past the block)
     unsigned hofs[NH];  // halo units: in-plane byte offsets, or kOutside
     int hl[NH];         // halo units: LDS element index, or -1
+    bool cut, hcut[NH]; // RAG: the lane's unit (halo unit) is cut by the row end
+    T dacc = T(0);      // DOT
     V q[B][QL];  // per column, the lane's unit at planes x-R .. x+R (one vector per plane)
     // the two load stages (values for one plane: its halo, the queue head at
     // plane t+R, V_eff and yprev at the lane's unit), one named member per
@@ -129,7 +154,7 @@ struct FStep {
             for (int i = 0; i < NH; ++i) s.h[b][i] = vload<T, 0>(rk, hofs[i]);
             s.qh[b] = vload<T, 0>(plane_rsrc(yk[b], t + R, a.n1, P), pofs);
         }
-        s.v = vload<T, 0>(plane_rsrc(a.veff, t, a.n1, P), pofs);
+        if constexpr (POT) s.v = vload<T, 0>(plane_rsrc(a.veff, t, a.n1, P), pofs);
         if constexpr (PREV) {
 #pragma unroll
             for (int b = 0; b < B; ++b) s.p[b] = vload<T, STREAM ? kNonTemporal : 0>(plane_rsrc(yp[b], t, a.n1, P), pofs);
@@ -143,15 +168,16 @@ struct FStep {
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             T *L = sh.plane[S][b];
-            q[b][slot<Q>(2 * R)] = stage<S>().qh[b];
+            q[b][slot<Q>(2 * R)] = place_unit<T, RAG>(stage<S>().qh[b], cut);
             *(V *)&L[(R + ly) * SZ + PADZ + VZ * lz] = q[b][slot<Q>(R)];
 #pragma unroll
             for (int i = 0; i < NH; ++i)
-                if (hl[i] >= 0) *(V *)&L[hl[i]] = stage<S>().h[b][i];
+                if (hl[i] >= 0) *(V *)&L[hl[i]] = place_unit<T, RAG>(stage<S>().h[b][i], hcut[i]);
         }
         __syncthreads();
 
-        const V vv = stage<S>().v;
+        V vv;
+        if constexpr (POT) vv = place_unit<T, RAG>(stage<S>().v, cut);
         V pv[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) pv[b] = PREV ? stage<S>().p[b] : V{};
@@ -203,8 +229,10 @@ struct FStep {
                     acc[j] += a.cp[p - 1] * six;
                 }
             }
+            if constexpr (POT) {
 #pragma unroll
-            for (int j = 0; j < VZ; ++j) acc[j] += (vv[j] - a.shift) * cen[j];
+                for (int j = 0; j < VZ; ++j) acc[j] += (vv[j] - a.shift) * cen[j];
+            }
 
             V rv;
 #pragma unroll
@@ -212,9 +240,17 @@ struct FStep {
                 T r = a.alpha * acc[j];
                 if constexpr (PREV) r -= a.beta * pv[b][j];
                 rv[j] = r;
+                if constexpr (DOT) dacc += cen[j] * r;  // cen is zero off the grid
             }
             // written once; units outside the grid are dropped by the range check
-            vstore<T, STREAM ? kNonTemporal : 0>(rv, plane_rsrc((const T *)out[b], x, a.n1, P), sofs[b]);
+            const auto ro = plane_rsrc((const T *)out[b], x, a.n1, P);
+            if (RAG > 0 && cut) {
+#pragma unroll
+                for (int j = 0; j + RAG < VZ; ++j)
+                    buf_store<T, STREAM ? kNonTemporal : 0>(rv[j], ro, sofs[b] + (j + RAG) * (unsigned)sizeof(T));
+            } else {
+                vstore<T, STREAM ? kNonTemporal : 0>(rv, ro, sofs[b]);
+            }
         }
     }
 
@@ -254,7 +290,8 @@ struct FStep {
         zg = z0 + VZ * lz;
         P = (long long)a.n2 * a.n3;
         const bool own_ok = (zg < a.n3) && (y < a.n2);
-        pofs = own_ok ? (unsigned)(y * a.n3 + zg) * (unsigned)sizeof(T) : kOutside;
+        cut = RAG > 0 && own_ok && zg + VZ > a.n3;
+        pofs = own_ok ? (unsigned)(y * a.n3 + zg - (cut ? RAG : 0)) * (unsigned)sizeof(T) : kOutside;
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             // a column past the block repeats the last one and stores nothing
@@ -289,14 +326,16 @@ struct FStep {
             hl[i] = lrow >= 0 ? lrow * SZ + lcol : -1;
             const int gy = y0 - R + lrow, gz = z0 - PADZ + lcol;
             const bool hok = lrow >= 0 && gy >= 0 && gy < a.n2 && gz >= 0 && gz < a.n3;
-            hofs[i] = hok ? (unsigned)(gy * a.n3 + gz) * (unsigned)sizeof(T) : kOutside;
+            hcut[i] = RAG > 0 && hok && gz + VZ > a.n3;
+            hofs[i] = hok ? (unsigned)(gy * a.n3 + gz - (hcut[i] ? RAG : 0)) * (unsigned)sizeof(T) : kOutside;
         }
 
         // queue: planes xs-R .. xs+R-1 (heads are filled from the stages)
 #pragma unroll
         for (int b = 0; b < B; ++b)
 #pragma unroll
-            for (int d = 0; d < 2 * R; ++d) q[b][d] = vload<T, 0>(plane_rsrc(yk[b], xs - R + d, a.n1, P), pofs);
+            for (int d = 0; d < 2 * R; ++d) 
+                q[b][d] = place_unit<T, RAG>(vload<T, 0>(plane_rsrc(yk[b], xs - R + d, a.n1, P), pofs), cut);
         load_stage<0>(xs);
         load_stage<1>(xs + 1);
         for (int x0 = xs; x0 < xe; x0 += 2 * QL) run_block<0>(x0, xe, sh);

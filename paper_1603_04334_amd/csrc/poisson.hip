@@ -14,17 +14,23 @@
 //    nodes one axis step off a face are ever read by the stencil);
 //  * right-hand side c - d, with d from the slabs, and the partial sums of
 //    its square;
-//  * CG iteration: q = A p through the fused stencil kernel of H on a
-//    zero-potential operator (A = (1/2 pi) (-1/2 lap_h)), then p.q, then one
-//    kernel that updates x and r, multiplies each block of r by the inverse of
-//    A restricted to the block (a dense symmetric matrix, one per block shape,
-//    kept in L2; blocks are taken in bricks along z so that global accesses
-//    are coalesced rows) and forms the partials of r.z and r.r, then the
-//    update of p.  Scalars never leave the device: every
-//    workgroup finishes the partial sums it needs in the same fixed order, so
-//    alpha, beta and the convergence test are bitwise the same everywhere.
-//    The host enqueues iterations in chunks and reads one flag per chunk;
-//    kernels after convergence return at once.
+//  * CG iteration, three launches: q = A p with the partial sums of p.q (the
+//    stencil kernel of poisson_step.hip on vectors without a potential; A =
+//    (1/2 pi) (-1/2 lap_h)); r -= alpha q, z = M^-1 r per block and the
+//    partials of r.z and r.r; x += alpha p, the convergence test and
+//    p = z + beta p.  Scalars never leave the device: every workgroup finishes
+//    the partial sums it needs in the same fixed order, so alpha, beta and the
+//    convergence test are bitwise the same everywhere.  The host enqueues
+//    iterations in chunks and reads one flag per chunk; kernels of iterations
+//    after the converged one return at once.
+//  * block Jacobi, each block's operator inverted exactly: blocks of 4 x 4 x 4
+//    nodes in the eigenbasis of their axes (bj_diag_kernel), other block shapes
+//    by a dense symmetric inverse per shape, in bricks along z so that global
+//    accesses are coalesced rows (bj_kernel).
+//  What bounds it: 11 passes of 8 N_d bytes per iteration (14 with p.q and the
+//  x update in passes of their own): 160^3 138 -> 80 us per iteration, 361 MB at
+//  4.5 TB/s; 96^3 57 -> 33 us; 49 x 44 x 41 33 -> 27 us, launches and their
+//  latency.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -46,10 +52,17 @@ struct HarmNorm {
     double c[kNM];
 };
 
+// device-side state: the iteration that reached the tolerance (-1: the start,
+// kNotDone: none yet), and the scalars handed from launch to launch, one slot
+// per parity of the iteration (a launch reads the slot of its own iteration and
+// writes the other's)
+constexpr int kNotDone = 0x7fffffff;
 struct PcgState {
     int done;
     int iters;
     double rr, bb;
+    double rz[2];  // r.z at the start of an iteration
+    double alpha;
 };
 
 // regular solid harmonics R_lm(x) = |x|^l Y_lm(x/|x|), index l*l + l + m:
@@ -115,6 +128,26 @@ __device__ __forceinline__ double sum_partials(const double *part, int n, double
     return block_sum(v, red);
 }
 
+// two such sums with one pair of barriers
+__device__ __forceinline__ void sum_partials2(const double *a, const double *b, int n, double (&red)[8], double &sa,
+                                              double &sb)
+{
+    double v = 0.0, w = 0.0;
+    for (int i = threadIdx.x; i < n; i += kPT) {
+        v += a[i];
+        w += b[i];
+    }
+    v = wave_sum(v);
+    w = wave_sum(w);
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = v;
+        red[4 + (threadIdx.x >> 6)] = w;
+    }
+    __syncthreads();
+    sa = (red[0] + red[1]) + (red[2] + red[3]);
+    sb = (red[4] + red[5]) + (red[6] + red[7]);
+}
+
 struct GridGeo {
     int n0, n1, n2;
     long long nd;
@@ -169,6 +202,7 @@ __global__ void __launch_bounds__(kPT) moments_finish(const double *__restrict__
     const int q = threadIdx.x;
     if (q >= kNM) return;
     double v = 0.0;
+#pragma unroll 16
     for (int b = 0; b < nparts; ++b) v += partial[(long long)b * kNM + q];
     const int l = (int)sqrtf((float)q + 0.5f);
     Q[q] = l <= lmax ? h3 * v : 0.0;
@@ -300,14 +334,13 @@ __device__ __forceinline__ int bj_shape(const BjGeo &q, int bi, int bj, int bk, 
 // `row` of M^-1 r for block `slot` (sum over j ascending; the interior
 // blocks' inverse read from LDS), and the result goes back through LDS to the
 // brick order for the coalesced store.
-// UPDATE: alpha = rz_old / pq, x += alpha p, r -= alpha q; both modes:
-// z = M^-1 r per block, p = z (INIT only), partials of r.z and r.r
+// UPDATE: alpha = rz / pq, r -= alpha q; both modes: z = M^-1 r per block,
+// p = z (INIT only), partials of r.z and r.r
 template <bool UPDATE>
 __global__ void __launch_bounds__(kPT)
-    bj_kernel(const BjGeo q, const double *__restrict__ minv, double *__restrict__ x, double *__restrict__ r,
-              double *__restrict__ p, const double *__restrict__ qv, double *__restrict__ z,
-              const double *__restrict__ part_rz_old, int n_rz_old, const double *__restrict__ part_pq, int n_pq,
-              double *__restrict__ part_rz, double *__restrict__ part_rr, const PcgState *__restrict__ state)
+    bj_kernel(const BjGeo q, const double *__restrict__ minv, double *__restrict__ r, double *__restrict__ p,
+              const double *__restrict__ qv, double *__restrict__ z, const double *__restrict__ part_pq, int n_pq,
+              double *__restrict__ part_rz, double *__restrict__ part_rr, int iter, PcgState *__restrict__ state)
 {
     __shared__ double red[4];
     __shared__ double rs[kPT];
@@ -316,12 +349,15 @@ __global__ void __launch_bounds__(kPT)
     // every interior block, staged once per workgroup (blocks of at most
     // kBjStage nodes)
     __shared__ double sM[kBjStage * kBjStage];
-    if (UPDATE && state->done) return;
+    if (UPDATE && state->done < iter) return;
     const bool staged = q.maxm <= kBjStage;
     if (staged)
         for (int e = threadIdx.x; e < q.maxm * q.maxm; e += kPT) sM[e] = minv[e];
     double alpha = 0.0;
-    if (UPDATE) alpha = sum_partials(part_rz_old, n_rz_old, red) / sum_partials(part_pq, n_pq, red);
+    if (UPDATE) {
+        alpha = state->rz[iter & 1] / sum_partials(part_pq, n_pq, red);
+        if (blockIdx.x == 0 && threadIdx.x == 0) state->alpha = alpha;
+    }
     const int G = kPT / q.maxm;          // blocks per brick
     const int bpr = (q.nb[2] + G - 1) / G;  // bricks per (block x, block y) row
     const long long nbricks = (long long)q.nb[0] * q.nb[1] * bpr;
@@ -351,7 +387,6 @@ __global__ void __launch_bounds__(kPT)
         double rv = 0.0;
         if (act) {
             if (UPDATE) {
-                x[node] += alpha * p[node];
                 rv = r[node] - alpha * qv[node];
                 r[node] = rv;
             } else {
@@ -398,62 +433,274 @@ __global__ void __launch_bounds__(kPT)
     }
 }
 
+// Block-Jacobi step for blocks of 4 x 4 x 4 nodes in the eigenbasis of the
+// block.  A restricted to a box of nodes is the sum of one small matrix per
+// axis, T_x + T_y + T_z (Kronecker sum), T_m the m x m corner of the banded 1D
+// operator; with T_m = U_m diag(l) U_m^T its inverse is three 4 x 4 products
+// along the axes, a division by l_x + l_y + l_z and the three transposed
+// products: 24 multiply-adds per node instead of the 64 of the dense inverse.
+// Blocks cut short use the U_m of their extents, padded with zeros.
+//
+// Four lanes own a block, lane a its plane x = a (16 nodes); the x products
+// exchange values within the quad of lanes (DPP), nothing goes through LDS but
+// the tables.  Consecutive quads take blocks that follow each other along z,
+// so a wave reads and writes rows of 512 bytes.
+// What bounds it: r, q in, r, z out, 32 bytes per node (4.5 TB/s at 160^3).  Per
+// application, 160^3: 29 us; dense inverses from LDS 75 us (with the x update,
+// now in xp_update_kernel), dense inverses on the matrix cores 40 us; 96^3 11
+// and 19 us.  Two waves per SIMD hold the 208 registers; at three or four the
+// products spill (94 and 97 instead of 80 us per CG iteration).
+constexpr int kDiagTab = 5 * 20;  // per m = 0..4: U_m (16 values, row i, column of the eigenvector j at 4 i + j), l (4)
+
+// the value of quad lane J in every lane of the quad
+template <int J>
+__device__ __forceinline__ double quad_bcast(double v)
+{
+    constexpr int ctrl = J | (J << 2) | (J << 4) | (J << 6);
+    union {
+        double d;
+        int i[2];
+    } u;
+    u.d = v;
+    u.i[0] = __builtin_amdgcn_mov_dpp(u.i[0], ctrl, 0xf, 0xf, true);
+    u.i[1] = __builtin_amdgcn_mov_dpp(u.i[1], ctrl, 0xf, 0xf, true);
+    return u.d;
+}
+
+// v <- sum_j c[j] (v of quad lane j)
+__device__ __forceinline__ void quad_product(double (&v)[4][4], const double (&c)[4])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double x = v[i][k];
+            v[i][k] = c[0] * quad_bcast<0>(x) + c[1] * quad_bcast<1>(x) + c[2] * quad_bcast<2>(x) +
+                      c[3] * quad_bcast<3>(x);
+        }
+}
+
+// along z (ROW) or y of the lane's plane: v <- U^T v (FWD) or U v
+template <bool ROW, bool FWD>
+__device__ __forceinline__ void axis_product(double (&v)[4][4], const double *U)
+{
+    // keep the tables in LDS between products (registers decide the waves in flight)
+    asm volatile("" ::: "memory");
+    double u[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) u[e] = U[e];
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {
+        double x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = ROW ? v[o][i] : v[i][o];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            double t = 0.0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) t += (FWD ? u[4 * i + j] : u[4 * j + i]) * x[i];
+            if (ROW)
+                v[o][j] = t;
+            else
+                v[j][o] = t;
+        }
+    }
+}
+
+// dinv: 1 / (l_x + l_y + l_z) per extents (m_x, m_y, m_z) = 1..4 each, [64][a][b][c]
+template <bool UPDATE>
+__global__ void __launch_bounds__(kPT, 2)
+    bj_diag_kernel(const BjGeo q, const double *__restrict__ tab, const double *__restrict__ dinv,
+                   double *__restrict__ r, double *__restrict__ p, const double *__restrict__ qv,
+                   double *__restrict__ z, const double *__restrict__ part_pq, int n_pq, double *__restrict__ part_rz,
+                   double *__restrict__ part_rr, int iter, PcgState *__restrict__ state)
+{
+    typedef double V4 __attribute__((ext_vector_type(4), aligned(8)));
+    __shared__ double red[4];
+    __shared__ double sU[kDiagTab];
+    if (UPDATE && state->done < iter) return;
+    if (threadIdx.x < kDiagTab) sU[threadIdx.x] = tab[threadIdx.x];
+    double alpha = 0.0;
+    if (UPDATE) {
+        alpha = state->rz[iter & 1] / sum_partials(part_pq, n_pq, red);
+        if (blockIdx.x == 0 && threadIdx.x == 0) state->alpha = alpha;
+    } else {
+        __syncthreads();
+    }
+    const int a = threadIdx.x & 3;
+    double arz = 0.0, arr = 0.0;
+    for (long long blk = (blockIdx.x * (long long)kPT + threadIdx.x) >> 2; blk < q.nblocks;
+         blk += (long long)gridDim.x * (kPT / 4)) {
+        const int bk = (int)(blk % q.nb[2]);
+        const long long u = blk / q.nb[2];
+        const int bj = (int)(u % q.nb[1]), bi = (int)(u / q.nb[1]);
+        const int mx = bi == q.nb[0] - 1 ? q.last[0] : 4;
+        const int my = bj == q.nb[1] - 1 ? q.last[1] : 4;
+        const int mz = bk == q.nb[2] - 1 ? q.last[2] : 4;
+        const long long n0 = ((long long)(4 * bi + a) * q.n1 + 4 * bj) * q.n2 + 4 * bk;
+        const bool whole = a < mx && mz == 4;
+        double v[4][4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[b][c] = 0.0;
+        if (whole) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                if (b < my) {
+                    const long long n = n0 + (long long)b * q.n2;
+                    V4 x = *(const V4 *)(r + n);
+                    if (UPDATE) {
+                        const V4 y = *(const V4 *)(qv + n);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) x[c] -= alpha * y[c];
+                        *(V4 *)(r + n) = x;
+                    }
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[b][c] = x[c];
+                }
+        } else if (a < mx) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    if (b < my && c < mz) {
+                        const long long n = n0 + (long long)b * q.n2 + c;
+                        double x = r[n];
+                        if (UPDATE) {
+                            x -= alpha * qv[n];
+                            r[n] = x;
+                        }
+                        v[b][c] = x;
+                    }
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) arr += v[b][c] * v[b][c];
+        const double *Ux = sU + 20 * mx, *Uy = sU + 20 * my, *Uz = sU + 20 * mz;
+        axis_product<true, true>(v, Uz);
+        axis_product<false, true>(v, Uy);
+        {
+            const double c[4] = {Ux[a], Ux[4 + a], Ux[8 + a], Ux[12 + a]};
+            quad_product(v, c);
+        }
+        asm volatile("" ::: "memory");
+        const double *d = dinv + (((mx - 1) * 4 + (my - 1)) * 4 + (mz - 1)) * 64 + 16 * a;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double t = v[b][c] * d[4 * b + c];
+                arz += v[b][c] * t;  // r.z = sum of squares over the eigenvalues
+                v[b][c] = t;
+            }
+        {
+            const double c[4] = {Ux[4 * a], Ux[4 * a + 1], Ux[4 * a + 2], Ux[4 * a + 3]};
+            quad_product(v, c);
+        }
+        axis_product<false, false>(v, Uy);
+        axis_product<true, false>(v, Uz);
+        if (whole) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                if (b < my) {
+                    const long long n = n0 + (long long)b * q.n2;
+                    const V4 x = {v[b][0], v[b][1], v[b][2], v[b][3]};
+                    *(V4 *)(z + n) = x;
+                    if (!UPDATE) *(V4 *)(p + n) = x;
+                }
+        } else if (a < mx) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    if (b < my && c < mz) {
+                        const long long n = n0 + (long long)b * q.n2 + c;
+                        z[n] = v[b][c];
+                        if (!UPDATE) p[n] = v[b][c];
+                    }
+        }
+    }
+    const double s1 = block_sum(arz, red);
+    const double s2 = block_sum(arr, red);
+    if (threadIdx.x == 0) {
+        part_rz[blockIdx.x] = s1;
+        part_rr[blockIdx.x] = s2;
+    }
+}
+
 // partials of p.q
 __global__ void __launch_bounds__(kPT) dot_kernel(const double *__restrict__ a, const double *__restrict__ b,
-                                                  long long n, double *__restrict__ part,
+                                                  long long n, double *__restrict__ part, int iter,
                                                   const PcgState *__restrict__ state)
 {
     __shared__ double red[4];
-    if (state->done) return;
+    if (state->done < iter) return;
     double s = 0.0;
     for (long long t = blockIdx.x * (long long)kPT + threadIdx.x; t < n; t += (long long)gridDim.x * kPT) s += a[t] * b[t];
     s = block_sum(s, red);
     if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// convergence test and p = z + beta p, beta = rz_new / rz_old
+// x += alpha p, the convergence test and p = z + beta p, beta = rz_new / rz
 __global__ void __launch_bounds__(kPT)
-    pupdate_kernel(double *__restrict__ p, const double *__restrict__ z, long long n, const double *__restrict__ rz_new,
-                   const double *__restrict__ rz_old, const double *__restrict__ rr, int nbj,
-                   const double *__restrict__ part_bb, int nbb, double tol2, int iter, PcgState *__restrict__ state)
+    xp_update_kernel(double *__restrict__ x, double *__restrict__ p, const double *__restrict__ z, long long n,
+                     const double *__restrict__ rz_new, const double *__restrict__ rr, int nbj, double tol2, int iter,
+                     PcgState *__restrict__ state)
 {
-    __shared__ double red[4];
-    if (state->done) return;
-    const double rrv = sum_partials(rr, nbj, red);
-    const double bb = sum_partials(part_bb, nbb, red);
-    if (rrv <= tol2 * bb) {
-        __syncthreads();
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            state->done = 1;
-            state->iters = iter + 1;
-            state->rr = rrv;
-            state->bb = bb;
+    __shared__ double red[8];
+    if (state->done < iter) return;
+    const double alpha = state->alpha, rz_old = state->rz[iter & 1], bb = state->bb;
+    double rrv, rzv;
+    sum_partials2(rr, rz_new, nbj, red, rrv, rzv);
+    const bool done = rrv <= tol2 * bb;
+    const double beta = rzv / rz_old;
+    const long long step = (long long)gridDim.x * kPT, t0 = blockIdx.x * (long long)kPT + threadIdx.x;
+    // pairs of nodes, 16 bytes per access
+    typedef double v2d __attribute__((ext_vector_type(2), aligned(8)));
+    const long long n2 = n / 2;
+    for (long long t = t0; t < n2; t += step) {
+        const v2d pv = ((const v2d *)p)[t];
+        v2d xv = ((const v2d *)x)[t];
+        xv[0] += alpha * pv[0];
+        xv[1] += alpha * pv[1];
+        ((v2d *)x)[t] = xv;
+        if (!done) {
+            v2d zv = ((const v2d *)z)[t];
+            zv[0] += beta * pv[0];
+            zv[1] += beta * pv[1];
+            ((v2d *)p)[t] = zv;
         }
-        return;
     }
-    const double beta = sum_partials(rz_new, nbj, red) / sum_partials(rz_old, nbj, red);
-    for (long long t = blockIdx.x * (long long)kPT + threadIdx.x; t < n; t += (long long)gridDim.x * kPT)
-        p[t] = z[t] + beta * p[t];
+    if ((n & 1) && t0 == 0) {
+        const double pv = p[n - 1];
+        x[n - 1] += alpha * pv;
+        if (!done) p[n - 1] = z[n - 1] + beta * pv;
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (done) state->done = iter;
         state->iters = iter + 1;
         state->rr = rrv;
-        state->bb = bb;
+        state->rz[1 - (iter & 1)] = rzv;
     }
 }
 
 // state after the initial residual: converged already when r.r <= tol^2 b.b
-__global__ void __launch_bounds__(kPT) pcg_start_kernel(const double *__restrict__ rr, int nbj,
-                                                        const double *__restrict__ part_bb, int nbb, double tol2,
-                                                        PcgState *__restrict__ state)
+__global__ void __launch_bounds__(kPT) pcg_start_kernel(const double *__restrict__ rr, const double *__restrict__ rz,
+                                                        int nbj, const double *__restrict__ part_bb, int nbb,
+                                                        double tol2, PcgState *__restrict__ state)
 {
     __shared__ double red[4];
     const double rrv = sum_partials(rr, nbj, red);
+    const double rzv = sum_partials(rz, nbj, red);
     const double bb = sum_partials(part_bb, nbb, red);
     if (threadIdx.x == 0) {
-        state->done = rrv <= tol2 * bb ? 1 : 0;
+        state->done = rrv <= tol2 * bb ? -1 : kNotDone;
         state->iters = 0;
         state->rr = rrv;
         state->bb = bb;
+        state->rz[0] = rzv;
     }
 }
 
@@ -491,6 +738,42 @@ bool invert(std::vector<double> &A, int m)
     return true;
 }
 
+// eigenvalues l and eigenvectors (columns of U, m x m row-major in a 4 x 4
+// array) of a symmetric m x m matrix, m <= 4: cyclic Jacobi rotations
+void small_eigen(double (&A)[4][4], int m, double (&U)[4][4], double (&l)[4])
+{
+    for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < 4; ++j) U[i][j] = i == j && i < m ? 1.0 : 0.0;
+    for (int sweep = 0; sweep < 30; ++sweep) {
+        double off = 0.0;
+        for (int p = 0; p < m; ++p)
+            for (int q = p + 1; q < m; ++q) off += A[p][q] * A[p][q];
+        if (off == 0.0) break;
+        for (int p = 0; p < m; ++p)
+            for (int q = p + 1; q < m; ++q) {
+                if (A[p][q] == 0.0) continue;
+                const double tau = (A[q][q] - A[p][p]) / (2.0 * A[p][q]);
+                const double t = (tau >= 0 ? 1.0 : -1.0) / (std::fabs(tau) + std::sqrt(1.0 + tau * tau));
+                const double c = 1.0 / std::sqrt(1.0 + t * t), s = t * c;
+                for (int k = 0; k < m; ++k) {  // columns p, q of A and U
+                    const double x = A[k][p], y = A[k][q];
+                    A[k][p] = c * x - s * y;
+                    A[k][q] = s * x + c * y;
+                    const double a = U[k][p], b = U[k][q];
+                    U[k][p] = c * a - s * b;
+                    U[k][q] = s * a + c * b;
+                }
+                for (int k = 0; k < m; ++k) {  // rows
+                    const double x = A[p][k], y = A[q][k];
+                    A[p][k] = c * x - s * y;
+                    A[q][k] = s * x + c * y;
+                }
+                A[p][q] = A[q][p] = 0.0;
+            }
+    }
+    for (int i = 0; i < 4; ++i) l[i] = i < m ? A[i][i] : 1.0;
+}
+
 size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -508,15 +791,16 @@ struct sparc_poisson {
     sparc_op *op0 = nullptr;  // zero potential, no atoms: its step kernel applies -1/2 lap_h
     HarmNorm nrm{};
     double *d_minv = nullptr;
+    bool diag = false;  // blocks of 4 x 4 x 4 nodes: d_minv holds the tables of bj_diag_kernel
     double *d_w = nullptr;
     long long slab_total = 0;
-    int nmom = 0, nred = 0, nbjg = 0;  // workgroups of the moment, reduction and block-Jacobi kernels
+    int nmom = 0, nred = 0, nbjg = 0, npq = 0;  // workgroups of the moment, reduction and block-Jacobi kernels
 };
 
 namespace {
 
 struct PoisWs {
-    double *r, *z, *p, *q, *slab, *mpart, *Q, *bb, *pq, *rz[2], *rr;
+    double *r, *z, *p, *q, *slab, *mpart, *Q, *bb, *pq, *rz, *rr;
     PcgState *state;
     size_t total;
 };
@@ -540,9 +824,8 @@ PoisWs carve(const sparc_poisson *P, void *ws)
     W.mpart = (double *)take((size_t)P->nmom * kNM * sizeof(double));
     W.Q = (double *)take(kNM * sizeof(double));
     W.bb = (double *)take(kRedMax * sizeof(double));
-    W.pq = (double *)take(kRedMax * sizeof(double));
-    W.rz[0] = (double *)take(kRedMax * sizeof(double));
-    W.rz[1] = (double *)take(kRedMax * sizeof(double));
+    W.pq = (double *)take((size_t)std::max(P->npq, kRedMax) * sizeof(double));
+    W.rz = (double *)take(kRedMax * sizeof(double));
     W.rr = (double *)take(kRedMax * sizeof(double));
     W.state = (PcgState *)take(sizeof(PcgState));
     W.total = o;
@@ -616,36 +899,61 @@ extern "C" int sparc_poisson_create(const sparc_grid *grid, int32_t lmax, const 
     }
     q.maxm = q.b[0] * q.b[1] * q.b[2];
     const double *w = op0->w;
-    std::vector<double> minv((size_t)8 * q.maxm * q.maxm, 0.0);
-    for (int code = 0; code < 8; ++code) {
-        int dim[3];
-        for (int a = 0; a < 3; ++a) dim[a] = (code >> (2 - a)) & 1 ? q.last[a] : q.b[a];
-        const int m = dim[0] * dim[1] * dim[2];
-        std::vector<double> A((size_t)m * m, 0.0);
-        for (int t = 0; t < m; ++t) {
-            const int c[3] = {t / (dim[1] * dim[2]), (t / dim[2]) % dim[1], t % dim[2]};
-            A[(size_t)t * m + t] += 6.0 * w[0];
-            for (int a = 0; a < 3; ++a)
-                for (int p = 1; p <= grid->radius; ++p)
-                    for (int s = -1; s <= 1; s += 2) {
-                        int e[3] = {c[0], c[1], c[2]};
-                        e[a] += s * p;
-                        if (e[a] < 0 || e[a] >= dim[a]) continue;
-                        A[(size_t)t * m + (e[0] * dim[1] + e[1]) * dim[2] + e[2]] += w[p];
-                    }
-        }
-        for (double &v : A) v *= -1.0 / kFourPi;
-        if (!invert(A, m)) {
-            sparc_poisson_destroy(P);
-            return fail(SPARC_E_HIP, "block matrix is singular");
-        }
-        // symmetrise (the inverse of a symmetric matrix; removes rounding asymmetry)
-        for (int i = 0; i < m; ++i)
-            for (int j = i + 1; j < m; ++j) {
-                const double s = 0.5 * (A[(size_t)i * m + j] + A[(size_t)j * m + i]);
-                A[(size_t)i * m + j] = A[(size_t)j * m + i] = s;
+    P->diag = b[0] == 4 && b[1] == 4 && b[2] == 4;
+    std::vector<double> minv;
+    if (P->diag) {
+        minv.assign(kDiagTab + 64 * 64, 0.0);
+        for (int m = 1; m <= 4; ++m) {
+            double T[4][4] = {}, U[4][4], l[4];
+            for (int i = 0; i < m; ++i)
+                for (int j = 0; j < m; ++j) {
+                    const int p = std::abs(i - j);
+                    T[i][j] = p > grid->radius ? 0.0 : (p == 0 ? 2.0 : 1.0) * w[p] * (-1.0 / kFourPi);
+                }
+            small_eigen(T, m, U, l);
+            for (int i = 0; i < 4; ++i) {
+                for (int j = 0; j < 4; ++j) minv[20 * m + 4 * i + j] = U[i][j];
+                minv[20 * m + 16 + i] = l[i];
             }
-        std::copy(A.begin(), A.end(), minv.begin() + (size_t)code * q.maxm * q.maxm);
+        }
+        for (int e = 0; e < 64 * 64; ++e) {
+            const int m[3] = {e / 1024 + 1, e / 256 % 4 + 1, e / 64 % 4 + 1}, i[3] = {e / 16 % 4, e / 4 % 4, e % 4};
+            double sum = 0.0;
+            for (int d = 0; d < 3; ++d) sum += minv[20 * m[d] + 16 + i[d]];
+            minv[kDiagTab + e] = 1.0 / sum;
+        }
+    } else {
+        minv.assign((size_t)8 * q.maxm * q.maxm, 0.0);
+        for (int code = 0; code < 8; ++code) {
+            int dim[3];
+            for (int a = 0; a < 3; ++a) dim[a] = (code >> (2 - a)) & 1 ? q.last[a] : q.b[a];
+            const int m = dim[0] * dim[1] * dim[2];
+            std::vector<double> A((size_t)m * m, 0.0);
+            for (int t = 0; t < m; ++t) {
+                const int c[3] = {t / (dim[1] * dim[2]), (t / dim[2]) % dim[1], t % dim[2]};
+                A[(size_t)t * m + t] += 6.0 * w[0];
+                for (int a = 0; a < 3; ++a)
+                    for (int p = 1; p <= grid->radius; ++p)
+                        for (int s = -1; s <= 1; s += 2) {
+                            int e[3] = {c[0], c[1], c[2]};
+                            e[a] += s * p;
+                            if (e[a] < 0 || e[a] >= dim[a]) continue;
+                            A[(size_t)t * m + (e[0] * dim[1] + e[1]) * dim[2] + e[2]] += w[p];
+                        }
+            }
+            for (double &v : A) v *= -1.0 / kFourPi;
+            if (!invert(A, m)) {
+                sparc_poisson_destroy(P);
+                return fail(SPARC_E_HIP, "block matrix is singular");
+            }
+            // symmetrise (the inverse of a symmetric matrix; removes rounding asymmetry)
+            for (int i = 0; i < m; ++i)
+                for (int j = i + 1; j < m; ++j) {
+                    const double s = 0.5 * (A[(size_t)i * m + j] + A[(size_t)j * m + i]);
+                    A[(size_t)i * m + j] = A[(size_t)j * m + i] = s;
+                }
+            std::copy(A.begin(), A.end(), minv.begin() + (size_t)code * q.maxm * q.maxm);
+        }
     }
     std::vector<double> wv(kMaxRadius + 1, 0.0);
     for (int p = 0; p <= grid->radius; ++p) wv[p] = w[p];
@@ -661,9 +969,14 @@ extern "C" int sparc_poisson_create(const sparc_grid *grid, int32_t lmax, const 
     }
     P->nmom = (int)std::max<long long>(1, std::min<long long>(256, (nd + kPT - 1) / kPT));
     P->nred = (int)std::max<long long>(1, std::min<long long>(kRedMax, (nd + 4 * kPT - 1) / (4 * kPT)));
-    const int G = kPT / q.maxm;
-    const long long bricks = (long long)q.nb[0] * q.nb[1] * ((q.nb[2] + G - 1) / G);
-    P->nbjg = (int)std::max<long long>(1, std::min<long long>(kRedMax, bricks));
+    if (P->diag) {
+        P->nbjg = (int)std::max<long long>(1, std::min<long long>(kRedMax, (4 * q.nblocks + kPT - 1) / kPT));
+    } else {
+        const int G = kPT / q.maxm;
+        const long long bricks = (long long)q.nb[0] * q.nb[1] * ((q.nb[2] + G - 1) / G);
+        P->nbjg = (int)std::max<long long>(1, std::min<long long>(kRedMax, bricks));
+    }
+    P->npq = vstep_takes(op0) ? (int)vstep_blocks(op0) : 0;
     *out = P;
     return SPARC_OK;
 }
@@ -722,31 +1035,46 @@ extern "C" int sparc_poisson_solve(sparc_poisson *P, const double *charge, doubl
     } else {
         hipLaunchKernelGGL(fill_kernel, dim3(nvec), dim3(kPT), 0, s, phi, nd);
     }
-    hipLaunchKernelGGL(bj_kernel<false>, dim3(P->nbjg), dim3(kPT), 0, s, P->bj, (const double *)P->d_minv, phi, W.r,
-                       W.p, (const double *)nullptr, W.z, (const double *)nullptr, 0, (const double *)nullptr, 0,
-                       W.rz[0], W.rr, (const PcgState *)W.state);
+    // one block-Jacobi launch: INIT or the update of iteration `it`
+    const int npq = P->npq > 0 ? P->npq : nvec;
+    auto block_jacobi = [&](bool update, int it) {
+        const dim3 g(P->nbjg), b(kPT);
+#define SPARC_BJ(kernel, ...)                                                                                \
+    hipLaunchKernelGGL(kernel, g, b, 0, s, P->bj, (const double *)P->d_minv, __VA_ARGS__ W.r, W.p,           \
+                       (const double *)W.q, W.z, (const double *)W.pq, npq, W.rz, W.rr, it, W.state)
+        if (P->diag && update)
+            SPARC_BJ(bj_diag_kernel<true>, (const double *)P->d_minv + kDiagTab, );
+        else if (P->diag)
+            SPARC_BJ(bj_diag_kernel<false>, (const double *)P->d_minv + kDiagTab, );
+        else if (update)
+            SPARC_BJ(bj_kernel<true>, );
+        else
+            SPARC_BJ(bj_kernel<false>, );
+#undef SPARC_BJ
+    };
+    block_jacobi(false, 0);
     const double tol2 = tol * tol;
-    hipLaunchKernelGGL(pcg_start_kernel, dim3(1), dim3(kPT), 0, s, (const double *)W.rr, P->nbjg,
+    hipLaunchKernelGGL(pcg_start_kernel, dim3(1), dim3(kPT), 0, s, (const double *)W.rr, (const double *)W.rz, P->nbjg,
                        (const double *)W.bb, nvec, tol2, W.state);
     SPARC_HIP(hipGetLastError());
     PcgState hs{};
     SPARC_HIP(hipMemcpyAsync(&hs, W.state, sizeof(hs), hipMemcpyDeviceToHost, s));
     SPARC_HIP(hipStreamSynchronize(s));
     int it = 0;
-    while (!hs.done && it < max_iter) {
+    while (hs.done == kNotDone && it < max_iter) {
         const int chunk = std::min(kChunk, max_iter - it);
         for (int c = 0; c < chunk; ++c, ++it) {
-            const int o = it & 1;  // rz of this iteration's input in rz[o], its output in rz[1 - o]
-            if ((st = launch_h_step(P->op0, SPARC_F64, W.p, nd, nullptr, 0, W.q, nd, 1, nullptr, cA, L, s, &V)))
-                return st;
-            hipLaunchKernelGGL(dot_kernel, dim3(nvec), dim3(kPT), 0, s, (const double *)W.p, (const double *)W.q, nd,
-                               W.pq, (const PcgState *)W.state);
-            hipLaunchKernelGGL(bj_kernel<true>, dim3(P->nbjg), dim3(kPT), 0, s, P->bj, (const double *)P->d_minv, phi,
-                               W.r, W.p, (const double *)W.q, W.z, (const double *)W.rz[o], P->nbjg,
-                               (const double *)W.pq, nvec, W.rz[1 - o], W.rr, (const PcgState *)W.state);
-            hipLaunchKernelGGL(pupdate_kernel, dim3(nvec), dim3(kPT), 0, s, W.p, (const double *)W.z, nd,
-                               (const double *)W.rz[1 - o], (const double *)W.rz[o], (const double *)W.rr, P->nbjg,
-                               (const double *)W.bb, nvec, tol2, it, W.state);
+            if (P->npq > 0) {
+                if ((st = launch_vstep(P->op0, W.p, W.q, cA.alpha, false, W.pq, &W.state->done, it, s))) return st;
+            } else {
+                if ((st = launch_h_step(P->op0, SPARC_F64, W.p, nd, nullptr, 0, W.q, nd, 1, nullptr, cA, L, s, &V)))
+                    return st;
+                hipLaunchKernelGGL(dot_kernel, dim3(nvec), dim3(kPT), 0, s, (const double *)W.p, (const double *)W.q, nd,
+                                   W.pq, it, (const PcgState *)W.state);
+            }
+            block_jacobi(true, it);
+            hipLaunchKernelGGL(xp_update_kernel, dim3(nvec), dim3(kPT), 0, s, phi, W.p, (const double *)W.z, nd,
+                               (const double *)W.rz, (const double *)W.rr, P->nbjg, tol2, it, W.state);
         }
         SPARC_HIP(hipGetLastError());
         SPARC_HIP(hipMemcpyAsync(&hs, W.state, sizeof(hs), hipMemcpyDeviceToHost, s));

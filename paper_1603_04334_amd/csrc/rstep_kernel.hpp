@@ -79,20 +79,7 @@ struct RStep {
     template <int Q>
     static constexpr int slot(int d) { return (Q + d) % QL; }
 
-    // the unit as loaded, at its place
-    static __device__ __forceinline__ V place(const V &v, bool c)
-    {
-        if constexpr (RAG == 0) return v;
-        V r;
-#pragma unroll
-        for (int j = 0; j < VZ; ++j) {
-            T m = T(0);
-            if constexpr (RAG > 0)
-                if (j + RAG < VZ) m = v[(j + RAG) % VZ];
-            r[j] = c ? m : v[j];
-        }
-        return r;
-    }
+    static __device__ __forceinline__ V place(const V &v, bool c) { return place_unit<T, RAG>(v, c); }
 
     __device__ __forceinline__ void load_head(int t)
     {

@@ -1,0 +1,108 @@
+// The step of one FP64 vector without Y_{k-1}: H v for Lanczos (with the
+// projections of v gathered by the first workgroups of the launch) and A p for
+// the Poisson solver (no potential), each with the partial sums of v.(out) per
+// workgroup that the caller's next kernel finishes in a fixed order.
+//
+// One vector is small (7 MB at 96^3, 33 MB at 160^3) and stays in the caches;
+// what costs time is getting enough workgroups in flight with few repeated
+// planes.  16-byte units on patches of 16 x 32 nodes (256 threads), x cut so
+// that about four workgroups share a CU: at 160^3 91.7 us per CG iteration
+// (8 x 32: 93.9, 8 x 64: 93.6, 16 x 64: 93.8, 4 x 32: 96.0; 512 or 2048
+// workgroups: 95.2, 93.4).
+#include <algorithm>
+#include <cstring>
+
+#include "fstep_kernel.hpp"
+#include "nonlocal_kernel.hpp"
+
+namespace sparc {
+
+constexpr int kVTY = 16, kVTZ = 32, kVThreads = kVTY * kVTZ / 2;
+
+// fixed-order workgroup sum of the lanes' products
+__device__ __forceinline__ void store_partial(double v, double *dot, int b)
+{
+    __shared__ double red[kVThreads / 64];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = red[0];
+        for (int i = 1; i < kVThreads / 64; ++i) t += red[i];
+        dot[b] = t;
+    }
+}
+
+// done: the launch is skipped when *done < iter (null: never)
+template <bool POT, int RAG>
+__global__ void __launch_bounds__(kVThreads)
+    vstep_kernel(const FStepArgs<double> a, double *dot, const int *done, int iter)
+{
+    using K = FStep<double, kVTY, false, false, 1, kVTZ, POT, true, RAG>;
+    __shared__ __align__(16) typename K::Shared sh;
+    if (done && *done < iter) return;
+    K k(a);
+    k.run(blockIdx.x, sh);
+    store_partial(k.dacc, dot, blockIdx.x);
+}
+
+struct VPlan {
+    int tiles_y, tiles_z, chunk_x, nchunks;
+    long long blocks() const { return (long long)tiles_y * tiles_z * nchunks; }
+};
+
+static VPlan vstep_plan(const sparc_op *op)
+{
+    VPlan v;
+    v.tiles_y = (op->n[1] + kVTY - 1) / kVTY;
+    v.tiles_z = (op->n[2] + kVTZ - 1) / kVTZ;
+    const long long want = 1024;  // workgroups: four to a CU
+    const long long tiles = (long long)v.tiles_y * v.tiles_z;
+    const long long nch = std::max<long long>(1, std::min<long long>((want + tiles - 1) / tiles, op->n[0] / 4));
+    v.chunk_x = (int)((op->n[0] + nch - 1) / nch);
+    v.nchunks = (op->n[0] + v.chunk_x - 1) / v.chunk_x;
+    return v;
+}
+
+bool vstep_takes(const sparc_op *op) { return op->n[2] >= 2 && vstep_plan(op).blocks() <= 65536; }
+
+long long vstep_blocks(const sparc_op *op) { return vstep_plan(op).blocks(); }
+
+int launch_vstep(const sparc_op *op, const double *v, double *out, double alpha, bool pot, double *dot, const int *done,
+                 int iter, hipStream_t stream)
+{
+    const VPlan p = vstep_plan(op);
+    FStepArgs<double> a;
+    std::memset(&a, 0, sizeof(a));
+    a.yk = v;
+    a.out = out;
+    a.veff = op->d_veff64;
+    a.ldk = a.ldo = op->nd;
+    a.n1 = op->n[0];
+    a.n2 = op->n[1];
+    a.n3 = op->n[2];
+    a.tiles_y = p.tiles_y;
+    a.tiles_z = p.tiles_z;
+    a.nchunks = p.nchunks;
+    a.chunk_x = p.chunk_x;
+    a.nblocks = (int)p.blocks();
+    a.remap = 1;
+    a.ns = a.cgroup = 1;
+    a.c0 = -3.0 * op->w[0];
+    for (int q = 1; q <= kMaxRadius; ++q) a.cp[q - 1] = -0.5 * op->w[q];
+    a.alpha = alpha;
+    const dim3 grid((unsigned)a.nblocks), blk(kVThreads);
+    const bool rag = op->n[2] & 1;
+    if (pot && rag)
+        hipLaunchKernelGGL((vstep_kernel<true, 1>), grid, blk, 0, stream, a, dot, done, iter);
+    else if (pot)
+        hipLaunchKernelGGL((vstep_kernel<true, 0>), grid, blk, 0, stream, a, dot, done, iter);
+    else if (rag)
+        hipLaunchKernelGGL((vstep_kernel<false, 1>), grid, blk, 0, stream, a, dot, done, iter);
+    else
+        hipLaunchKernelGGL((vstep_kernel<false, 0>), grid, blk, 0, stream, a, dot, done, iter);
+    SPARC_HIP(hipGetLastError());
+    return SPARC_OK;
+}
+
+}  // namespace sparc
