@@ -404,16 +404,38 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
             }
         }
         close_block((int)pts.size());
+        std::vector<int> proj(raw.size()), seg(kRedBlocks + 1);
+        for (size_t e = 0; e < raw.size(); ++e) proj[e] = op->atoms[raw[e].first].proj0;
+        const long long sl = red_segment(op->nd);
+        for (int b = 0; b <= kRedBlocks; ++b)
+            seg[b] = (int)(std::lower_bound(pts.begin(), pts.end(), b * sl,
+                                            [](int x, long long y) { return (long long)x < y; }) - pts.begin());
         if (chi_total > 0x7fffffffLL) return cleanup(fail(SPARC_E_SHAPE, "projector data too large"));
         op->nl_npts = (int)pts.size();
         op->nl_nblk = (int)blk_pt.size() - 1;
+        // one allocation and one copy for all of them
+        std::vector<int> all;
+        std::vector<std::pair<int **, size_t>> at;
         auto up = [&](int **dst, const std::vector<int> &v) {
-            if (hipMalloc(dst, std::max<size_t>(1, v.size()) * sizeof(int)) != hipSuccess) return false;
-            return v.empty() || hipMemcpy(*dst, v.data(), v.size() * sizeof(int), hipMemcpyHostToDevice) == hipSuccess;
+            at.push_back({dst, all.size()});
+            all.insert(all.end(), v.begin(), v.end());
+            all.resize((all.size() + 63) / 64 * 64, 0);
         };
-        if (!up(&op->d_box_off, boff) || !up(&op->d_units, units) || !up(&op->d_nl_pts, pts) || !up(&op->d_nl_off, off) || !up(&op->d_nl_ent, ent) ||
-            !up(&op->d_nl_blk_pt, blk_pt) || !up(&op->d_nl_blk_at, blk_at) || !up(&op->d_nl_blk_atoms, blk_atoms))
+        up(&op->d_box_off, boff);
+        up(&op->d_units, units);
+        up(&op->d_nl_pts, pts);
+        up(&op->d_nl_off, off);
+        up(&op->d_nl_ent, ent);
+        up(&op->d_nl_blk_pt, blk_pt);
+        up(&op->d_nl_blk_at, blk_at);
+        up(&op->d_nl_blk_atoms, blk_atoms);
+        up(&op->d_nl_proj, proj);
+        up(&op->d_nl_seg, seg);
+        if (hipMalloc(&op->d_tables, all.size() * sizeof(int)) != hipSuccess)
             return cleanup(fail(SPARC_E_NOMEM, "device allocation of projector tables failed"));
+        if (hipMemcpy(op->d_tables, all.data(), all.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
+            return cleanup(fail(SPARC_E_HIP, "copy of projector tables failed"));
+        for (auto &t : at) *t.first = op->d_tables + t.second;
     }
     *out = op;
     return SPARC_OK;
@@ -429,16 +451,9 @@ int sparc_op_destroy(sparc_op *op)
     (void)hipFree(op->d_chi32);
     (void)hipFree(op->d_hg64);
     (void)hipFree(op->d_hg32);
-    (void)hipFree(op->d_box_off);
-    (void)hipFree(op->d_units);
+    (void)hipFree(op->d_tables);
     (void)hipFree(op->d_chiu64);
     (void)hipFree(op->d_chiu32);
-    (void)hipFree(op->d_nl_pts);
-    (void)hipFree(op->d_nl_off);
-    (void)hipFree(op->d_nl_ent);
-    (void)hipFree(op->d_nl_blk_pt);
-    (void)hipFree(op->d_nl_blk_at);
-    (void)hipFree(op->d_nl_blk_atoms);
     (void)hipFree(op->d_fatoms);
     (void)hipFree(op->d_funits);
     (void)hipFree(op->d_ffun);

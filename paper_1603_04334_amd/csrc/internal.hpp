@@ -15,6 +15,7 @@ namespace sparc {
 
 constexpr int kMaxRadius = 6;    // largest stencil half-width n_o supported
 constexpr int kMaxProj = 16;     // largest projector count per atom
+constexpr int kRedBlocks = 1024;  // workgroups of a reduction pass over one vector: one partial each
 constexpr int kBlock = 256;      // threads per workgroup of the stencil kernels
 constexpr int kGatherSplit = 8;  // workgroups sharing one atom's cube points in the gather
 constexpr int kScatterSlots = 32;  // most atoms one scatter block may touch
@@ -71,6 +72,7 @@ struct sparc_op {
     float *d_chi32 = nullptr;
     double *d_hg64 = nullptr;  // h^3 gamma per global projector
     float *d_hg32 = nullptr;
+    int *d_tables = nullptr;   // the integer tables below, back to back
     int *d_box_off = nullptr;  // grid index of every cube node (atoms back to back)
     int *d_units = nullptr;  // int2 records of the gather's units (atoms back to back)
     double *d_chiu64 = nullptr;  // chi in unit layout
@@ -87,6 +89,10 @@ struct sparc_op {
     int *d_nl_blk_pt = nullptr;
     int *d_nl_blk_at = nullptr;
     int *d_nl_blk_atoms = nullptr;
+    // for the Lanczos update: the first projector of every entry's atom, and the
+    // first covered node of every reduction segment (kRedBlocks + 1)
+    int *d_nl_proj = nullptr;
+    int *d_nl_seg = nullptr;
     // launch overrides (set by sparc_op_set_launch; -1 / 0 = library choice)
     int tune_shape[2] = {-1, -1};
     int tune_chunk[2] = {0, 0};
@@ -119,6 +125,9 @@ int fail(int status, const std::string &msg);
     } while (0)
 
 size_t elem_size(int dtype);
+
+// nodes per workgroup of a reduction pass over n nodes
+inline __host__ __device__ long long red_segment(long long n) { return ((n + kRedBlocks - 1) / kRedBlocks + 63) / 64 * 64; }
 inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
 // Launch parameters of one fused step: out = alpha*((H - shift) yk) - beta*yprev
@@ -216,14 +225,15 @@ int launch_step_f32_to_f64(const sparc_op *op, const float *yk, int64_t ldk, dou
 // workgroups.
 bool vstep_takes(const sparc_op *op);
 long long vstep_blocks(const sparc_op *op);
+int launch_vstep_gather(const sparc_op *op, const double *v, double *out, double *dot, double *part, hipStream_t stream);
 int launch_vstep(const sparc_op *op, const double *v, double *out, double alpha, bool pot, double *dot, const int *done,
                  int iter, hipStream_t stream);
 
 // One launch for one FP64 vector v (N_d values, contiguous): out = H_loc v,
 // dot[b] = sum over workgroup b's points of v(x) (H_loc v)(x) for
-// b < step_dot_blocks(op), and the projector gather of v into part (as
+// b < lanczos_dot_blocks(op), and the projector gather of v into part (as
 // launch_gather with ns = 1); the scatter follows separately
-long long step_dot_blocks(const sparc_op *op);
+long long lanczos_dot_blocks(const sparc_op *op);
 int launch_lanczos_h_f64(const sparc_op *op, const double *v, double *out, double *dot, double *part,
                          hipStream_t stream);
 

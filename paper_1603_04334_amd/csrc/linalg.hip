@@ -33,7 +33,6 @@ namespace sparc {
 
 thread_local bool g_rr_rank_deficient = false;  // set by the last Rayleigh-Ritz call of this thread
 
-constexpr int kRedBlocks = 1024;  // blocks of the first reduction pass: one partial per block
 constexpr int kDotGroup = 8;      // vectors per pass over a block's segment
 constexpr int kUnroll = 4;        // points per thread with loads in flight together
 
@@ -68,172 +67,176 @@ __device__ inline double sum_partials(const double *partial, int stride, int i, 
 // the contiguous segment of n points owned by block b of a reduction pass
 __device__ inline void block_segment(long long n, long long &beg, long long &end)
 {
-    const long long seg = ((n + kRedBlocks - 1) / kRedBlocks + 63) / 64 * 64;
+    const long long seg = red_segment(n);
     beg = blockIdx.x * seg;
     end = (beg + seg < n) ? beg + seg : n;
 }
 
-// block-level partial inner products: partial[b*(nv+1) + i] = sum over block
-// b's points of V_i(x) w(x) for i < nv, and of w(x)^2 for i = nv.  Groups of
-// 8 vectors per pass over the segment.
-__device__ __forceinline__ void multidot_block(const double *__restrict__ V, long long ldv, int nv,
-                                               const double *__restrict__ w, long long n,
-                                               double *__restrict__ partial, double *red)
+// per-block partials of |w|^2
+__global__ void __launch_bounds__(256) norm2_kernel(const double *__restrict__ w, long long n,
+                                                    double *__restrict__ partial)
 {
-    long long beg, end;
-    block_segment(n, beg, end);
-    double *out = partial + (long long)blockIdx.x * (nv + 1);
-    for (int i0 = 0; i0 <= nv; i0 += kDotGroup) {
-        double acc[kDotGroup];
-#pragma unroll
-        for (int u = 0; u < kDotGroup; ++u) acc[u] = 0.0;
-        for (long long x0 = beg + threadIdx.x; x0 < end; x0 += 256 * kUnroll) {
-            double wx[kUnroll];
-#pragma unroll
-            for (int r = 0; r < kUnroll; ++r) {
-                const long long x = x0 + 256 * r;
-                wx[r] = x < end ? w[x] : 0.0;
-            }
-#pragma unroll
-            for (int u = 0; u < kDotGroup; ++u) {
-                const int i = i0 + u;
-                if (i > nv) break;
-                double vx[kUnroll];
-#pragma unroll
-                for (int r = 0; r < kUnroll; ++r) {
-                    const long long x = x0 + 256 * r;
-                    vx[r] = (i == nv) ? wx[r] : (x < end ? V[(long long)i * ldv + x] : 0.0);
-                }
-#pragma unroll
-                for (int r = 0; r < kUnroll; ++r) acc[u] += vx[r] * wx[r];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kDotGroup; ++u) {
-            const double t = block_sum(acc[u], red);
-            if (threadIdx.x == 0 && i0 + u <= nv) out[i0 + u] = t;
-        }
-    }
-}
-
-__global__ void __launch_bounds__(256) multidot_kernel(const double *__restrict__ V, long long ldv, int nv,
-                                                       const double *__restrict__ w, long long n,
-                                                       double *__restrict__ partial)
-{
-    __shared__ double red[4];
-    multidot_block(V, ldv, nv, w, n, partial, red);
-}
-
-// out[i] = sum over the block partials of entry i (stride per block), one
-// block per i.  alpha_out[0] = out[alpha_index] if set; mode 1 stores the
-// square root.
-__global__ void __launch_bounds__(256) finish_sums(const double *partial, int stride, double *out,
-                                                   double *alpha_out, int alpha_index, int mode, const int *run)
-{
-    if (run && !*run) return;
-    __shared__ double red[4];
-    const int i = blockIdx.x;
-    const double t = sum_partials(partial, stride, i, red);
-    if (threadIdx.x == 0) {
-        out[i] = mode == 1 ? sqrt(t) : t;
-        if (alpha_out && i == alpha_index) alpha_out[0] = t;
-    }
-}
-
-// w -= sum_i coeff[i] V_i, and partial[b] = sum over block b's points of the new w^2
-__global__ void __launch_bounds__(256) orth_apply_norm(double *w, const double *__restrict__ V, long long ldv, int nv,
-                                                       const double *__restrict__ coeff, long long n,
-                                                       double *__restrict__ partial, const int *run)
-{
-    if (run && !*run) return;
     __shared__ double red[4];
     long long beg, end;
     block_segment(n, beg, end);
-    double nrm = 0.0;
-    for (long long x0 = beg + threadIdx.x; x0 < end; x0 += 256 * kUnroll) {
-        double s[kUnroll];
-#pragma unroll
-        for (int r = 0; r < kUnroll; ++r) s[r] = 0.0;
-        for (int i = 0; i < nv; ++i) {
-            const double c = coeff[i];
-#pragma unroll
-            for (int r = 0; r < kUnroll; ++r) {
-                const long long x = x0 + 256 * r;
-                s[r] += c * (x < end ? V[(long long)i * ldv + x] : 0.0);
-            }
-        }
+    double s = 0.0;
+    for (long long x0 = beg + threadIdx.x; x0 < end; x0 += 256 * kUnroll)
 #pragma unroll
         for (int r = 0; r < kUnroll; ++r) {
             const long long x = x0 + 256 * r;
-            if (x < end) {
-                const double v = w[x] - s[r];
-                w[x] = v;
-                nrm += v * v;
-            }
+            const double v = x < end ? w[x] : 0.0;
+            s += v * v;
         }
-    }
-    const double t = block_sum(nrm, red);
-    if (threadIdx.x == 0) partial[blockIdx.x] = t;
+    s = block_sum(s, red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
+// The Lanczos vectors are kept as they come out of the recurrence, u_j = nu_j
+// v_j with nu_j = |u_j| = beta_{j-1} (nu_0 = 1): nothing is scaled in a pass of
+// its own.
+//
 // alpha_j = v_j^T H v_j from its two parts: the step kernel's workgroup
-// partials of v^T (H_loc v), and the projections g_p = chi_p^T v (the
-// gather's split partials, nproj of them per split), since
-// v^T V_nl v = sum_p hg_p g_p^2.  One fixed order in every block.
-__device__ inline double lanczos_alpha(const double *dot, int nb, const double *gpart, const double *hg, int nproj,
-                                       double *red)
+// partials of u^T (H_loc u), and the projections g_p = chi_p^T u (the gather's
+// split partials, nproj of them per split), since u^T V_nl u = sum_p hg_p
+// g_p^2.  table (LDS, may be null) receives hg_p g_p.  nu_j is finished first
+// when the step before re-orthogonalised u_j (its |u_j|^2 partials).  One fixed
+// order in every block.
+struct LanczosAlpha {
+    const double *dot;
+    int ndot;
+    const double *gpart, *hg;
+    int nproj;
+    const int *redo;      // u_j was re-orthogonalised (null: never)
+    const double *npart;  // then: partials of |u_j|^2
+};
+
+__device__ inline double lanczos_alpha(const LanczosAlpha &q, double *nu_j, double *table, double *red, double &nu)
 {
     double v = 0.0;
-    for (int b = threadIdx.x; b < nb; b += 256) v += dot[b];
-    for (int p = threadIdx.x; p < nproj; p += 256) {
+    for (int b = threadIdx.x; b < q.ndot; b += 256) v += q.dot[b];
+    for (int p = threadIdx.x; p < q.nproj; p += 256) {
         double g = 0.0;
 #pragma unroll
-        for (int q = 0; q < kGatherSplit; ++q) g += gpart[(long long)q * nproj + p];
-        v += hg[p] * g * g;
+        for (int s = 0; s < kGatherSplit; ++s) g += q.gpart[(long long)s * q.nproj + p];
+        const double t = q.hg[p] * g;
+        if (table) table[p] = t;
+        v += t * g;
     }
-    return block_sum(v, red);
+    v = block_sum(v, red);
+    nu = *nu_j;
+    if (q.redo && *q.redo) {
+        nu = sqrt(sum_partials(q.npart, 1, 0, red));
+        if (blockIdx.x == 0 && threadIdx.x == 0) *nu_j = nu;
+    }
+    return v / (nu * nu);
 }
 
-__global__ void __launch_bounds__(256) alpha_finish(const double *dot, int nb, const double *gpart, const double *hg,
-                                                    int nproj, double *alpha)
+__global__ void __launch_bounds__(256) alpha_finish(const LanczosAlpha q, double *nu_j, double *alpha)
 {
     __shared__ double red[4];
-    const double a = lanczos_alpha(dot, nb, gpart, hg, nproj, red);
+    double nu;
+    const double a = lanczos_alpha(q, nu_j, nullptr, red, nu);
     if (threadIdx.x == 0) *alpha = a;
 }
 
-// three-term Lanczos step: alpha_j is finished first (block 0 stores it),
-// then w -= alpha_j v_j + beta_{j-1} v_{j-1} (bprev may be null at j = 0) and
-// partial[b] = sum over block b's points of the new w^2
-__global__ void __launch_bounds__(256) lanczos_3term(double *w, const double *__restrict__ vj,
-                                                     const double *__restrict__ vjm, const double *dot, int nb,
-                                                     const double *gpart, const double *hg, int nproj,
-                                                     double *alpha, const double *bprev, long long n,
-                                                     double *__restrict__ partial)
+// nonlocal nodes of a reduction segment (see scatter_item for the tables):
+// block b's segment covers entries seg[b] .. seg[b+1] of pts
+struct LanczosScatter {
+    const int *seg;
+    const int *pts, *ent_off;
+    const int4 *ent;
+    const int *ent_proj;  // first projector of each entry's atom
+    const double *chi;
+};
+
+constexpr int kLanczosProj = 2048;  // projectors whose table the fused scatter keeps in LDS (16 KiB)
+
+// Three-term step: on entry w = H_loc u_j.  The projector scatter of the
+// block's own nodes comes first (FUSED: w += V_nl u_j, the sums of
+// scatter_item; otherwise the scatter was a launch of its own), then
+//   w <- w / nu_j - (alpha_j / nu_j) u_j - (beta_{j-1} / nu_{j-1}) u_{j-1}
+// and partial[b] = sum over block b's nodes of the new w^2.
+// What bounds it: the chain of dependent launches.  A step takes four (H u with
+// the projections, this one, the orthogonality estimates, the conditional
+// re-orthogonalisation) where it took seven (scatter, sums and scaling apart).
+template <bool FUSED>
+__global__ void __launch_bounds__(256)
+    lanczos_3term(double *w, const double *__restrict__ uj, const double *__restrict__ ujm, const LanczosAlpha q,
+                  const LanczosScatter sc, double *nu_j, double *alpha, long long n, double *__restrict__ partial)
 {
     __shared__ double red[4];
-    const double a = lanczos_alpha(dot, nb, gpart, hg, nproj, red);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = a;
-    const double b = bprev ? *bprev : 0.0;
-    const double *vm = bprev ? vjm : vj;
+    __shared__ double table[FUSED ? kLanczosProj : 1];
+    // what the sums do not decide is requested before them: the thread's first
+    // nodes of u_j and u_{j-1}, and its first nonlocal node
     long long beg, end;
     block_segment(n, beg, end);
+    const double *um = ujm ? ujm : uj;
+    double v1[kUnroll], v2[kUnroll];
+#pragma unroll
+    for (int r = 0; r < kUnroll; ++r) {
+        const long long x = beg + threadIdx.x + 256 * r;
+        v1[r] = x < end ? uj[x] : 0.0;
+        v2[r] = x < end ? um[x] : 0.0;
+    }
+    int pi = 0, pe = 0, node = 0, e0 = 0, e1 = 0, pj = 0;
+    int4 en = make_int4(0, 0, 0, 0);
+    if (FUSED) {
+        pi = sc.seg[blockIdx.x] + threadIdx.x;
+        pe = sc.seg[blockIdx.x + 1];
+        if (pi < pe) {
+            node = sc.pts[pi];
+            e0 = sc.ent_off[pi];
+            e1 = sc.ent_off[pi + 1];
+            en = sc.ent[e0];
+            pj = sc.ent_proj[e0];
+        }
+    }
+    double nu;
+    const double a = lanczos_alpha(q, nu_j, FUSED ? table : nullptr, red, nu);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = a;
+    if (FUSED) {  // table complete: block_sum ends in a barrier
+        while (pi < pe) {
+            const double cur = w[node];
+            double acc = 0.0;
+            for (int e = e0; e < e1; ++e) {
+                if (e > e0) {
+                    en = sc.ent[e];
+                    pj = sc.ent_proj[e];
+                }
+                const double *S = table + pj;
+                for (int p = 0; p < en.w; ++p) acc += sc.chi[en.x + (long long)p * en.y] * S[p];
+            }
+            w[node] = cur + acc;
+            pi += 256;
+            if (pi < pe) {
+                node = sc.pts[pi];
+                e0 = sc.ent_off[pi];
+                e1 = sc.ent_off[pi + 1];
+                en = sc.ent[e0];
+                pj = sc.ent_proj[e0];
+            }
+        }
+        __syncthreads();
+    }
+    const double c0 = 1.0 / nu, c1 = a / nu, c2 = ujm ? nu / nu_j[-1] : 0.0;
     double nrm = 0.0;
     for (long long x0 = beg + threadIdx.x; x0 < end; x0 += 256 * kUnroll) {
-        double wv[kUnroll], v1[kUnroll], v2[kUnroll];
+        double wv[kUnroll];
 #pragma unroll
         for (int r = 0; r < kUnroll; ++r) {
             const long long x = x0 + 256 * r;
             const bool ok = x < end;
             wv[r] = ok ? w[x] : 0.0;
-            v1[r] = ok ? vj[x] : 0.0;
-            v2[r] = ok ? vm[x] : 0.0;
+            if (x0 >= beg + 256 * kUnroll) {
+                v1[r] = ok ? uj[x] : 0.0;
+                v2[r] = ok ? um[x] : 0.0;
+            }
         }
 #pragma unroll
         for (int r = 0; r < kUnroll; ++r) {
             const long long x = x0 + 256 * r;
             if (x < end) {
-                const double v = wv[r] - (a * v1[r] + b * v2[r]);
+                const double v = c0 * wv[r] - (c1 * v1[r] + c2 * v2[r]);
                 w[x] = v;
                 nrm += v * v;
             }
@@ -242,6 +245,8 @@ __global__ void __launch_bounds__(256) lanczos_3term(double *w, const double *__
     const double t = block_sum(nrm, red);
     if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
+
+constexpr int kDotBlocks = 256;  // workgroups of the inner products: few partials for every workgroup to finish
 
 // Partial reorthogonalisation (Simon's omega recurrence).  Row j of the
 // estimates holds v_j^T v_i, i < j; after the three-term step of step j
@@ -259,7 +264,8 @@ __global__ void __launch_bounds__(256) lanczos_3term(double *w, const double *__
 // owed[j+1] (orthogonalise the next vector too).  Per-step slots keep the
 // values read (owed[j], anorm[j]) apart from those written.  When the
 // vector is to be orthogonalised, the workgroups go on to the inner products
-// V^T w with v_0 .. v_j (partials as multidot_kernel); otherwise they exit.
+// u_i^T w, i = 0 .. j (the first kDotBlocks workgroups, partial[i][block]);
+// otherwise they exit.
 __global__ void __launch_bounds__(256) omega_dots_kernel(const double *alpha, double *beta, int j, double eps1,
                                                          const double *Wp, const double *Wc, double *Wn,
                                                          int *owed, int *full, double *anorm,
@@ -305,50 +311,111 @@ __global__ void __launch_bounds__(256) omega_dots_kernel(const double *alpha, do
         if (lane == 0) sfull = f ? 1 : 0;
     }
     __syncthreads();
-    if (!sfull) return;
-    multidot_block(V, ldv, j + 1, w, n, partial, red);
+    if (!sfull || blockIdx.x >= kDotBlocks) return;
+    const long long seg = ((n + kDotBlocks - 1) / kDotBlocks + 63) / 64 * 64;
+    const long long beg = blockIdx.x * seg, end = beg + seg < n ? beg + seg : n;
+    const int nv = j + 1;
+    for (int i0 = 0; i0 < nv; i0 += kDotGroup) {
+        double acc[kDotGroup];
+#pragma unroll
+        for (int u = 0; u < kDotGroup; ++u) acc[u] = 0.0;
+        for (long long x0 = beg + threadIdx.x; x0 < end; x0 += 256 * kUnroll) {
+            double wx[kUnroll];
+#pragma unroll
+            for (int r = 0; r < kUnroll; ++r) {
+                const long long x = x0 + 256 * r;
+                wx[r] = x < end ? w[x] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < kDotGroup; ++u) {
+                const int i = i0 + u;
+                if (i >= nv) break;
+                double vx[kUnroll];
+#pragma unroll
+                for (int r = 0; r < kUnroll; ++r) {
+                    const long long x = x0 + 256 * r;
+                    vx[r] = x < end ? V[(long long)i * ldv + x] : 0.0;
+                }
+#pragma unroll
+                for (int r = 0; r < kUnroll; ++r) acc[u] += vx[r] * wx[r];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kDotGroup; ++u) {
+            const double t = block_sum(acc[u], red);
+            if (threadIdx.x == 0 && i0 + u < nv) partial[(long long)(i0 + u) * kDotBlocks + blockIdx.x] = t;
+        }
+    }
 }
 
-// rows j = 0 (1 at i = 0) and j = -1 (zero); owed[0] = 0, anorm[0] = 0
-__global__ void omega_init(double *rows, int len, int *owed, double *anorm)
+// where the decision (run) asks for it: c_i = u_i^T w / nu_i^2 from the
+// partials (every workgroup in the same fixed order, one wave per c_i), w -=
+// sum_i c_i u_i, and partial[b] = sum over block b's nodes of the new w^2
+__global__ void __launch_bounds__(256) orth_apply_norm(double *w, const double *__restrict__ V, long long ldv, int nv,
+                                                       const double *__restrict__ dots, const double *__restrict__ nu,
+                                                       long long n, double *__restrict__ partial, const int *run)
+{
+    extern __shared__ double coeff[];
+    if (!*run) return;
+    __shared__ double red[4];
+    for (int i = threadIdx.x >> 6; i < nv; i += 4) {
+        double v = 0.0;
+#pragma unroll
+        for (int u = 0; u < kDotBlocks / 64; ++u) v += dots[(long long)i * kDotBlocks + 64 * u + (threadIdx.x & 63)];
+        v = wave_sum(v);
+        if ((threadIdx.x & 63) == 0) coeff[i] = v / (nu[i] * nu[i]);
+    }
+    __syncthreads();
+    long long beg, end;
+    block_segment(n, beg, end);
+    double nrm = 0.0;
+    for (long long x0 = beg + threadIdx.x; x0 < end; x0 += 256 * kUnroll) {
+        double s[kUnroll];
+#pragma unroll
+        for (int r = 0; r < kUnroll; ++r) s[r] = 0.0;
+        for (int i = 0; i < nv; ++i) {
+            const double c = coeff[i];
+#pragma unroll
+            for (int r = 0; r < kUnroll; ++r) {
+                const long long x = x0 + 256 * r;
+                s[r] += c * (x < end ? V[(long long)i * ldv + x] : 0.0);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kUnroll; ++r) {
+            const long long x = x0 + 256 * r;
+            if (x < end) {
+                const double v = w[x] - s[r];
+                w[x] = v;
+                nrm += v * v;
+            }
+        }
+    }
+    const double t = block_sum(nrm, red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = t;
+}
+
+// rows j = 0 (1 at i = 0) and j = -1 (zero); owed[0] = 0, anorm[0] = 0,
+// nu[0] = 1
+__global__ void omega_init(double *rows, int len, int *owed, double *anorm, double *nu)
 {
     for (int i = threadIdx.x; i < 3 * len; i += blockDim.x) rows[i] = (i == 0) ? 1.0 : 0.0;
     if (threadIdx.x == 0) {
         owed[0] = 0;
         *anorm = 0.0;
+        nu[0] = 1.0;
     }
 }
 
-// dst = src / nrm.  When redo is null or *redo is set, nrm = sqrt(sum of the
-// block partials of |src|^2) is finished here (block 0 stores it in *norm);
-// otherwise nrm = *norm.  One 256-thread block per reduction segment.
-__global__ void __launch_bounds__(256) scale_by_norm(double *dst, const double *__restrict__ src, double *norm,
-                                                     const double *partial, const int *redo, long long n)
+// dst = src / |src|, |src|^2 from its block partials
+__global__ void __launch_bounds__(256) scale_by_norm(double *dst, const double *__restrict__ src,
+                                                     const double *partial, long long n)
 {
     __shared__ double red[4];
-    double nrm;
-    if (!redo || *redo) {
-        nrm = sqrt(sum_partials(partial, 1, 0, red));
-        if (blockIdx.x == 0 && threadIdx.x == 0) *norm = nrm;
-    } else {
-        nrm = *norm;
-    }
-    const double inv = 1.0 / nrm;
+    const double inv = 1.0 / sqrt(sum_partials(partial, 1, 0, red));
     long long beg, end;
     block_segment(n, beg, end);
-    for (long long x0 = beg + threadIdx.x; x0 < end; x0 += 256 * kUnroll) {
-        double v[kUnroll];
-#pragma unroll
-        for (int r = 0; r < kUnroll; ++r) {
-            const long long x = x0 + 256 * r;
-            v[r] = x < end ? src[x] : 0.0;
-        }
-#pragma unroll
-        for (int r = 0; r < kUnroll; ++r) {
-            const long long x = x0 + 256 * r;
-            if (x < end) dst[x] = v[r] * inv;
-        }
-    }
+    for (long long x = beg + threadIdx.x; x < end; x += 256) dst[x] = src[x] * inv;
 }
 
 __global__ void f64_to_f32_dense(const double *src, float *dst, long long n)
@@ -755,11 +822,11 @@ extern "C" {
 size_t sparc_lanczos_workspace_bytes(const sparc_op *op, int32_t k)
 {
     if (!op || k < 1) return 0;
-    size_t b = align_up((size_t)op->nd * (k + 1) * sizeof(double));  // basis V_0..V_{k-1} and w
+    size_t b = align_up((size_t)op->nd * (k + 1) * sizeof(double));  // vectors u_0..u_{k-1} and one more
     b += gather_bytes(op, SPARC_F64, 1);                                  // gathered projections
-    b += align_up((size_t)(4 * k + 8) * sizeof(double));                  // alpha, beta, coeff, norm
-    b += align_up((size_t)kRedBlocks * (k + 3) * sizeof(double));         // block partial sums
-    b += align_up((size_t)step_dot_blocks(op) * sizeof(double));           // v^T H_loc v partials
+    b += align_up((size_t)(4 * k + 8) * sizeof(double));                  // alpha, nu
+    b += align_up((size_t)kRedBlocks * (k + 3) * sizeof(double));         // partials: inner products, |w|^2 twice
+    b += align_up((size_t)lanczos_dot_blocks(op) * sizeof(double));        // u^T H_loc u partials
     b += align_up((size_t)(3 * (k + 2) + k + 1) * sizeof(double));        // omega rows, ||T|| per step
     b += align_up((size_t)(2 * k + 1) * sizeof(int));                       // reorthogonalisation flags per step
     return b;
@@ -782,73 +849,75 @@ int sparc_lanczos(const sparc_op *op, int32_t k, const double *v0, double *alpha
     hipStream_t s = (hipStream_t)stream;
     const long long n = op->nd;
     char *p = (char *)ws;
-    double *V = (double *)p;  // k+1 vectors of n (the last is w)
+    double *V = (double *)p;  // k+1 vectors of n
     p += align_up((size_t)n * (k + 1) * sizeof(double));
     double *G = (double *)p;
     p += gather_bytes(op, SPARC_F64, 1);
     double *d_alpha = (double *)p;
-    double *d_beta = d_alpha + k;
-    double *d_coeff = d_beta + k;       // k + 1 entries (coefficients and |w|^2)
-    double *d_norm = d_coeff + k + 2;
+    double *d_nu = d_alpha + k;  // k + 1 entries; beta_j = nu_{j+1}
     p += align_up((size_t)(4 * k + 8) * sizeof(double));
-    double *partial = (double *)p;                        // inner products, k + 2 per block
-    double *npart = partial + (size_t)kRedBlocks * (k + 2);  // |w|^2, one per block
+    double *partial = (double *)p;  // inner products (kDotBlocks per vector)
+    double *npart[2];               // |w|^2, one per block, by the parity of the step
+    npart[0] = partial + (size_t)kDotBlocks * (k + 1);
+    npart[1] = npart[0] + kRedBlocks;
     p += align_up((size_t)kRedBlocks * (k + 3) * sizeof(double));
-    double *dotp = (double *)p;  // step kernel partials of v_j^T H_loc v_j
-    const int ndot = (int)step_dot_blocks(op);
+    double *dotp = (double *)p;  // step kernel partials of u_j^T H_loc u_j
+    const int ndot = (int)lanczos_dot_blocks(op);
     p += align_up((size_t)ndot * sizeof(double));
     double *rows = (double *)p;  // three rows of orthogonality estimates, k + 2 entries each
     double *d_anorm = rows + 3 * (k + 2);  // ||T|| estimate after each step (k + 1)
     p += align_up((size_t)(3 * (k + 2) + k + 1) * sizeof(double));
     int *d_owed = (int *)p;     // k + 1: orthogonalise the vector of step j regardless
     int *d_full = d_owed + k + 1;  // k: the vector of step j is orthogonalised
-    double *w = V + (long long)k * n;
     const double eps1 = 0.5 * std::sqrt((double)n) * 2.220446049250313e-16;
 
     const dim3 rg(kRedBlocks), tb(256);
     int st;
-    hipLaunchKernelGGL(omega_init, dim3(1), tb, 0, s, rows, k + 2, d_owed, d_anorm);
-    // V_0 = v0 / |v0|
-    hipLaunchKernelGGL(multidot_kernel, rg, tb, 0, s, v0, (long long)n, 0, v0, n, npart);
-    hipLaunchKernelGGL(scale_by_norm, rg, tb, 0, s, V, v0, d_norm, (const double *)npart, (const int *)nullptr, n);
+    hipLaunchKernelGGL(omega_init, dim3(1), tb, 0, s, rows, k + 2, d_owed, d_anorm, d_nu);
+    // u_0 = v0 / |v0|
+    hipLaunchKernelGGL(norm2_kernel, rg, tb, 0, s, v0, n, npart[1]);
+    hipLaunchKernelGGL(scale_by_norm, rg, tb, 0, s, V, v0, (const double *)npart[1], n);
     const int nproj = op->nproj_total;
+    const bool fused = op->natoms > 0 && nproj <= kLanczosProj;
+    const LanczosScatter sc{op->d_nl_seg, op->d_nl_pts, op->d_nl_off, (const int4 *)op->d_nl_ent, op->d_nl_proj,
+                            op->d_chi64};
     for (int j = 0; j < k; ++j) {
-        double *vj = V + (long long)j * n;
-        // w = H v_j, with the two parts of alpha_j = v_j^T H v_j left as partials
-        if ((st = launch_lanczos_h_f64(op, vj, w, dotp, G, s))) return st;
-        if ((st = launch_scatter(op, SPARC_F64, w, n, 1, G, kGatherSplit, 1.0, s))) return st;
+        double *uj = V + (long long)j * n, *w = uj + n;
+        // w = H_loc u_j, with the two parts of u_j^T H u_j left as partials
+        if ((st = launch_lanczos_h_f64(op, uj, w, dotp, G, s))) return st;
+        const LanczosAlpha q{dotp, ndot, G, op->d_hg64, nproj, j > 0 ? d_full + j - 1 : nullptr, npart[(j + 1) & 1]};
         if (j + 1 == k) {
-            hipLaunchKernelGGL(alpha_finish, dim3(1), tb, 0, s, (const double *)dotp, ndot, (const double *)G,
-                               (const double *)op->d_hg64, nproj, d_alpha + j);
+            hipLaunchKernelGGL(alpha_finish, dim3(1), tb, 0, s, q, d_nu + j, d_alpha + j);
             break;
         }
-        // alpha_j; w -= alpha_j v_j + beta_{j-1} v_{j-1}; partials of |w|^2
-        hipLaunchKernelGGL(lanczos_3term, rg, tb, 0, s, w, (const double *)vj, (const double *)(vj - (j > 0 ? n : 0)),
-                           (const double *)dotp, ndot, (const double *)G, (const double *)op->d_hg64, nproj,
-                           d_alpha + j, (const double *)(j > 0 ? d_beta + j - 1 : nullptr), n, npart);
-        // beta_j, the orthogonality estimates and, when they ask for it, the
-        // inner products of one classical Gram-Schmidt pass against
-        // v_0 .. v_j, whose new |w|^2 partials the scaling kernel finishes
-        // into beta_j
+        // w += V_nl u_j; alpha_j; w / nu_j - alpha_j v_j - beta_{j-1} v_{j-1}; partials of |w|^2
+        const double *ujm = j > 0 ? uj - n : nullptr;
+        if (fused) {
+            hipLaunchKernelGGL(lanczos_3term<true>, rg, tb, 0, s, w, (const double *)uj, ujm, q, sc, d_nu + j,
+                               d_alpha + j, n, npart[j & 1]);
+        } else {
+            if ((st = launch_scatter(op, SPARC_F64, w, n, 1, G, kGatherSplit, 1.0, s))) return st;
+            hipLaunchKernelGGL(lanczos_3term<false>, rg, tb, 0, s, w, (const double *)uj, ujm, q, sc, d_nu + j,
+                               d_alpha + j, n, npart[j & 1]);
+        }
+        // beta_j, the orthogonality estimates and, when they ask for it, one
+        // classical Gram-Schmidt pass against v_0 .. v_j, whose new |w|^2
+        // partials the next step finishes into beta_j
         const double *Wc = rows + (size_t)(j % 3) * (k + 2);
         const double *Wp = rows + (size_t)((j + 2) % 3) * (k + 2);
         double *Wn = rows + (size_t)((j + 1) % 3) * (k + 2);
         const int nv = j + 1;
-        const int *full = d_full + j;
-        hipLaunchKernelGGL(omega_dots_kernel, rg, tb, 0, s, (const double *)d_alpha, d_beta, j, eps1, Wp, Wc, Wn,
-                           d_owed, d_full, d_anorm, (const double *)npart, (const double *)V, (long long)n,
+        hipLaunchKernelGGL(omega_dots_kernel, rg, tb, 0, s, (const double *)d_alpha, d_nu + 1, j, eps1, Wp, Wc, Wn,
+                           d_owed, d_full, d_anorm, (const double *)npart[j & 1], (const double *)V, (long long)n,
                            (const double *)w, n, partial);
-        hipLaunchKernelGGL(finish_sums, dim3(nv), tb, 0, s, (const double *)partial, nv + 1, d_coeff, nullptr, -1, 0,
-                           full);
-        hipLaunchKernelGGL(orth_apply_norm, rg, tb, 0, s, w, V, (long long)n, nv, d_coeff, n, npart, full);
-        hipLaunchKernelGGL(scale_by_norm, rg, tb, 0, s, vj + n, (const double *)w, d_beta + j, (const double *)npart,
-                           full, n);
+        hipLaunchKernelGGL(orth_apply_norm, rg, tb, nv * sizeof(double), s, w, (const double *)V, (long long)n, nv,
+                           (const double *)partial, (const double *)d_nu, n, npart[j & 1], (const int *)(d_full + j));
         SPARC_HIP(hipGetLastError());
     }
     SPARC_HIP(hipGetLastError());
     std::vector<double> ha(k), hb(std::max(1, k - 1));
     SPARC_HIP(hipMemcpyAsync(ha.data(), d_alpha, k * sizeof(double), hipMemcpyDeviceToHost, s));
-    if (k > 1) SPARC_HIP(hipMemcpyAsync(hb.data(), d_beta, (k - 1) * sizeof(double), hipMemcpyDeviceToHost, s));
+    if (k > 1) SPARC_HIP(hipMemcpyAsync(hb.data(), d_nu + 1, (k - 1) * sizeof(double), hipMemcpyDeviceToHost, s));
     SPARC_HIP(hipStreamSynchronize(s));
     for (int j = 0; j + 1 < k; ++j)
         if (!(hb[j] > 0.0) || !std::isfinite(hb[j])) return fail(SPARC_E_BREAKDOWN, "Lanczos breakdown at step " + std::to_string(j));

@@ -49,7 +49,8 @@ namespace sparc {
 // FP32 blocks)
 const TileShape kShapes[kNumShapes] = {{32, 2, 256}, {32, 2, 512}};
 
-// H v for one FP64 vector in one launch: the first ngather workgroups gather
+// H v for one FP64 vector in one launch, for the grids the 16-byte kernels of
+// vstep.hip do not take (rows of one node): the first ngather workgroups gather
 // the projections of v (atom i % natoms, split i / natoms, as the standalone
 // gather), the rest run the DOT step on 32 x 16 patches.  ngather is a
 // multiple of 8, so the step's XCD-aware index remap still sees the hardware
@@ -152,7 +153,7 @@ static StepLaunch dot_launch(const sparc_op *op)
     return L;
 }
 
-long long step_dot_blocks(const sparc_op *op)
+static long long step_dot_blocks(const sparc_op *op)
 {
     const TileShape &s = kShapes[0];
     const StepLaunch L = dot_launch(op);
@@ -160,9 +161,12 @@ long long step_dot_blocks(const sparc_op *op)
            ((op->n[2] + s.tz - 1) / s.tz);
 }
 
+long long lanczos_dot_blocks(const sparc_op *op) { return vstep_takes(op) ? vstep_blocks(op) : step_dot_blocks(op); }
+
 int launch_lanczos_h_f64(const sparc_op *op, const double *v, double *out, double *dot, double *part,
                          hipStream_t stream)
 {
+    if (vstep_takes(op)) return launch_vstep_gather(op, v, out, dot, part, stream);
     const TileShape &s = kShapes[0];
     const StepLaunch L = dot_launch(op);
     StepArgs<double, double> a;

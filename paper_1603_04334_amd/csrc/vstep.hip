@@ -33,6 +33,31 @@ __device__ __forceinline__ void store_partial(double v, double *dot, int b)
     }
 }
 
+// H u for Lanczos: the first ngather workgroups gather the projections of u
+// (atom i % natoms, split i / natoms, as the standalone gather; ngather is a
+// multiple of 8, so the step's XCD-aware index remap still sees the hardware
+// round-robin), the rest step
+template <int RAG>
+__global__ void __launch_bounds__(kVThreads)
+    vstep_gather_kernel(const FStepArgs<double> a, const GatherArgs<double, double> g, int natoms, int ngather,
+                        double *dot)
+{
+    using K = FStep<double, kVTY, false, false, 1, kVTZ, true, true, RAG>;
+    __shared__ __align__(16) union {
+        typename K::Shared step;
+        double tile[4][16][16];
+    } sh;
+    static_assert(kVThreads == 256, "one gather item per workgroup");
+    if ((int)blockIdx.x < ngather) {
+        gather_item<double, double>(g, blockIdx.x % natoms, 0, blockIdx.x / natoms, sh.tile, threadIdx.x);
+        return;
+    }
+    const int b = blockIdx.x - ngather;
+    K k(a);
+    k.run(b, sh.step);
+    store_partial(k.dacc, dot, b);
+}
+
 // done: the launch is skipped when *done < iter (null: never)
 template <bool POT, int RAG>
 __global__ void __launch_bounds__(kVThreads)
@@ -68,8 +93,7 @@ bool vstep_takes(const sparc_op *op) { return op->n[2] >= 2 && vstep_plan(op).bl
 
 long long vstep_blocks(const sparc_op *op) { return vstep_plan(op).blocks(); }
 
-int launch_vstep(const sparc_op *op, const double *v, double *out, double alpha, bool pot, double *dot, const int *done,
-                 int iter, hipStream_t stream)
+static FStepArgs<double> vstep_args(const sparc_op *op, const double *v, double *out, double alpha)
 {
     const VPlan p = vstep_plan(op);
     FStepArgs<double> a;
@@ -91,6 +115,38 @@ int launch_vstep(const sparc_op *op, const double *v, double *out, double alpha,
     a.c0 = -3.0 * op->w[0];
     for (int q = 1; q <= kMaxRadius; ++q) a.cp[q - 1] = -0.5 * op->w[q];
     a.alpha = alpha;
+    return a;
+}
+
+int launch_vstep_gather(const sparc_op *op, const double *v, double *out, double *dot, double *part, hipStream_t stream)
+{
+    const FStepArgs<double> a = vstep_args(op, v, out, 1.0);
+    GatherArgs<double, double> g;
+    std::memset(&g, 0, sizeof(g));
+    g.Y = v;
+    g.ldy = op->nd;
+    g.ns = 1;
+    g.nproj_total = op->nproj_total;
+    g.small = op->nd < kUnit;
+    g.atoms = op->d_atoms;
+    g.box_off = op->d_box_off;
+    g.chi = op->d_chi64;
+    g.part = part;
+    const int ngather = op->natoms * kGatherSplit;
+    const dim3 grid((unsigned)(ngather + a.nblocks)), blk(kVThreads);
+    ProfScope prof(3, stream);
+    if (op->n[2] & 1)
+        hipLaunchKernelGGL(vstep_gather_kernel<1>, grid, blk, 0, stream, a, g, std::max(1, op->natoms), ngather, dot);
+    else
+        hipLaunchKernelGGL(vstep_gather_kernel<0>, grid, blk, 0, stream, a, g, std::max(1, op->natoms), ngather, dot);
+    SPARC_HIP(hipGetLastError());
+    return SPARC_OK;
+}
+
+int launch_vstep(const sparc_op *op, const double *v, double *out, double alpha, bool pot, double *dot, const int *done,
+                 int iter, hipStream_t stream)
+{
+    const FStepArgs<double> a = vstep_args(op, v, out, alpha);
     const dim3 grid((unsigned)a.nblocks), blk(kVThreads);
     const bool rag = op->n[2] & 1;
     if (pot && rag)
