@@ -33,8 +33,8 @@
 namespace sparc {
 
 constexpr int kEigMax = 64;
-constexpr int kEigThreads = 1024;
 
+template <int NT>
 __device__ inline double block_sum_eig(double v, double *red)
 {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -42,7 +42,7 @@ __device__ inline double block_sum_eig(double v, double *red)
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     double t = 0.0;
-    for (int w = 0; w < kEigThreads / 64; ++w) t += red[w];
+    for (int w = 0; w < NT / 64; ++w) t += red[w];
     return t;
 }
 
@@ -109,7 +109,11 @@ __device__ inline void round_pair(int np, int r, int k, int &p, int &q)
     }
 }
 
-__global__ void __launch_bounds__(kEigThreads) small_sygv_kernel(const double *__restrict__ Hs,
+// NT threads: (n/2)^2 of them own a block of C, and a barrier costs the more
+// the more waves meet at it: 64 for n <= 16, 256 for n <= 32, 1024 beyond
+// (8 columns: 41 -> 36 us per solve; the rest is the dependent chain).
+template <int NT>
+__global__ void __launch_bounds__(NT) small_sygv_kernel(const double *__restrict__ Hs,
                                                                   const double *__restrict__ Ms, int n,
                                                                   double *theta, double *evec, int *info,
                                                                   int max_sweeps)
@@ -117,14 +121,14 @@ __global__ void __launch_bounds__(kEigThreads) small_sygv_kernel(const double *_
     __shared__ double CB[2][kEigMax][kEigMax + 1];  // C, double-buffered across Jacobi rounds
     __shared__ double Z[kEigMax][kEigMax + 1];
     __shared__ double L[kEigMax][kEigMax + 1];
-    __shared__ double red[kEigThreads / 64];
+    __shared__ double red[NT / 64];
     __shared__ double lam[kEigMax];
     __shared__ double2 rcs[kEigMax / 2];                 // (c, s) of each pair of the round
     __shared__ unsigned short rpq[kEigMax - 1][kEigMax / 2];  // p | q << 8 per round and pair
     __shared__ int rank[kEigMax];
     __shared__ int bad;
     const int tid = threadIdx.x;
-    const int nt = blockDim.x;
+    constexpr int nt = NT;
     const int np = n + (n & 1);
     double (*C)[kEigMax + 1] = CB[0];
 
@@ -163,12 +167,14 @@ __global__ void __launch_bounds__(kEigThreads) small_sygv_kernel(const double *_
 
     // 2. X = L^{-1} (in Z): row i needs rows k < i; 16 lanes share each entry
     for (int i = 0; i < n; ++i) {
-        const int c = tid >> 4, part = tid & 15;
-        double acc = 0.0;
-        if (c < i)
-            for (int k = c + part; k < i; k += 16) acc += L[i][k] * Z[k][c];
-        for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 16);
-        if (part == 0 && c < n) Z[i][c] = c < i ? -acc / L[i][i] : (c == i ? 1.0 / L[i][i] : 0.0);
+        for (int c = tid >> 4; c < n; c += nt / 16) {
+            const int part = tid & 15;
+            double acc = 0.0;
+            if (c < i)
+                for (int k = c + part; k < i; k += 16) acc += L[i][k] * Z[k][c];
+            for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 16);
+            if (part == 0) Z[i][c] = c < i ? -acc / L[i][i] : (c == i ? 1.0 / L[i][i] : 0.0);
+        }
         __syncthreads();
     }
     // W = X H_s (CB[1]), C = W X^T (CB[0]), symmetrised
@@ -221,8 +227,8 @@ __global__ void __launch_bounds__(kEigThreads) small_sygv_kernel(const double *_
             tot += v;
             if (i != j) off += v;
         }
-        off = block_sum_eig(off, red);
-        tot = block_sum_eig(tot, red);
+        off = block_sum_eig<NT>(off, red);
+        tot = block_sum_eig<NT>(tot, red);
         if (!(off > 1e-30 * tot)) {
             converged = true;
             break;
@@ -295,7 +301,12 @@ int launch_small_sygv(const double *Hs, const double *Ms, int n, double *theta, 
                       hipStream_t stream)
 {
     if (n < 1 || n > kEigMax) return fail(SPARC_E_ARG, "small eigensolver needs 1 <= n <= 64");
-    hipLaunchKernelGGL(small_sygv_kernel, dim3(1), dim3(kEigThreads), 0, stream, Hs, Ms, n, theta, evec, info, 40);
+    if (n <= 16)
+        hipLaunchKernelGGL(small_sygv_kernel<64>, dim3(1), dim3(64), 0, stream, Hs, Ms, n, theta, evec, info, 40);
+    else if (n <= 32)
+        hipLaunchKernelGGL(small_sygv_kernel<256>, dim3(1), dim3(256), 0, stream, Hs, Ms, n, theta, evec, info, 40);
+    else
+        hipLaunchKernelGGL(small_sygv_kernel<1024>, dim3(1), dim3(1024), 0, stream, Hs, Ms, n, theta, evec, info, 40);
     SPARC_HIP(hipGetLastError());
     return SPARC_OK;
 }

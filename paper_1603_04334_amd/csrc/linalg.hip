@@ -24,6 +24,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstdio>
+#include <cstring>
 #include <map>
 #include <vector>
 
@@ -575,28 +576,41 @@ __global__ void __launch_bounds__(256, 2) rr_project_kernel(const TY *__restrict
             }
 }
 
-// Ms, Hs (column-major ns x ns) = sum over chunks of the partial tiles, in
-// chunk order, for the entries of the upper tiles (row tile <= column tile)
-__global__ void rr_reduce_kernel(const double *partial, int nchunks, int ns, double *Ms, double *Hs)
+// Ms, Hs (column-major ns x ns) = sum over chunks of the partial tiles for the
+// entries on and above the diagonal, each written to both triangles.  G lanes
+// share an entry (chunks dealt round-robin, their sums added in lane order): a
+// small matrix has few entries and many chunks, and one lane per entry walked
+// them in 17 us for 8 columns of 24^3; 16 consecutive entries per group keep
+// the loads whole lines.
+template <int G>
+__global__ void __launch_bounds__(256) rr_reduce_kernel(const double *partial, int nchunks, int ns, double *Ms,
+                                                        double *Hs)
 {
+    constexpr int E = 256 / G;  // entries per workgroup
+    __shared__ double sum[G][E];
     const long long mat = (long long)ns * ns;
-    const long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (e >= 2 * mat) return;
+    const long long e = blockIdx.x * (long long)E + threadIdx.x % E;
+    const int g = threadIdx.x / E;
     const long long which = e / mat, off = e - which * mat;
     const int row = (int)(off % ns), col = (int)(off / ns);
-    if (row / kRrTile > col / kRrTile) return;
+    const bool upper = e < 2 * mat && row <= col;
     double s = 0.0;
+    if (upper) {
 #pragma unroll 16
-    for (int c = 0; c < nchunks; ++c) s += partial[((long long)c * 2 + which) * mat + off];
-    (which == 0 ? Ms : Hs)[off] = s;
-}
-
-// the lower triangle of an ns x ns column-major matrix copied from the upper
-__global__ void mirror_upper(double *A, int ns)
-{
-    const int i = blockIdx.y * blockDim.y + threadIdx.y;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < ns && j < ns && i < j) A[(long long)i * ns + j] = A[(long long)j * ns + i];
+        for (int c = g; c < nchunks; c += G) s += partial[((long long)c * 2 + which) * mat + off];
+    }
+    if (G > 1) {
+        sum[g][threadIdx.x % E] = s;
+        __syncthreads();
+        if (g > 0) return;
+        s = 0.0;
+#pragma unroll
+        for (int k = 0; k < G; ++k) s += sum[k][threadIdx.x % E];
+    }
+    if (!upper) return;
+    double *A = which == 0 ? Ms : Hs;
+    A[off] = s;
+    A[(long long)row * ns + col] = s;
 }
 
 static dim3 stream_grid(long long n)
@@ -674,6 +688,42 @@ __global__ void __launch_bounds__(256) rotate_kernel(const T *__restrict__ Y, lo
         for (int c = 0; c < NC; ++c)
             if (c0 + c < ns) out[(long long)(c0 + c) * ldo + x] = acc[c];
     }
+}
+
+// The same sums for up to NC <= 16 columns straight from the FP64 rotation
+// (rounded to T as it is read, wave-uniform): no padded copy and no products
+// with padding.  24^3 x 8 FP64: 6 us instead of 13 + 3 us.
+constexpr int kRotSmall = 16;
+template <typename T, int NC>
+__global__ void __launch_bounds__(256) rotate_small_kernel(const T *__restrict__ Y, long long ldy,
+                                                           const double *__restrict__ Q, T *__restrict__ out,
+                                                           long long ldo, long long nd, int ns)
+{
+    const long long x = blockIdx.x * 256LL + threadIdx.x;
+    if (x >= nd) return;
+    T y[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) y[j] = j < ns ? Y[(long long)j * ldy + x] : T(0);
+#pragma unroll 2
+    for (int c = 0; c < ns; ++c) {
+        T t = T(0);
+#pragma unroll
+        for (int j = 0; j < NC; ++j) t += y[j] * (j < ns ? (T)Q[(long long)c * ns + j] : T(0));
+        out[(long long)c * ldo + x] = t;
+    }
+}
+
+template <typename T>
+static void launch_rotate_small(const T *Y, long long ldy, const double *Q, T *out, long long ldo, long long nd, int ns,
+                                hipStream_t s)
+{
+    const dim3 g((unsigned)((nd + 255) / 256)), b(256);
+    if (ns <= 4)
+        hipLaunchKernelGGL((rotate_small_kernel<T, 4>), g, b, 0, s, Y, ldy, Q, out, ldo, nd, ns);
+    else if (ns <= 8)
+        hipLaunchKernelGGL((rotate_small_kernel<T, 8>), g, b, 0, s, Y, ldy, Q, out, ldo, nd, ns);
+    else
+        hipLaunchKernelGGL((rotate_small_kernel<T, 16>), g, b, 0, s, Y, ldy, Q, out, ldo, nd, ns);
 }
 
 // ---------------------------------------------------------------- BLAS handles
@@ -949,7 +999,7 @@ size_t sparc_rr_workspace_bytes(const sparc_op *op, int32_t dtype, int32_t ns)
     b += align_up((size_t)op->nd * ns * sizeof(double));                           // H Y
     b += gather_bytes(op, SPARC_F64, ns);                                           // gathered projections
     b += 2 * align_up((size_t)ns * ns * sizeof(double));                           // H_s, M_s
-    b += 2 * align_up((size_t)ns * sizeof(double)) + align_up(sizeof(int));       // D, E, info
+    b += align_up(((size_t)ns + 1) * sizeof(double)) + align_up((size_t)ns * sizeof(double));  // D and info, E
     const long long nch = (op->nd + rr_chunk(op->nd, ns) - 1) / rr_chunk(op->nd, ns);
     b += align_up((size_t)nch * 2 * ns * ns * sizeof(double));                     // projection partials
     return b;
@@ -980,12 +1030,11 @@ int sparc_rayleigh_ritz(const sparc_op *op, int32_t dtype, const void *Y, int64_
     p += align_up((size_t)ns * ns * sizeof(double));
     double *Ms = (double *)p;
     p += align_up((size_t)ns * ns * sizeof(double));
-    double *D = (double *)p;
-    p += align_up((size_t)ns * sizeof(double));
+    double *D = (double *)p;  // ns values, then the solver's status
+    int *info = (int *)(D + ns);
+    p += align_up(((size_t)ns + 1) * sizeof(double));
     double *E = (double *)p;
     p += align_up((size_t)ns * sizeof(double));
-    int *info = (int *)p;
-    p += align_up(sizeof(int));
     double *partial = (double *)p;
 
     int st;
@@ -1011,15 +1060,17 @@ int sparc_rayleigh_ritz(const sparc_op *op, int32_t dtype, const void *Y, int64_
                            nd, ns, kc, partial);
     }
     const long long tot = 2LL * ns * ns;
-    hipLaunchKernelGGL(rr_reduce_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, partial, nch, ns, Ms, Hs);
-    dim3 tb(16, 16), tg((ns + 15) / 16, (ns + 15) / 16);
-    hipLaunchKernelGGL(mirror_upper, tg, tb, 0, s, Hs, ns);
-    hipLaunchKernelGGL(mirror_upper, tg, tb, 0, s, Ms, ns);
+    if (ns <= 64)
+        hipLaunchKernelGGL(rr_reduce_kernel<16>, dim3((unsigned)((tot + 15) / 16)), dim3(256), 0, s, partial, nch, ns, Ms,
+                           Hs);
+    else
+        hipLaunchKernelGGL(rr_reduce_kernel<1>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, partial, nch, ns,
+                           Ms, Hs);
     SPARC_HIP(hipGetLastError());
 
     if (ns <= 64) {
-        // one-workgroup Cholesky + Jacobi; eigenvectors land in Hs
-        if ((st = launch_small_sygv(Hs, Ms, ns, D, Hs, info, s))) return st;
+        // one-workgroup Cholesky + Jacobi
+        if ((st = launch_small_sygv(Hs, Ms, ns, D, evec ? evec : Hs, info, s))) return st;
     } else {
         BlasLease lease(s);
         rocblas_handle hb = lease.h;
@@ -1068,11 +1119,15 @@ int sparc_rayleigh_ritz(const sparc_op *op, int32_t dtype, const void *Y, int64_
                                                                  ns, &one, Ms, ns, Hs, ns))))
             return st;
     }
-    int hinfo = 0;
-    SPARC_HIP(hipMemcpyAsync(theta, D, ns * sizeof(double), hipMemcpyDeviceToHost, s));
-    SPARC_HIP(hipMemcpyAsync(&hinfo, info, sizeof(int), hipMemcpyDeviceToHost, s));
-    if (evec) SPARC_HIP(hipMemcpyAsync(evec, Hs, (size_t)ns * ns * sizeof(double), hipMemcpyDeviceToDevice, s));
+    // Ritz values and the solver's status in one copy
+    std::vector<double> host((size_t)ns + 1);
+    SPARC_HIP(hipMemcpyAsync(host.data(), D, ((size_t)ns + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
+    if (evec && ns > 64)
+        SPARC_HIP(hipMemcpyAsync(evec, Hs, (size_t)ns * ns * sizeof(double), hipMemcpyDeviceToDevice, s));
     SPARC_HIP(hipStreamSynchronize(s));
+    std::copy(host.begin(), host.begin() + ns, theta);
+    int hinfo;
+    std::memcpy(&hinfo, &host[ns], sizeof(int));
     if (hinfo != 0) {
         if (ns <= 64 && hinfo == ns + 1)
             return fail(SPARC_E_BREAKDOWN, "Jacobi eigensolver did not converge within its sweep limit");
@@ -1145,6 +1200,14 @@ int sparc_rotate(int32_t dtype, const void *Y, int64_t ldy, int64_t nd, int32_t 
         if (rs != rocblas_status_success)
             return fail(SPARC_E_HIP, std::string("rocBLAS GEMM of the rotation failed: ") + rocblas_status_to_string(rs));
         if (after != hipSuccess) return fail(SPARC_E_HIP, std::string("rotation: ") + hipGetErrorString(after));
+        return SPARC_OK;
+    }
+    if (ns <= kRotSmall) {
+        if (dtype == SPARC_F64)
+            launch_rotate_small((const double *)Y, ldy, Q, (double *)out, ldo, nd, ns, s);
+        else
+            launch_rotate_small((const float *)Y, ldy, Q, (float *)out, ldo, nd, ns, s);
+        SPARC_HIP(hipGetLastError());
         return SPARC_OK;
     }
     if (dtype == SPARC_F64) {
