@@ -11,13 +11,22 @@
 // exactly: F lives on the cube widened by the stencil radius along d, is a
 // property of the operator, and is built once (host, FP64) on the first call.
 // Y and the three W components are then four projector-like contractions of
-// the same block, which run on the matrix cores through the gather of the
-// nonlocal operator (one gather record per atom and contraction, 4 natoms
-// records in one launch), reading each orbital once per record instead of
-// forming 3 N_s gradient fields.  A second kernel, one workgroup per atom,
-// sums the split partials in a fixed order and reduces over orbitals and
-// projectors in a fixed order, so the forces are reproducible bit for bit.
+// the same nodes.  An atom's nodes are read once: the cube's rows, widened along
+// z, with all 4 nproj functions as columns of the matrix product, then the arms
+// that widen the cube along x and y with the one function set that is not zero
+// there.  Large launches give an atom and 32 orbitals to one workgroup, which
+// reduces its contractions to the three force components of its orbitals on
+// the spot; small ones split the nodes over workgroups.  Either way a second
+// kernel adds in a fixed order, so the forces are reproducible bit for bit.
 // FP32 blocks are widened as they are loaded; all sums are FP64.
+//
+// What bounds it: the lines of the short node rows, 843 per atom and orbital at
+// 160^3.  Orbital blocks run fastest, so that an atom's functions stay in the
+// cache (2.24 against 2.38 ms with atoms fastest); two blocks of 16 orbitals
+// share the function loads (2.38 against 2.78 ms with one).  128 atoms, 9
+// projectors, 600 FP32 orbitals: 5.34 -> 2.26 ms (8.3 GB of lines at 3.7 TB/s);
+// with the four boxes as records of their own it read 1701 lines per atom and
+// orbital.  16 atoms x 200 orbitals at 96^3: 146 -> 72 us.
 #include <algorithm>
 #include <vector>
 
@@ -37,6 +46,19 @@ void gradient_weights(int no, double h, double *w)
     }
 }
 
+// one box of units of an atom with nf functions on it ([function][unit][4])
+struct ForceBox {
+    int unit0, nunits;
+    long long fun0;
+    int nf;
+};
+// the atom's boxes: the cube's rows widened along z with the functions chi, F_x,
+// F_y, F_z (nproj each), and the arms along x and y with F_x and F_y
+struct ForceAtom {
+    ForceBox box[3];
+    int nproj, proj0;
+};
+
 int build_force_tables(const sparc_op *op)
 {
     const int natoms = op->natoms;
@@ -48,64 +70,93 @@ int build_force_tables(const sparc_op *op)
     std::vector<double> chi(chi_total);
     SPARC_HIP(hipMemcpy(chi.data(), op->d_chi64, chi_total * sizeof(double), hipMemcpyDeviceToHost));
 
-    std::vector<AtomDev> rec;
-    std::vector<int> boff, upos;
-    std::vector<double> fun;
-    rec.reserve(4 * natoms);
+    // the boxes' parts (the widened rows; the arms below and above the cube),
+    // their units and the position of each of their nodes in the box
+    struct Part {
+        int lo[3], ext[3];
+        std::vector<int> at;
+    };
+    std::vector<ForceAtom> rec(natoms);
+    std::vector<std::vector<Part>> parts(3 * natoms);
+    std::vector<int> units;
+    size_t nfun = 0;
     for (int J = 0; J < natoms; ++J) {
         const AtomDev &A = op->atoms[J];
-        const int cube = A.ext[0] * A.ext[1] * A.ext[2];
-        // chi of atom J at grid node z (zero off the cube)
-        auto chi_at = [&](int p, const int z[3]) {
-            for (int e = 0; e < 3; ++e)
-                if (z[e] < A.lo[e] || z[e] >= A.lo[e] + A.ext[e]) return 0.0;
-            const int idx = ((z[0] - A.lo[0]) * A.ext[1] + (z[1] - A.lo[1])) * A.ext[2] + (z[2] - A.lo[2]);
-            return chi[A.chi0 + (int64_t)p * cube + idx];
-        };
-        for (int r = 0; r < 4; ++r) {
-            AtomDev F = A;
-            const int d = r - 1;
-            if (r > 0) {
-                F.lo[d] = std::max(0, A.lo[d] - R);
-                F.ext[d] = std::min(op->n[d], A.lo[d] + A.ext[d] + R) - F.lo[d];
+        ForceAtom &F = rec[J];
+        F.nproj = A.nproj;
+        F.proj0 = A.proj0;
+        for (int k = 0; k < 3; ++k) {
+            ForceBox &B = F.box[k];
+            B.unit0 = (int)(units.size() / 2);
+            B.fun0 = (long long)nfun;
+            B.nf = k == 0 ? 4 * A.nproj : A.nproj;
+            B.nunits = 0;
+            auto part = [&](int axis, int from, int to) {
+                from = std::max(from, 0);
+                to = std::min(to, op->n[axis]);
+                if (from >= to) return;
+                Part P;
+                for (int e = 0; e < 3; ++e) {
+                    P.lo[e] = e == axis ? from : A.lo[e];
+                    P.ext[e] = e == axis ? to - from : A.ext[e];
+                }
+                const int first = 4 * B.nunits;
+                B.nunits += append_units(op->n, op->nd, P.lo, P.ext, units, P.at);
+                for (int &o : P.at) o += first;
+                parts[3 * J + k].push_back(std::move(P));
+            };
+            if (k == 0) {
+                part(2, A.lo[2] - R, A.lo[2] + A.ext[2] + R);
+            } else {
+                const int d = k - 1;
+                part(d, A.lo[d] - R, A.lo[d]);
+                part(d, A.lo[d] + A.ext[d], A.lo[d] + A.ext[d] + R);
             }
-            F.proj0 = 4 * A.proj0 + r * A.nproj;
-            if (boff.size() > 0x7fffffffULL) return fail(SPARC_E_SHAPE, "force tables too large");
-            F.unit0 = (int)(boff.size() / 2);
-            F.chiu0 = (long long)fun.size();
-            upos.clear();
-            F.nunits = append_units(op->n, op->nd, F.lo, F.ext, boff, upos);
-            const int nb = 4 * F.nunits;
-            fun.resize(fun.size() + (size_t)nb * A.nproj, 0.0);
-            double *out = fun.data() + F.chiu0;
-            for (int p = 0; p < A.nproj; ++p) {
-                int t = 0;
-                for (int i = 0; i < F.ext[0]; ++i)
-                    for (int j = 0; j < F.ext[1]; ++j)
-                        for (int k = 0; k < F.ext[2]; ++k, ++t) {
-                            const int y[3] = {F.lo[0] + i, F.lo[1] + j, F.lo[2] + k};
-                            double v;
-                            if (r == 0) {
-                                v = chi_at(p, y);
-                            } else {
-                                // -grad_d chi = sum_q w_q (chi(y - q e_d) - chi(y + q e_d))
-                                v = 0.0;
-                                for (int q = 1; q <= R; ++q) {
-                                    int zm[3] = {y[0], y[1], y[2]}, zp[3] = {y[0], y[1], y[2]};
-                                    zm[d] -= q;
-                                    zp[d] += q;
-                                    v += w[q] * (chi_at(p, zm) - chi_at(p, zp));
+            if (units.size() > 0x7fffffffULL) return fail(SPARC_E_SHAPE, "force tables too large");
+            nfun += 4 * (size_t)B.nunits * B.nf;
+        }
+    }
+    std::vector<double> fun(nfun, 0.0);
+    for (int J = 0; J < natoms; ++J) {
+        const AtomDev &A = op->atoms[J];
+        const int st[3] = {A.ext[1] * A.ext[2], A.ext[2], 1};
+        for (int k = 0; k < 3; ++k) {
+            const ForceBox &B = rec[J].box[k];
+            for (int f = 0; f < B.nf; ++f) {
+                // r = 0: chi; r = 1 + d: -grad_d chi = sum_q w_q (chi(y - q e_d) - chi(y + q e_d)), chi 0 off the cube
+                const int r = k == 0 ? f / A.nproj : k, p = f % A.nproj, d = r - 1;
+                const double *c = chi.data() + A.chi0 + (int64_t)p * st[0] * A.ext[0];
+                double *out = fun.data() + B.fun0 + 4 * (size_t)B.nunits * f;
+                for (const Part &P : parts[3 * J + k]) {
+                    size_t t = 0;
+                    for (int i = 0; i < P.ext[0]; ++i)
+                        for (int j = 0; j < P.ext[1]; ++j)
+                            for (int l = 0; l < P.ext[2]; ++l, ++t) {
+                                const int y[3] = {P.lo[0] + i - A.lo[0], P.lo[1] + j - A.lo[1], P.lo[2] + l - A.lo[2]};
+                                bool in = true;
+                                for (int e = 0; e < 3; ++e)
+                                    if (e != d && (y[e] < 0 || y[e] >= A.ext[e])) in = false;
+                                if (!in) continue;
+                                const double *cy = c + y[0] * st[0] + y[1] * st[1] + y[2];
+                                if (r == 0) {
+                                    out[P.at[t]] = *cy;
+                                    continue;
                                 }
+                                double v = 0.0;
+                                for (int q = 1; q <= R; ++q) {
+                                    const int a = y[d] - q, b = y[d] + q;
+                                    v += w[q] * ((a >= 0 && a < A.ext[d] ? cy[-q * st[d]] : 0.0) -
+                                                 (b >= 0 && b < A.ext[d] ? cy[q * st[d]] : 0.0));
+                                }
+                                out[P.at[t]] = v;
                             }
-                            out[(size_t)p * nb + upos[t]] = v;
-                        }
+                }
             }
-            rec.push_back(F);
         }
     }
     std::vector<double> gam(op->gamma.begin(), op->gamma.end());
-    if (hipMalloc(&op->d_fatoms, rec.size() * sizeof(AtomDev)) != hipSuccess ||
-        hipMalloc(&op->d_funits, boff.size() * sizeof(int)) != hipSuccess ||
+    if (hipMalloc(&op->d_fatoms, rec.size() * sizeof(ForceAtom)) != hipSuccess ||
+        hipMalloc(&op->d_funits, units.size() * sizeof(int)) != hipSuccess ||
         hipMalloc(&op->d_ffun, fun.size() * sizeof(double)) != hipSuccess ||
         hipMalloc(&op->d_fgamma, gam.size() * sizeof(double)) != hipSuccess) {
         for (void **p : {(void **)&op->d_fatoms, (void **)&op->d_funits, (void **)&op->d_ffun,
@@ -115,54 +166,215 @@ int build_force_tables(const sparc_op *op)
         }
         return fail(SPARC_E_NOMEM, "allocation of the force tables failed");
     }
-    SPARC_HIP(hipMemcpy(op->d_fatoms, rec.data(), rec.size() * sizeof(AtomDev), hipMemcpyHostToDevice));
-    SPARC_HIP(hipMemcpy(op->d_funits, boff.data(), boff.size() * sizeof(int), hipMemcpyHostToDevice));
+    SPARC_HIP(hipMemcpy(op->d_fatoms, rec.data(), rec.size() * sizeof(ForceAtom), hipMemcpyHostToDevice));
+    SPARC_HIP(hipMemcpy(op->d_funits, units.data(), units.size() * sizeof(int), hipMemcpyHostToDevice));
     SPARC_HIP(hipMemcpy(op->d_ffun, fun.data(), fun.size() * sizeof(double), hipMemcpyHostToDevice));
     SPARC_HIP(hipMemcpy(op->d_fgamma, gam.data(), gam.size() * sizeof(double), hipMemcpyHostToDevice));
     op->force_ready = true;
     return SPARC_OK;
 }
 
-template <typename TI>
-__global__ void __launch_bounds__(256) force_gather_kernel(const GatherArgs<double, TI> g)
+// acc[s][t] += contraction of orbital block s (16 columns) with functions 16 t
+// .. 16 t + 15 of the box, over this wave's share of its units (groups of 4
+// units dealt round-robin to all the waves; lane (i, k) as in gather_accum)
+template <typename TI, int NT, int NS>
+__device__ __forceinline__ void force_accum(const ForceBox &B, const int2 *__restrict__ units,
+                                            const double *__restrict__ fun, const TI *const (&y)[NS],
+                                            const bool (&ok)[NS], bool small, int waves, int wave, int lane,
+                                            double (&acc)[NS][NT][4])
 {
-    __shared__ double tile[4][16][16];
-    gather_units<double, TI>(g, blockIdx.x, blockIdx.y, blockIdx.z, tile, threadIdx.x);
+    typedef TI VY __attribute__((ext_vector_type(kUnit), aligned(sizeof(TI))));
+    typedef double VC __attribute__((ext_vector_type(kUnit)));
+    const int i = lane & 15, k = lane >> 4;
+    const int2 *un = units + B.unit0;
+    const double *f[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int j = 16 * t + i;
+        f[t] = fun + B.fun0 + (long long)(j < B.nf ? j : 0) * B.nunits * kUnit;
+    }
+    const int nu = B.nunits, step = 4 * waves;
+    int u = 4 * wave + k;
+    int2 qn = un[u < nu ? u : 0];
+#pragma unroll 1
+    for (int u0 = 4 * wave; u0 < nu; u0 += step) {
+        const int2 q = qn;
+        const bool in = u < nu;
+        const int uc = in ? u : 0;
+        u += step;
+        qn = un[u < nu ? u : 0];  // the next unit's offset travels while this one's nodes do
+        VY yv[NS];
+        VC cv[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) cv[t] = *(const VC *)(f[t] + (long long)kUnit * uc);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (!small) {
+                yv[s] = *(const VY *)(y[s] + q.x);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kUnit; ++j) yv[s][j] = (q.y >> j) & 1 ? y[s][q.x + j] : TI(0);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int mask = in && ok[s] ? q.y : 0;
+#pragma unroll
+            for (int j = 0; j < kUnit; ++j) {
+                const double v = (mask >> j) & 1 ? (double)yv[s][j] : 0.0;
+#pragma unroll
+                for (int t = 0; t < NT; ++t) mfma_16x16x4(v, cv[t][j], acc[s][t]);
+            }
+        }
+    }
 }
 
+// S_rp(n) below is the contraction of orbital n with function r of projector p.
+// Whole (!SPLIT): part[(J ncb + cb) 3 + d] = sum over the workgroup's 16 NS
+// orbitals n and the atom's projectors p of occ[n] gamma_p S_0p(n) S_dp(n).
+// SPLIT: the workgroup takes share ks of gridDim.z of the units and writes its
+// part of S, part[(ks 4 nproj_total + 4 proj0 + r nproj + p) ns + n].
+// NT: tiles of 16 functions of the first box (4 nproj <= 16 NT).
+template <typename TI, int NT, int NW, int NS, bool SPLIT>
+__global__ void __launch_bounds__(64 * NW)
+    force_kernel(const TI *__restrict__ psi, long long ld, int ns, int nproj_total,
+                 const ForceAtom *__restrict__ atoms, const int2 *__restrict__ units, const double *__restrict__ fun,
+                 const double *__restrict__ gamma, const double *__restrict__ occ, int small,
+                 double *__restrict__ part)
+{
+    constexpr int NC = 16 * NS;
+    constexpr int G = SPLIT ? 4 : 1;
+    __shared__ double S[G][16 * NT][NC];
+    __shared__ double red[3][NW];
+        const int J = blockIdx.y, cb = blockIdx.x;
+    const ForceAtom &F = atoms[J];
+    const int c0 = cb * NC, np = F.nproj;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15;
+    bool ok[NS];
+    const TI *y[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        ok[s] = c0 + 16 * s + i < ns;
+        y[s] = psi + (long long)(ok[s] ? c0 + 16 * s + i : c0) * ld;
+    }
+    // s[rows 16 t + i][columns] (+)= the wave's sums
+    auto put = [&](double (*s)[NC], const auto &acc, int rows, bool first) {
+#pragma unroll
+        for (int b = 0; b < NS; ++b)
+#pragma unroll
+            for (int t = 0; t < (int)(sizeof(acc[0]) / sizeof(acc[0][0])); ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (16 * t + i >= rows) continue;
+                    double &d = s[16 * t + i][16 * b + acc_row<double>(lane, r)];
+                    d = first ? acc[b][t][r] : d + acc[b][t][r];
+                }
+    };
+    if constexpr (SPLIT) {
+        // half of the waves take the first box (two copies of S), a quarter each
+        // arm (a copy each): one pass over the units, NW / 4 rounds of sums
+        constexpr int NB = NW / 2, NA = NW / 4;
+        const int box = wave < NB ? 0 : 1 + (wave - NB) / NA, w = box ? wave % NA : wave, parts = gridDim.z;
+        double acc[NS][NT][4] = {}, arm[NS][1][4] = {};
+        if (box == 0)
+            force_accum<TI, NT, NS>(F.box[0], units, fun, y, ok, small != 0, NB * parts, NB * blockIdx.z + w, lane, acc);
+        else
+            force_accum<TI, 1, NS>(F.box[box], units, fun, y, ok, small != 0, NA * parts, NA * blockIdx.z + w, lane, arm);
+        for (int r = 0; r < NA; ++r) {
+            if (box == 0 && w / 2 == r) put(S[w & 1], acc, 16 * NT, r == 0);
+            if (box != 0 && w == r) put(S[1 + box] + box * np, arm, np, r == 0);
+            __syncthreads();
+        }
+        for (int e = threadIdx.x; e < 4 * np * NC; e += 64 * NW) {
+            const int j = e / NC, c = e % NC, r = j / np;
+            double v = S[0][j][c] + S[1][j][c];
+            if (r == 1 || r == 2) v += S[1 + r][j][c];
+            if (c0 + c < ns) part[((long long)blockIdx.z * 4 * nproj_total + 4 * F.proj0 + j) * ns + c0 + c] = v;
+        }
+        return;
+    }
+    {
+        double acc[NS][NT][4] = {};
+        force_accum<TI, NT, NS>(F.box[0], units, fun, y, ok, small != 0, NW, wave, lane, acc);
+        for (int w = 0; w < NW; ++w) {
+            if (wave == w) put(S[0], acc, 16 * NT, w == 0);
+            __syncthreads();
+        }
+    }
+#pragma unroll 1
+    for (int k = 1; k < 3; ++k) {
+        double acc[NS][1][4] = {};
+        force_accum<TI, 1, NS>(F.box[k], units, fun, y, ok, small != 0, NW, wave, lane, acc);
+        for (int w = 0; w < NW; ++w) {
+            if (wave == w) put(S[0] + k * np, acc, np, false);
+            __syncthreads();
+        }
+    }
+    const int c = threadIdx.x % NC;
+    double v[3] = {0.0, 0.0, 0.0};
+    if (c0 + c < ns) {
+        for (int p = threadIdx.x / NC; p < np; p += 64 * NW / NC) {
+            const double gy = gamma[F.proj0 + p] * S[0][p][c];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) v[d] += gy * S[0][(1 + d) * np + p][c];
+        }
+        const double g = occ[c0 + c];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) v[d] *= g;
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        for (int off = 32; off > 0; off >>= 1) v[d] += __shfl_xor(v[d], off);
+        if (lane == 0) red[d][wave] = v[d];
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        double f = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) f += red[threadIdx.x][w];
+        part[((long long)J * gridDim.x + cb) * 3 + threadIdx.x] = f;
+    }
+}
+
+// force[e] = scale * sum over the orbital blocks, in order; e = 3 J + d
+__global__ void __launch_bounds__(64) force_sum_kernel(const double *__restrict__ part, int ncb, int n3, double scale,
+                                                          double *__restrict__ force)
+{
+    const int e = blockIdx.x * 64 + threadIdx.x;
+    if (e >= n3) return;
+    double v = 0.0;
+#pragma unroll 8
+    for (int b = 0; b < ncb; ++b) v += part[((long long)(e / 3) * ncb + b) * 3 + e % 3];
+    force[e] = scale * v;
+}
+
+constexpr int kFinishThreads = 1024;
+
 // one workgroup per atom: f[3J + d] = scale * sum_n occ[n] sum_p gamma_p S_0p(n) S_dp(n),
-// S_rp(n) the record-r contraction of projector p with orbital n (split
-// partials summed in split order); orbitals are dealt n = t + 256 i to thread
-// t, and the per-thread sums meet in a fixed butterfly and wave order
-__global__ void __launch_bounds__(256) force_finish_kernel(const double *__restrict__ part, int nrec_proj, int ns,
-                                                           const AtomDev *__restrict__ atoms,
+// S the sum of the parts in order; the (projector, orbital) pairs are dealt to
+// the threads, whose sums meet in a fixed butterfly and wave order
+__global__ void __launch_bounds__(kFinishThreads) force_finish_kernel(const double *__restrict__ part, int parts, int nproj_total,
+                                                           int ns, const ForceAtom *__restrict__ atoms,
                                                            const double *__restrict__ gamma,
                                                            const double *__restrict__ occ, double scale,
                                                            double *__restrict__ force)
 {
-    const AtomDev A = atoms[blockIdx.x];
-    const long long split = (long long)nrec_proj * ns;
+    const int np = atoms[blockIdx.x].nproj, proj0 = atoms[blockIdx.x].proj0;
+    const long long split = 4LL * nproj_total * ns;
     double acc[3] = {0.0, 0.0, 0.0};
-    for (int n = threadIdx.x; n < ns; n += 256) {
-        const double g = occ[n];
-        double s3[3] = {0.0, 0.0, 0.0};
-        for (int p = 0; p < A.nproj; ++p) {
-            double S[4];
+    for (long long e = threadIdx.x; e < (long long)np * ns; e += kFinishThreads) {
+        const int p = (int)(e / ns), n = (int)(e - (long long)p * ns);
+        const double *q = part + (4LL * proj0 + p) * ns + n;
+        double S[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (int k = 0; k < parts; ++k)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const long long base = (long long)(4 * A.proj0 + r * A.nproj + p) * ns + n;
-                double v = 0.0;
-                for (int ks = 0; ks < kGatherSplit; ++ks) v += part[ks * split + base];
-                S[r] = v;
-            }
-            const double gy = gamma[A.proj0 + p] * S[0];
+            for (int r = 0; r < 4; ++r) S[r] += q[k * split + (long long)r * np * ns];
+        const double gy = occ[n] * (gamma[proj0 + p] * S[0]);
 #pragma unroll
-            for (int d = 0; d < 3; ++d) s3[d] += gy * S[1 + d];
-        }
-#pragma unroll
-        for (int d = 0; d < 3; ++d) acc[d] += g * s3[d];
+        for (int d = 0; d < 3; ++d) acc[d] += gy * S[1 + d];
     }
-    __shared__ double red[3][4];
+    __shared__ double red[3][kFinishThreads / 64];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         double v = acc[d];
@@ -171,14 +383,73 @@ __global__ void __launch_bounds__(256) force_finish_kernel(const double *__restr
     }
     __syncthreads();
     if (threadIdx.x < 3) {
-        const int d = threadIdx.x;
-        force[3 * blockIdx.x + d] = scale * ((red[d][0] + red[d][1]) + (red[d][2] + red[d][3]));
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < kFinishThreads / 64; ++w) v += red[threadIdx.x][w];
+        force[3 * blockIdx.x + threadIdx.x] = scale * v;
     }
 }
 
-size_t force_part_bytes(const sparc_op *op, int ns)
+template <typename TI, int NW, int NS, bool SPLIT>
+void launch_force(const sparc_op *op, const TI *psi, long long ld, int ns, const double *occ, int parts, double *part,
+                  double *force, hipStream_t s)
 {
-    return (size_t)kGatherSplit * 4 * op->nproj_total * ns * sizeof(double);
+    const int ncb = (ns + 16 * NS - 1) / (16 * NS), small = op->nd < kUnit;
+    const int2 *units = (const int2 *)op->d_funits;
+    const double *fun = op->d_ffun, *gamma = op->d_fgamma;
+    const double h3 = op->h * op->h * op->h, scale = -4.0 * h3 * h3;
+    for (int J = 0; J < op->natoms; J += 65535) {
+        const ForceAtom *atoms = (const ForceAtom *)op->d_fatoms + J;
+        const dim3 grid(ncb, std::min(op->natoms - J, 65535), parts), b(64 * NW);
+        double *out = SPLIT ? part : part + 3LL * J * ncb;
+#define SPARC_FORCE(N)                                                                                               \
+    hipLaunchKernelGGL((force_kernel<TI, N, NW, NS, SPLIT>), grid, b, 0, s, psi, ld, ns, op->nproj_total, atoms, units, \
+                       fun, gamma, occ, small, out)
+        switch ((4 * op->max_nproj + 15) / 16) {
+            case 1: SPARC_FORCE(1); break;
+            case 2: SPARC_FORCE(2); break;
+            case 3: SPARC_FORCE(3); break;
+            default: SPARC_FORCE(4); break;
+        }
+#undef SPARC_FORCE
+    }
+    if (SPLIT)
+        hipLaunchKernelGGL(force_finish_kernel, dim3(op->natoms), dim3(kFinishThreads), 0, s, part, parts,
+                           op->nproj_total, ns, (const ForceAtom *)op->d_fatoms, gamma, occ, scale, force);
+    else
+        hipLaunchKernelGGL(force_sum_kernel, dim3((3 * op->natoms + 63) / 64), dim3(64), 0, s, part, ncb,
+                           3 * op->natoms, scale, force);
+}
+
+// Whole units lists per workgroup once the chip is full of them.  Measured,
+// FP32, whole against 4 parts: 512 workgroups (128 atoms x 100 orbitals) 482
+// against 383 us, 589 (31 x 600) 510 against 488, 1024 (FP64, 128 x 240) 944
+// against 999, 2432 (128 x 600, 9 projectors) 2257 against 2453.
+bool force_whole(const sparc_op *op, int ns) { return (long long)op->natoms * ((ns + 31) / 32) >= 1024; }
+
+// Parts of the units of a split launch: 16 where an atom and 16 orbitals make
+// fewer than 32 workgroups (96^3, 16 atoms x 12 orbitals: 15.2 us, with 4
+// parts 23.6), else 4 (48^3, 2 atoms x 300 orbitals: 34, with 16 parts 54 us).
+constexpr int kMinParts = 4, kMaxParts = 16;
+int force_parts(const sparc_op *op, int ns)
+{
+    return (long long)op->natoms * ((ns + 15) / 16) < 32 ? kMaxParts : kMinParts;
+}
+
+// the partial sums; a whole launch writes natoms x orbital blocks x 3 values of them
+size_t force_part_bytes(const sparc_op *op, int ns, int parts)
+{
+    return (size_t)parts * 4 * op->nproj_total * ns * sizeof(double);
+}
+
+template <typename TI>
+void force_any(const sparc_op *op, const TI *psi, long long ld, int ns, const double *occ, double *part,
+               int parts, double *force, hipStream_t s)
+{
+    if (force_whole(op, ns))
+        launch_force<TI, 4, 2, false>(op, psi, ld, ns, occ, 1, part, force, s);
+    else
+        launch_force<TI, 8, 1, true>(op, psi, ld, ns, occ, parts, part, force, s);
 }
 
 }  // namespace
@@ -189,7 +460,7 @@ using namespace sparc;
 extern "C" size_t sparc_force_workspace_bytes(const sparc_op *op, int32_t ns)
 {
     if (!op || ns < 1) return 0;
-    return std::max<size_t>(force_part_bytes(op, ns), 256);
+    return std::max<size_t>(force_part_bytes(op, ns, force_parts(op, ns)), 256);
 }
 
 extern "C" int sparc_nonlocal_force(const sparc_op *op, int32_t dtype, const void *psi, int64_t ld, int32_t ns,
@@ -200,14 +471,21 @@ extern "C" int sparc_nonlocal_force(const sparc_op *op, int32_t dtype, const voi
     if (ns < 1 || ld < op->nd) return fail(SPARC_E_SHAPE, "ns < 1 or ld < N_d");
     if ((ns + 15) / 16 > 65535) return fail(SPARC_E_SHAPE, "too many columns for one launch");
     if (op->natoms == 0) return SPARC_OK;
-    const size_t need = force_part_bytes(op, ns);
+    const size_t need = force_part_bytes(op, ns, kMinParts);
     if (!ws || ws_bytes < need) return fail(SPARC_E_WORKSPACE, "workspace missing or too small");
     const size_t es = elem_size(dtype);
     const char *p0 = (const char *)psi, *p1 = p0 + ((size_t)(ns - 1) * ld + op->nd) * es;
-    const char *w0 = (const char *)ws, *w1 = w0 + need;
+    const char *w0 = (const char *)ws;
     const char *f0 = (const char *)force, *f1 = f0 + (size_t)op->natoms * 3 * sizeof(double);
-    if ((w0 < p1 && p0 < w1) || (f0 < p1 && p0 < f1) || (f0 < w1 && w0 < f1))
-        return fail(SPARC_E_ALIAS, "psi, the workspace and the forces overlap");
+    auto overlap = [&](size_t bytes) {
+        const char *w1 = w0 + bytes;
+        return (w0 < p1 && p0 < w1) || (f0 < w1 && w0 < f1);
+    };
+    if (overlap(need) || (f0 < p1 && p0 < f1)) return fail(SPARC_E_ALIAS, "psi, the workspace and the forces overlap");
+    // a workspace without room for the parts this size is best split into gets the fewest
+    int parts = force_parts(op, ns);
+    const size_t room = force_part_bytes(op, ns, parts);
+    if (ws_bytes < room || overlap(room)) parts = kMinParts;
     {
         std::lock_guard<std::mutex> lk(op->force_mu);
         if (!op->force_ready) {
@@ -217,22 +495,11 @@ extern "C" int sparc_nonlocal_force(const sparc_op *op, int32_t dtype, const voi
     }
     TraceRange trace("sparc_nonlocal_force");
     hipStream_t s = (hipStream_t)stream;
-    const dim3 grid(4 * op->natoms, (ns + 15) / 16, kGatherSplit);
-    const double h3 = op->h * op->h * op->h;
     ProfScope prof(5, s);
-    if (dtype == SPARC_F64) {
-        GatherArgs<double, double> a{(const double *)psi, ld, ns, 4 * op->nproj_total, op->nd < kUnit, op->d_fatoms,
-                                     (const int2 *)op->d_funits,
-                                     op->d_ffun, nullptr, nullptr, (double *)ws};
-        hipLaunchKernelGGL(force_gather_kernel<double>, grid, dim3(256), 0, s, a);
-    } else {
-        GatherArgs<double, float> a{(const float *)psi, ld, ns, 4 * op->nproj_total, op->nd < kUnit, op->d_fatoms,
-                                     (const int2 *)op->d_funits,
-                                    op->d_ffun, nullptr, nullptr, (double *)ws};
-        hipLaunchKernelGGL(force_gather_kernel<float>, grid, dim3(256), 0, s, a);
-    }
-    hipLaunchKernelGGL(force_finish_kernel, dim3(op->natoms), dim3(256), 0, s, (const double *)ws,
-                       4 * op->nproj_total, ns, op->d_atoms, op->d_fgamma, occ, -4.0 * h3 * h3, force);
+    if (dtype == SPARC_F64)
+        force_any(op, (const double *)psi, ld, ns, occ, (double *)ws, parts, force, s);
+    else
+        force_any(op, (const float *)psi, ld, ns, occ, (double *)ws, parts, force, s);
     SPARC_HIP(hipGetLastError());
     return SPARC_OK;
 }

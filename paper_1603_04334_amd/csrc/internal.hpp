@@ -99,13 +99,12 @@ struct sparc_op {
     int tune_ns[2] = {-1, -1};  // block width the launch choice was tuned for; -1: every width
     int tune_group[2] = {0, 0};  // column group of the vector step (0 = library choice)
     int tune_cblk[2] = {0, 0};   // columns per workgroup of the vector step (0 = library choice)
-    // nonlocal-force tables, built on the first sparc_nonlocal_force call:
-    // per atom four gather records (the cube with chi, and for each axis d
-    // the cube widened by the stencil radius along d with -grad_d chi), their
-    // grid offsets and function values (FP64), and gamma per projector
+    // nonlocal-force tables, built on the first sparc_nonlocal_force call
+    // (force.hip): per atom the boxes its functions live on, their units and
+    // function values (FP64), and gamma per projector
     mutable std::mutex force_mu;
     mutable bool force_ready = false;
-    mutable sparc::AtomDev *d_fatoms = nullptr;
+    mutable void *d_fatoms = nullptr;
     mutable int *d_funits = nullptr;
     mutable double *d_ffun = nullptr;
     mutable double *d_fgamma = nullptr;

@@ -16,7 +16,7 @@
 //    1.5 lines of 128 bytes per column, 3.3 GB at 160^3 x 600 with 128 cubes.
 //    Node by node (4 bytes per lane, a table entry and a chi value per matrix
 //    instruction) the gather took 948 us there, by units of 4 nodes 676 us
-//    (4.9 TB/s of those lines); the FP64 gathers of the force 5.2 -> 4.2 ms.
+//    (4.9 TB/s of those lines).
 //  * scatter: out(x,c) += alpha * sum_{J: x in cube_J} sum_p chi_Jp(x) h^3 gamma_Jp S_Jp(c)
 //    over the unique nodes covered by at least one cube, grouped in blocks of
 //    at most 256 nodes that touch at most kScatterSlots atoms (tables built at
