@@ -26,6 +26,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <type_traits>
 #include <vector>
 
 #include "internal.hpp"
@@ -430,29 +431,33 @@ __global__ void f64_to_f32_dense(const double *src, float *dst, long long n)
 // M_s = Y^T Y and H_s = Y^T (HY) in FP64 on the matrix cores
 // (v_mfma_f64_16x16x4f64).  The contraction runs over the N_d grid points,
 // which are split into chunks; a workgroup owns one 64 x 64 tile pair of
-// (M_s, H_s) on or above the diagonal for one chunk (both matrices are
-// symmetric: the lower tiles are copies), stages 32-point slices of the three
-// column panels in LDS (coalesced along the contiguous grid axis) and writes
-// its partial tiles, which a second kernel sums in chunk order; the upper
-// triangle is then mirrored.  Each of the four waves owns a 32 x 32 quarter of
-// both tiles (2 x 2 MFMA blocks each).  Workgroup indices are remapped so
-// that all tile pairs of one chunk run back to back on the same XCD: the ten
-// pairs that read a column panel then share it in that XCD's L2, and each
-// panel of a chunk comes from HBM about once.
+// (M_s, H_s) on or above the diagonal for one chunk, stages 32-point slices of
+// the three column panels in LDS (16 bytes per lane along the contiguous grid
+// axis) and writes its part of the upper triangles, packed; a second kernel
+// sums them in chunk order and writes both triangles.  The four waves share the
+// 16 x 16 blocks of the tile that are on or above the diagonal and within ns,
+// of both matrices (741 of the 880 in 55 whole tiles at ns = 600).  Workgroup
+// indices are remapped so that all tile pairs of one chunk run on the same XCD.
+//
+// What bounds it: the matrix cores, busy 79 % of the time at 160^3 x 600 (FP32
+// block): 53.3 ms, 62.7 with whole tiles and 4-byte loads; 45 with the loads
+// taken out.  The panels come from the last-level cache (193 GB, the XCD's L2
+// holds too few slices for the tile pairs of a chunk to meet in it), with a
+// latency the next slice's loads cover.  Tiles of 128 halve those bytes but
+// leave two waves per SIMD, one workgroup per CU: 62.8 ms.
 
 constexpr int kRrTile = 64;
-constexpr int kRrK = 32;  // chunks of the contraction are multiples of this
+constexpr int kRrK = 32;  // points per staged slice; chunks of the contraction are multiples of it
 
-// Staged slice geometry per block type.  FP32 panels stay FP32 in LDS (widened
-// when read as MFMA operands).  Row strides put the 16 rows x 4 points of one
-// operand read in distinct banks.
+// Staged slice: FP32 panels stay FP32 in LDS (widened when read as MFMA
+// operands).  The row strides (36 floats, 34 doubles) keep the 16-byte writes
+// aligned and put the 16 rows of one operand read in distinct banks.
 template <typename TY>
-struct RrSlice {
-    static constexpr int K = kRrK;                              // points per slice
-    static constexpr int SA = sizeof(TY) == 4 ? K + 4 : K + 1;  // Y panel row stride (elements)
-    static constexpr int SH = K + 1;                            // HY panel row stride (doubles)
-    static constexpr int CPP = 256 / K;                         // columns staged per pass
-    static constexpr int NP = kRrTile / CPP;                    // passes per slice
+struct RrPanels {
+    static constexpr int SA = sizeof(TY) == 4 ? kRrK + 4 : kRrK + 2;
+    alignas(16) TY A[kRrTile][SA];            // Y columns of the row tile, [col][k]
+    alignas(16) TY B[kRrTile][SA];            // Y columns of the column tile
+    alignas(16) double H[kRrTile][kRrK + 2];  // HY columns of the column tile
 };
 
 __device__ inline void mfma_f64(double a, double b, double (&acc)[4])
@@ -466,16 +471,168 @@ __device__ inline void mfma_f64(double a, double b, double (&acc)[4])
     acc[3] = c[3];
 }
 
-template <typename TY>
-__global__ void __launch_bounds__(256, 2) rr_project_kernel(const TY *__restrict__ Y, long long ldy,
-                                                          const double *__restrict__ HY, long long ldh, long long nd,
-                                                          int ns, long long kchunk, double *__restrict__ partial)
+// acc += the 16 x 16 blocks of one wave of a diagonal tile over a staged slice:
+// the five blocks on and above the diagonal of block rows W and 3 - W of Y^T Y
+// or, HY, of Y^T (H Y)
+template <typename TY, int W, bool HY>
+__device__ __forceinline__ void rr_diag(const RrPanels<TY> &S, int li, int lk, double (&acc)[8][4])
 {
-    using G = RrSlice<TY>;
-    constexpr int KS = G::K;
-    __shared__ TY sA[kRrTile][G::SA];         // Y columns of the row tile, [col][k]
-    __shared__ TY sB[kRrTile][G::SA];         // Y columns of the column tile
-    __shared__ double sH[kRrTile][G::SH];     // HY columns of the column tile
+#pragma unroll
+    for (int ks = 0; ks < kRrK; ks += 4) {
+        const double a0 = (double)S.A[16 * W + li][ks + lk];
+        const double a1 = (double)S.A[16 * (3 - W) + li][ks + lk];
+#pragma unroll
+        for (int v = W; v < 4; ++v) {
+            const double b = HY ? S.H[16 * v + li][ks + lk] : (double)S.A[16 * v + li][ks + lk];
+            mfma_f64(a0, b, acc[v - W]);
+            if (v >= 3 - W) mfma_f64(a1, b, acc[1 + v]);
+        }
+    }
+}
+
+template <typename T, int N>
+struct RrVec {
+    typedef T type __attribute__((ext_vector_type(N)));
+};
+
+// N points from p[k] on; TAIL: zeros past point kl
+template <int N, bool TAIL, typename T>
+__device__ __forceinline__ typename RrVec<T, N>::type rr_load(const T *p, int k, int kl)
+{
+    typedef T V __attribute__((ext_vector_type(N), aligned(sizeof(T))));
+    if (!TAIL) return *(const V *)(p + k);
+    typename RrVec<T, N>::type v;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        const T t = p[min(k + e, kl)];
+        v[e] = k + e <= kl ? t : T(0);
+    }
+    return v;
+}
+
+// One tile pair over the points [k0, k1).  The 16 x 16 blocks a wave forms:
+//  NC = 4, a whole tile pair: 2 x 2 blocks of both matrices,
+//  NC = 1..3, one cut by the matrix's edge: a block row and its NC columns,
+//  NC = 0, a diagonal one: see rr_diag.
+template <typename TY, int NC>
+__device__ __forceinline__ void rr_pair(const TY *__restrict__ Y, long long ldy, const double *__restrict__ HY,
+                                        long long ldh, int ns, int ti, int tj, long long k0, long long k1,
+                                        RrPanels<TY> &S, double *__restrict__ pm)
+{
+    constexpr int T = kRrTile, KS = kRrK;
+    constexpr bool DIAG = NC == 0;
+    // 16 bytes per lane: VY points of a Y column (TY_ lanes a column), 2 of an HY column
+    constexpr int VY = 16 / sizeof(TY), LY = KS / VY, CY = 256 / LY, PY = T / CY;
+    constexpr int LH = KS / 2, CH = 256 / LH, PH = T / CH;
+    typedef typename RrVec<TY, VY>::type VecY;
+    typedef typename RrVec<double, 2>::type VecH;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
+    const int w = wave >> 1, hy = wave & 1;
+    const int li = lane & 15, lk = lane >> 4;
+    double acc[8][4] = {};
+    VecY ra[PY], rb[PY];  // raw values of the next slice (keeps the loads in flight)
+    VecH rh[PH];
+
+    // On a diagonal tile pair both Y panels are the same columns: read and
+    // stage them once.  Columns past ns repeat the last one (the blocks' rows
+    // and columns past ns are not stored), points past k1 are staged as zeros.
+    const int cy = tid / LY, ky = tid % LY * VY, ch = tid / LH, kh = tid % LH * 2;
+    auto fetch_slice = [&](long long kb, auto tail) {
+        constexpr bool TAIL = decltype(tail)::value;
+        const int kl = (int)(k1 - 1 - kb);
+        // (made again for each slice: the twelve column addresses would not fit
+        // beside the sums)
+        int y = cy, h = ch;
+        asm volatile("" : "+v"(y), "+v"(h));
+#pragma unroll
+        for (int pass = 0; pass < PY; ++pass) {
+            const int ca = ti * T + pass * CY + y, cb = min(tj * T + pass * CY + y, ns - 1);
+            if (!DIAG) ra[pass] = rr_load<VY, TAIL>(Y + kb + ca * ldy, ky, kl);
+            rb[pass] = rr_load<VY, TAIL>(Y + kb + cb * ldy, ky, kl);
+        }
+#pragma unroll
+        for (int pass = 0; pass < PH; ++pass)
+            rh[pass] = rr_load<2, TAIL>(HY + kb + min(tj * T + pass * CH + h, ns - 1) * ldh, kh, kl);
+    };
+    auto fetch = [&](long long kb) {
+        if (kb + KS <= k1)
+            fetch_slice(kb, std::false_type());
+        else
+            fetch_slice(kb, std::true_type());
+    };
+    fetch(k0);
+    for (long long kb = k0; kb < k1; kb += KS) {
+        __syncthreads();
+#pragma unroll
+        for (int pass = 0; pass < PY; ++pass) {
+            const int c = pass * CY + cy;
+            *(VecY *)&S.A[c][ky] = DIAG ? rb[pass] : ra[pass];
+            if (!DIAG) *(VecY *)&S.B[c][ky] = rb[pass];
+        }
+#pragma unroll
+        for (int pass = 0; pass < PH; ++pass) *(VecH *)&S.H[pass * CH + ch][kh] = rh[pass];
+        __syncthreads();
+        if (kb + KS < k1) fetch(kb + KS);
+        if constexpr (DIAG) {
+            switch (wave) {
+                case 0: rr_diag<TY, 0, false>(S, li, lk, acc); break;
+                case 1: rr_diag<TY, 0, true>(S, li, lk, acc); break;
+                case 2: rr_diag<TY, 1, false>(S, li, lk, acc); break;
+                default: rr_diag<TY, 1, true>(S, li, lk, acc); break;
+            }
+        } else {
+            constexpr int NR = NC == 4 ? 2 : 1, NV = NC == 4 ? 2 : NC;
+            const int r0 = NC == 4 ? wi : 16 * wave, c0 = NC == 4 ? wj : 0;
+#pragma unroll
+            for (int ks = 0; ks < KS; ks += 4) {
+                double a[NR], b[NV], h[NV];
+#pragma unroll
+                for (int u = 0; u < NR; ++u) a[u] = (double)S.A[r0 + 16 * u + li][ks + lk];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    b[v] = (double)S.B[c0 + 16 * v + li][ks + lk];
+                    h[v] = S.H[c0 + 16 * v + li][ks + lk];
+                }
+#pragma unroll
+                for (int u = 0; u < NR; ++u)
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) {
+                        mfma_f64(a[u], b[v], acc[2 * (NV * u + v)]);
+                        mfma_f64(a[u], h[v], acc[2 * (NV * u + v) + 1]);
+                    }
+            }
+        }
+    }
+    // pm: the two upper triangles, packed by columns
+    const long long tri = (long long)ns * (ns + 1) / 2;
+    auto put = [&](const double (&v)[4], int r0, int c0, bool h) {
+        const long long col = tj * T + c0 + (lane & 15);
+        double *p = pm + (h ? tri : 0) + col * (col + 1) / 2;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = ti * T + r0 + (lane >> 4) + 4 * r;
+            if (row <= col && col < ns) p[row] = v[r];
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        if (NC == 4) put(acc[q], wi + 16 * (q / 4), wj + 16 * (q / 2 % 2), q & 1);
+        if (!DIAG && NC < 4 && q < 2 * NC) put(acc[q], 16 * wave, 16 * (q / 2), q & 1);
+        if (DIAG && q < 5) {
+            const bool first = q < 4 - w;
+            put(acc[q], 16 * (first ? w : 3 - w), 16 * (first ? q + w : q - 1), hy);
+        }
+    }
+}
+
+template <typename TY>
+__global__ void __launch_bounds__(256, 3)
+    rr_project_kernel(const TY *__restrict__ Y, long long ldy, const double *__restrict__ HY, long long ldh,
+                      long long nd, int ns, long long kchunk, double *__restrict__ partial)
+{
+    __shared__ RrPanels<TY> S;
     // (chunk, tile pair) from the XCD-contiguous workgroup order; tile pair
     // (ti <= tj) numbered in row order: both matrices are symmetric, so only
     // the upper tiles are formed
@@ -492,88 +649,14 @@ __global__ void __launch_bounds__(256, 2) rr_project_kernel(const TY *__restrict
     const int tj = ti + rem;
     const long long k0 = chunk * kchunk;
     const long long k1 = (k0 + kchunk < nd) ? k0 + kchunk : nd;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;  // wave's quarter
-    const int li = lane & 15, lk = lane >> 4;
-    const int kk = tid % KS;
-    double accM[2][2][4] = {}, accH[2][2][4] = {};
-    TY ra[G::NP], rb[G::NP];  // raw values of the next slice (keeps the loads in flight)
-    double rh[G::NP];
-
-    // thread -> (column c = CPP*pass + tid/KS, point kk = tid%KS of the slice).
-    // On a diagonal tile pair both Y panels are the same columns: read and
-    // stage them once.
-    const bool diag = ti == tj;
-    // Addresses: a workgroup-uniform 64-bit base per pass (column CPP*pass of
-    // the tile) plus a 32-bit lane offset (its column within the pass times
-    // the leading dimension, plus the point), so no 64-bit lane addresses
-    // stay live across the slice loop.
-    const int cl = tid / KS;
-    auto fetch = [&](long long kb) {
-        const long long k = kb + kk;
-        const bool kin = k < k1;
-        const unsigned oy = (unsigned)(cl * ldy + k), oh = (unsigned)(cl * ldh + k);
-#pragma unroll
-        for (int pass = 0; pass < G::NP; ++pass) {
-            const int c0 = pass * G::CPP;
-            const int ca = ti * kRrTile + c0 + cl, cb = tj * kRrTile + c0 + cl;
-            const TY *ya = Y + (long long)(ti * kRrTile + c0) * ldy;
-            const TY *yb = Y + (long long)(tj * kRrTile + c0) * ldy;
-            const double *hb = HY + (long long)(tj * kRrTile + c0) * ldh;
-            ra[pass] = (kin && ca < ns) ? ya[oy] : TY(0);
-            if (!diag) rb[pass] = (kin && cb < ns) ? yb[oy] : TY(0);
-            rh[pass] = (kin && cb < ns) ? hb[oh] : 0.0;
-        }
-    };
-    fetch(k0);
-    for (long long kb = k0; kb < k1; kb += KS) {
-        __syncthreads();
-#pragma unroll
-        for (int pass = 0; pass < G::NP; ++pass) {
-            const int c = pass * G::CPP + tid / KS;
-            sA[c][kk] = ra[pass];
-            if (!diag) sB[c][kk] = rb[pass];
-            sH[c][kk] = rh[pass];
-        }
-        __syncthreads();
-        if (kb + KS < k1) fetch(kb + KS);
-        const TY(*SB)[G::SA] = diag ? sA : sB;
-#pragma unroll
-        for (int ks = 0; ks < KS; ks += 4) {
-            double a[2], b[2], h[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                a[u] = (double)sA[wi + 16 * u + li][ks + lk];
-                b[u] = (double)SB[wj + 16 * u + li][ks + lk];
-                h[u] = sH[wj + 16 * u + li][ks + lk];
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int v = 0; v < 2; ++v) {
-                    mfma_f64(a[u], b[v], accM[u][v]);
-                    mfma_f64(a[u], h[v], accH[u][v]);
-                }
-        }
+    double *pm = partial + (long long)chunk * ns * (ns + 1);
+    switch (ti == tj ? 0 : min(4, (ns - tj * kRrTile + 15) / 16)) {  // block columns within ns
+        case 0: rr_pair<TY, 0>(Y, ldy, HY, ldh, ns, ti, tj, k0, k1, S, pm); break;
+        case 1: rr_pair<TY, 1>(Y, ldy, HY, ldh, ns, ti, tj, k0, k1, S, pm); break;
+        case 2: rr_pair<TY, 2>(Y, ldy, HY, ldh, ns, ti, tj, k0, k1, S, pm); break;
+        case 3: rr_pair<TY, 3>(Y, ldy, HY, ldh, ns, ti, tj, k0, k1, S, pm); break;
+        default: rr_pair<TY, 4>(Y, ldy, HY, ldh, ns, ti, tj, k0, k1, S, pm); break;
     }
-    // partial[(chunk*2 + which)][col][row] of the full ns x ns matrices
-    const long long mat = (long long)ns * ns;
-    double *pm = partial + (long long)chunk * 2 * mat;
-    double *ph = pm + mat;
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 2; ++v)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = ti * kRrTile + wi + 16 * u + (lane >> 4) + 4 * r;
-                const int col = tj * kRrTile + wj + 16 * v + (lane & 15);
-                if (row < ns && col < ns) {
-                    pm[(long long)col * ns + row] = accM[u][v][r];
-                    ph[(long long)col * ns + row] = accH[u][v][r];
-                }
-            }
 }
 
 // Ms, Hs (column-major ns x ns) = sum over chunks of the partial tiles for the
@@ -588,16 +671,15 @@ __global__ void __launch_bounds__(256) rr_reduce_kernel(const double *partial, i
 {
     constexpr int E = 256 / G;  // entries per workgroup
     __shared__ double sum[G][E];
-    const long long mat = (long long)ns * ns;
+    const long long tri = (long long)ns * (ns + 1) / 2;
     const long long e = blockIdx.x * (long long)E + threadIdx.x % E;
     const int g = threadIdx.x / E;
-    const long long which = e / mat, off = e - which * mat;
-    const int row = (int)(off % ns), col = (int)(off / ns);
-    const bool upper = e < 2 * mat && row <= col;
+    const bool in = e < 2 * tri;
+    const long long which = e >= tri ? 1 : 0, off = e - which * tri;
     double s = 0.0;
-    if (upper) {
+    if (in) {
 #pragma unroll 16
-        for (int c = g; c < nchunks; c += G) s += partial[((long long)c * 2 + which) * mat + off];
+        for (int c = g; c < nchunks; c += G) s += partial[((long long)c * 2 + which) * tri + off];
     }
     if (G > 1) {
         sum[g][threadIdx.x % E] = s;
@@ -607,9 +689,14 @@ __global__ void __launch_bounds__(256) rr_reduce_kernel(const double *partial, i
 #pragma unroll
         for (int k = 0; k < G; ++k) s += sum[k][threadIdx.x % E];
     }
-    if (!upper) return;
+    if (!in) return;
+    // off = col (col + 1) / 2 + row, row <= col
+    int col = (int)((sqrt(8.0 * (double)off + 1.0) - 1.0) * 0.5);
+    while ((long long)(col + 1) * (col + 2) / 2 <= off) ++col;
+    while ((long long)col * (col + 1) / 2 > off) --col;
+    const int row = (int)(off - (long long)col * (col + 1) / 2);
     double *A = which == 0 ? Ms : Hs;
-    A[off] = s;
+    A[(long long)col * ns + row] = s;
     A[(long long)row * ns + col] = s;
 }
 
@@ -979,17 +1066,34 @@ int sparc_lanczos(const sparc_op *op, int32_t k, const double *v0, double *alpha
     return SPARC_OK;
 }
 
-static long long rr_chunk(long long nd, int ns)
+// points per chunk for about nch chunks: a multiple of the staged slice
+static long long rr_points(long long nd, long long nch)
 {
-    // at least 512 workgroups in total (upper tile pairs x chunks) and at
-    // least 8 chunks per XCD; chunks a multiple of the staged slice
+    nch = std::max<long long>(1, std::min<long long>(nch, nd / kRrK));
+    const long long c = ((nd + nch - 1) / nch + kRrK - 1) / kRrK * kRrK;
+    return std::max<long long>(c, kRrK);
+}
+
+// ns x ns pairs of partial matrices the workspace has room for
+static long long rr_room(long long nd, int ns)
+{
     const long long nt = (ns + kRrTile - 1) / kRrTile;
     const long long tiles = nt * (nt + 1) / 2;
-    long long nch = std::max<long long>(64, (512 + tiles - 1) / tiles);
-    nch = std::max<long long>(1, std::min<long long>(nch, nd / kRrK));
-    long long c = (nd + nch - 1) / nch;
-    c = (c + kRrK - 1) / kRrK * kRrK;
-    return std::max<long long>(c, kRrK);
+    const long long c = rr_points(nd, std::max<long long>(64, (512 + tiles - 1) / tiles));
+    return (nd + c - 1) / c;
+}
+
+// The chip holds 768 workgroups of the projection (three per CU): as many
+// chunks as make whole multiples of that and whose packed triangles fit the
+// room.  160^3 x 100: 768 workgroups 6.82 ms, 512 6.99, 640 7.28 (the whole
+// step); 160^3 x 600: 125 chunks (8.95 times 768) 83.2 ms, 64 chunks 84.9.
+static long long rr_chunk(long long nd, int ns)
+{
+    const long long nt = (ns + kRrTile - 1) / kRrTile;
+    const long long tiles = nt * (nt + 1) / 2;
+    const long long most = std::max<long long>(1, rr_room(nd, ns) * 2 * ns / (ns + 1));
+    const long long rounds = most * tiles / 768;
+    return rr_points(nd, rounds > 0 ? 768 * rounds / tiles : most);
 }
 
 size_t sparc_rr_workspace_bytes(const sparc_op *op, int32_t dtype, int32_t ns)
@@ -1000,8 +1104,7 @@ size_t sparc_rr_workspace_bytes(const sparc_op *op, int32_t dtype, int32_t ns)
     b += gather_bytes(op, SPARC_F64, ns);                                           // gathered projections
     b += 2 * align_up((size_t)ns * ns * sizeof(double));                           // H_s, M_s
     b += align_up(((size_t)ns + 1) * sizeof(double)) + align_up((size_t)ns * sizeof(double));  // D and info, E
-    const long long nch = (op->nd + rr_chunk(op->nd, ns) - 1) / rr_chunk(op->nd, ns);
-    b += align_up((size_t)nch * 2 * ns * ns * sizeof(double));                     // projection partials
+    b += align_up((size_t)rr_room(op->nd, ns) * 2 * ns * ns * sizeof(double));     // projection partials
     return b;
 }
 
@@ -1012,9 +1115,7 @@ int sparc_rayleigh_ritz(const sparc_op *op, int32_t dtype, const void *Y, int64_
     if (!op || !Y || !theta) return fail(SPARC_E_ARG, "null argument");
     if (dtype != SPARC_F64 && dtype != SPARC_F32) return fail(SPARC_E_ARG, "bad dtype");
     if (ns < 1 || ldy < op->nd) return fail(SPARC_E_SHAPE, "ns < 1 or ldy < N_d");
-    // the projection addresses a lane's point by a 32-bit element offset from
-    // its pass's first column
-    if ((long long)RrSlice<double>::CPP * ldy + op->nd >= (1LL << 32))
+    if ((long long)8 * ldy + op->nd >= (1LL << 32))
         return fail(SPARC_E_SHAPE, "ldy too large for the projection kernel");
     const size_t need = sparc_rr_workspace_bytes(op, dtype, ns);
     if (!ws || ws_bytes < need) return fail(SPARC_E_WORKSPACE, "workspace too small");
@@ -1059,7 +1160,7 @@ int sparc_rayleigh_ritz(const sparc_op *op, int32_t dtype, const void *Y, int64_
         hipLaunchKernelGGL(rr_project_kernel<float>, pg, dim3(256), 0, s, Yf, (long long)ldy, (const double *)HY, nd,
                            nd, ns, kc, partial);
     }
-    const long long tot = 2LL * ns * ns;
+    const long long tot = (long long)ns * (ns + 1);
     if (ns <= 64)
         hipLaunchKernelGGL(rr_reduce_kernel<16>, dim3((unsigned)((tot + 15) / 16)), dim3(256), 0, s, partial, nch, ns, Ms,
                            Hs);
