@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <new>
 
 #include <rocprofiler-sdk-roctx/roctx.h>
@@ -302,14 +303,15 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
         op->chi_trace.push_back(tr);
         op->atom_gmax.push_back(gmax);
     }
+    if (box_total > 0x7fffffffLL) return cleanup(fail(SPARC_E_SHAPE, "projector cubes too large"));
     if (natoms > 0) {
-        std::vector<double> chi64(chi_total);
-        std::vector<float> chi32(chi_total);
+        // (not zero-filled: the copies below write all of it)
+        const std::unique_ptr<double[]> chi64(new (std::nothrow) double[chi_total]);
+        if (!chi64) return cleanup(fail(SPARC_E_NOMEM, "host allocation of projector data failed"));
         for (int J = 0; J < natoms; ++J) {
             const sparc_atom &A = atoms[J];
             const int64_t cnt = (int64_t)A.ext[0] * A.ext[1] * A.ext[2] * A.nproj;
             std::memcpy(&chi64[op->atoms[J].chi0], A.chi, cnt * sizeof(double));
-            for (int64_t i = 0; i < cnt; ++i) chi32[op->atoms[J].chi0 + i] = (float)A.chi[i];
         }
         const double h3 = op->h * op->h * op->h;
         std::vector<double> hg64(op->nproj_total);
@@ -327,8 +329,7 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
             hipMalloc(&op->d_hg32, op->nproj_total * sizeof(float)) != hipSuccess)
             return cleanup(fail(SPARC_E_NOMEM, "device allocation of projector data failed"));
         if (hipMemcpy(op->d_atoms, op->atoms.data(), natoms * sizeof(AtomDev), hipMemcpyHostToDevice) ||
-            hipMemcpy(op->d_chi64, chi64.data(), chi_total * sizeof(double), hipMemcpyHostToDevice) ||
-            hipMemcpy(op->d_chi32, chi32.data(), chi_total * sizeof(float), hipMemcpyHostToDevice) ||
+            hipMemcpy(op->d_chi64, chi64.get(), chi_total * sizeof(double), hipMemcpyHostToDevice) ||
             hipMemcpy(op->d_hg64, hg64.data(), op->nproj_total * sizeof(double), hipMemcpyHostToDevice) ||
             hipMemcpy(op->d_hg32, hg32.data(), op->nproj_total * sizeof(float), hipMemcpyHostToDevice))
             return cleanup(fail(SPARC_E_HIP, "copy of projector data failed"));
@@ -338,10 +339,11 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
 
     // cube-node grid offsets and the unique covered nodes with their (atom, cube index) entries
     if (natoms > 0) {
-        if (box_total > 0x7fffffffLL) return cleanup(fail(SPARC_E_SHAPE, "projector cubes too large"));
         std::vector<int> boff(box_total);
-        std::vector<std::pair<int64_t, std::pair<int, int>>> cover;
-        cover.reserve(box_total);
+        // node << 32 | position in boff, sorted by node (positions of a node stay
+        // in order): three passes of 11 bits, the nodes are below 2^31
+        std::vector<uint64_t> cover(box_total), other(box_total);
+        std::vector<int> atom_at(box_total);
         for (int J = 0; J < natoms; ++J) {
             const AtomDev &a = op->atoms[J];
             int loc = 0;
@@ -350,20 +352,28 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
                     for (int k = 0; k < a.ext[2]; ++k, ++loc) {
                         const int64_t g = (int64_t)(a.lo[2] + k) + (int64_t)op->n[2] * ((a.lo[1] + j) + (int64_t)op->n[1] * (a.lo[0] + i));
                         boff[a.box0 + loc] = (int)g;
-                        cover.push_back({g, {J, loc}});
+                        cover[a.box0 + loc] = (uint64_t)g << 32 | (uint64_t)(a.box0 + loc);
+                        atom_at[a.box0 + loc] = J;
                     }
         }
-        std::stable_sort(cover.begin(), cover.end(),
-                         [](const auto &x, const auto &y) { return x.first < y.first; });
+        for (int shift = 32; shift < 64; shift += 11) {
+            std::vector<size_t> start(2049, 0);
+            for (uint64_t v : cover) ++start[(v >> shift & 2047) + 1];
+            for (int b = 0; b < 2048; ++b) start[b + 1] += start[b];
+            for (uint64_t v : cover) other[start[v >> shift & 2047]++] = v;
+            cover.swap(other);
+        }
         // unique nodes and their (atom, cube index) entries
         std::vector<int> pts, off;
         std::vector<std::pair<int, int>> raw;
+        raw.reserve(cover.size());
         for (size_t e = 0; e < cover.size(); ++e) {
-            if (e == 0 || cover[e].first != cover[e - 1].first) {
-                pts.push_back((int)cover[e].first);
+            const int g = (int)(cover[e] >> 32), at = (int)(cover[e] & 0xffffffffu), J = atom_at[at];
+            if (e == 0 || g != pts.back()) {
+                pts.push_back(g);
                 off.push_back((int)e);
             }
-            raw.push_back(cover[e].second);
+            raw.push_back({J, at - op->atoms[J].box0});
         }
         off.push_back((int)cover.size());
         // scatter blocks: at most kBlock nodes touching at most kScatterSlots atoms
@@ -413,29 +423,32 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
         if (chi_total > 0x7fffffffLL) return cleanup(fail(SPARC_E_SHAPE, "projector data too large"));
         op->nl_npts = (int)pts.size();
         op->nl_nblk = (int)blk_pt.size() - 1;
-        // one allocation and one copy for all of them
-        std::vector<int> all;
-        std::vector<std::pair<int **, size_t>> at;
-        auto up = [&](int **dst, const std::vector<int> &v) {
-            at.push_back({dst, all.size()});
-            all.insert(all.end(), v.begin(), v.end());
-            all.resize((all.size() + 63) / 64 * 64, 0);
-        };
-        up(&op->d_box_off, boff);
-        up(&op->d_units, units);
-        up(&op->d_nl_pts, pts);
-        up(&op->d_nl_off, off);
-        up(&op->d_nl_ent, ent);
-        up(&op->d_nl_blk_pt, blk_pt);
-        up(&op->d_nl_blk_at, blk_at);
-        up(&op->d_nl_blk_atoms, blk_atoms);
-        up(&op->d_nl_proj, proj);
-        up(&op->d_nl_seg, seg);
-        if (hipMalloc(&op->d_tables, all.size() * sizeof(int)) != hipSuccess)
+        // one allocation for all of them
+        std::vector<std::pair<int **, const std::vector<int> *>> at = {
+            {&op->d_box_off, &boff},     {&op->d_units, &units},       {&op->d_nl_pts, &pts},
+            {&op->d_nl_off, &off},       {&op->d_nl_ent, &ent},        {&op->d_nl_blk_pt, &blk_pt},
+            {&op->d_nl_blk_at, &blk_at}, {&op->d_nl_blk_atoms, &blk_atoms}, {&op->d_nl_proj, &proj},
+            {&op->d_nl_seg, &seg}};
+        size_t total = 0;
+        for (auto &t : at) total += (t.second->size() + 63) / 64 * 64;
+        if (hipMalloc(&op->d_tables, total * sizeof(int)) != hipSuccess)
             return cleanup(fail(SPARC_E_NOMEM, "device allocation of projector tables failed"));
-        if (hipMemcpy(op->d_tables, all.data(), all.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
+        // small sets go over in one copy, large ones without a host copy of their own
+        std::vector<int> all;
+        const bool joint = total <= (size_t)1 << 16;
+        if (joint) all.resize(total);
+        size_t place = 0;
+        for (auto &t : at) {
+            if (joint)
+                std::copy(t.second->begin(), t.second->end(), all.begin() + place);
+            else if (hipMemcpy(op->d_tables + place, t.second->data(), t.second->size() * sizeof(int),
+                               hipMemcpyHostToDevice) != hipSuccess)
+                return cleanup(fail(SPARC_E_HIP, "copy of projector tables failed"));
+            *t.first = op->d_tables + place;
+            place += (t.second->size() + 63) / 64 * 64;
+        }
+        if (joint && hipMemcpy(op->d_tables, all.data(), total * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
             return cleanup(fail(SPARC_E_HIP, "copy of projector tables failed"));
-        for (auto &t : at) *t.first = op->d_tables + t.second;
     }
     *out = op;
     return SPARC_OK;

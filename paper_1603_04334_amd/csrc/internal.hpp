@@ -187,8 +187,9 @@ int launch_fstep(const sparc_op *op, int dtype, const FLaunch &L, const void *yk
 int append_units(const int n[3], int64_t nd, const int lo[3], const int ext[3], std::vector<int> &units,
                  std::vector<int> &pos);
 
-// chi in unit layout (op->d_chiu64, d_chiu32: total values) from op->d_chi64
-// and the places of the cube nodes, atoms back to back.  Synchronous.
+// chi in unit layout (op->d_chiu64, d_chiu32: total values) and in FP32
+// (op->d_chi32) from op->d_chi64 and the places of the cube nodes, atoms back to
+// back.  Synchronous.
 int build_unit_chi(sparc_op *op, const std::vector<int> &pos, int64_t total);
 
 // A gather whose (atom, 16 columns) pairs alone fill the chip takes one

@@ -62,19 +62,18 @@ __global__ void __launch_bounds__(256) scatter_kernel(const ScatterArgs<T> s, in
     scatter_item<T, NC, NP>(s, blockIdx.x, blockIdx.y, (T *)scatter_lds, npm);
 }
 
-// blockIdx.x: atom; its nodes' places from pos + (cube nodes of the atoms before it)
-__global__ void __launch_bounds__(256) unit_chi_kernel(const AtomDev *atoms, const double *chi, const int *pos,
-                                                       double *chiu64, float *chiu32)
+// blockIdx.x: atom; its nodes' places from pos + box0.  Also chi in FP32.
+__global__ void __launch_bounds__(256) unit_chi_kernel(const AtomDev *atoms, const double *chi, float *chi32,
+                                                       const int *pos, double *chiu64, float *chiu32)
 {
     const AtomDev A = atoms[blockIdx.x];
-    long long p0 = 0;
-    for (int J = 0; J < (int)blockIdx.x; ++J) p0 += (long long)atoms[J].ext[0] * atoms[J].ext[1] * atoms[J].ext[2];
     const int nbox = A.ext[0] * A.ext[1] * A.ext[2];
     for (int t = blockIdx.y * 256 + threadIdx.x; t < nbox; t += gridDim.y * 256) {
-        const int d = pos[p0 + t];
+        const int d = pos[A.box0 + t];
         for (int p = 0; p < A.nproj; ++p) {
             const double v = chi[A.chi0 + (long long)p * nbox + t];
             const long long o = A.chiu0 + (long long)p * A.nunits * kUnit + d;
+            chi32[A.chi0 + (long long)p * nbox + t] = (float)v;
             chiu64[o] = v;
             chiu32[o] = (float)v;
         }
@@ -90,8 +89,8 @@ int build_unit_chi(sparc_op *op, const std::vector<int> &pos, int64_t total)
     if (e == hipSuccess) e = hipMemset(op->d_chiu64, 0, total * sizeof(double));
     if (e == hipSuccess) e = hipMemset(op->d_chiu32, 0, total * sizeof(float));
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(unit_chi_kernel, dim3(op->natoms, 4), dim3(256), 0, 0, op->d_atoms, op->d_chi64, d_pos,
-                           op->d_chiu64, op->d_chiu32);
+        hipLaunchKernelGGL(unit_chi_kernel, dim3(op->natoms, 4), dim3(256), 0, 0, op->d_atoms, op->d_chi64,
+                           op->d_chi32, d_pos, op->d_chiu64, op->d_chiu32);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(0);
