@@ -215,9 +215,9 @@ size_t sparc_rotate_workspace_bytes(int32_t dtype, int32_t ns);
  * Y (ldy) is an nd x ns block of the given dtype, Q an FP64 ns x ns
  * column-major device matrix (rounded to dtype for an FP32 block), ws a device
  * workspace of sparc_rotate_workspace_bytes(dtype, ns) bytes, out (ldo) an
- * nd x ns block of dtype.  Sums run in dtype.  Blocks of up to 64 (FP32) /
- * 32 (FP64) columns take the library's kernel, which reads Y once; wider
- * blocks a rocBLAS GEMM (atomics off, so results are reproducible).  Y, out
+ * nd x ns block of dtype.  Sums run in dtype.  Blocks of up to 224 (FP32) /
+ * 192 (FP64) columns take the library's kernels; wider blocks a rocBLAS GEMM
+ * (atomics off, so results are reproducible).  Y, out
  * and ws must not overlap.  Asynchronous.  Errors: SPARC_E_ARG,
  * SPARC_E_SHAPE, SPARC_E_WORKSPACE, SPARC_E_ALIAS, SPARC_E_HIP. */
 int sparc_rotate(int32_t dtype, const void *Y, int64_t ldy, int64_t nd, int32_t ns, const double *Q,

@@ -192,6 +192,10 @@ int append_units(const int n[3], int64_t nd, const int lo[3], const int ext[3], 
 // back.  Synchronous.
 int build_unit_chi(sparc_op *op, const std::vector<int> &pos, int64_t total);
 
+// out = Y Q on the matrix cores (rotate.hip); false: not a size it takes
+bool launch_rotate_mfma(int dtype, const void *Y, int64_t ldy, const double *Q, void *out, int64_t ldo, int64_t nd,
+                        int ns, hipStream_t s);
+
 // A gather whose (atom, 16 columns) pairs alone fill the chip takes one
 // workgroup per pair, which finishes the projections (1 part); a smaller one
 // is spread over kGatherSplit workgroups per pair, which leave as many partial

@@ -1271,6 +1271,10 @@ int sparc_rotate(int32_t dtype, const void *Y, int64_t ldy, int64_t nd, int32_t 
         return fail(SPARC_E_ALIAS, "workspace overlaps Y or out");
     TraceRange trace("sparc_rotate");
     hipStream_t s = (hipStream_t)stream;
+    if (launch_rotate_mfma(dtype, Y, ldy, Q, out, ldo, nd, ns, s)) {
+        SPARC_HIP(hipGetLastError());
+        return SPARC_OK;
+    }
     const unsigned gx = (unsigned)((nd + 255) / 256);
     const int ldq = rot_ldq(ns);
     // Blocks wider than one column block of the kernel below would re-read Y

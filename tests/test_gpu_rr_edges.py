@@ -49,16 +49,24 @@ def test_projection_short_grids(n, dtype):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
-@pytest.mark.parametrize("ns", [1, 3, 4, 5, 8, 9, 15, 16, 17])
-def test_small_rotations(ns, dtype):
-    """X Q on the device against FP64: a sum of ns products, ns eps |X| |Q|."""
+@pytest.mark.parametrize("ns", [1, 3, 4, 5, 8, 9, 15, 16, 17, 31, 32, 33, 50, 64, 65, 80, 81, 97, 113, 127, 128, 129,
+                                160, 161, 192, 193, 224, 225])
+def test_rotations(ns, dtype):
+    """X Q on the device against FP64, a sum of ns products: ns eps |X| |Q|.
+    Points short of a lane's, a wave's and a workgroup's share, columns that
+    start on whole lines (704) and that do not; the values beside the columns
+    stay as they were."""
     from paper_1603_04334_amd import binding
-    nd = 693
-    rng = np.random.default_rng(ns)
-    X = inputs.round_to_f32(rng.standard_normal((ns, nd)))
-    Q = inputs.round_to_f32(rng.standard_normal((ns, ns)))
-    out = binding.rotate(torch.from_numpy(X).to(dtype).cuda(), torch.from_numpy(Q).cuda())
-    got = out.double().cpu().numpy()
-    eps = 2.0 ** -24 if dtype == torch.float32 else 2.0 ** -53
-    bound = (ns + 1) * eps * (np.abs(Q) @ np.abs(X))
-    assert (np.abs(got - Q @ X) <= bound).all()
+    for nd, pad in ((693, 0), (704, 0), (700, 4), (1, 0), (3, 2), (5, 0), (2113, 3)):
+        rng = np.random.default_rng(1000 * ns + nd)
+        X = inputs.round_to_f32(rng.standard_normal((ns, nd)))
+        Q = inputs.round_to_f32(rng.standard_normal((ns, ns)))
+        big = torch.full((ns, nd + pad), float("nan"), dtype=dtype, device="cuda")
+        big[:, :nd] = torch.from_numpy(X).to(dtype).cuda()
+        out = torch.full((ns, nd + pad), -7.0, dtype=dtype, device="cuda")
+        binding.rotate(big[:, :nd], torch.from_numpy(Q).cuda(), out=out[:, :nd])
+        got = out.double().cpu().numpy()
+        eps = 2.0 ** -24 if dtype == torch.float32 else 2.0 ** -53
+        bound = (ns + 1) * eps * (np.abs(Q) @ np.abs(X))
+        assert (np.abs(got[:, :nd] - Q @ X) <= bound).all(), (nd, pad)
+        assert (got[:, nd:] == -7.0).all(), (nd, pad)
