@@ -34,7 +34,8 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step_kernel_traffic_cluster160.tx
 # so that the benchmark runs the launch its committed counters were taken on
 TUNE_CACHE = os.path.join(ROOT, "paper_1603_04334_amd", "tune_mi355x.txt")
 STENCIL_SRCS = [os.path.join(ROOT, "paper_1603_04334_amd", "csrc", f)
-                for f in ("fstep.hip", "fstep_kernel.hpp", "fstep_launch.hpp", "nonlocal_kernel.hpp")]
+                for f in ("fstep.hip", "fstep_kernel.hpp", "fstep_launch.hpp", "nonlocal_kernel.hpp", "rstep_kernel.hpp",
+                          "rstep_launch.hpp")]
 
 
 def parse():

@@ -149,6 +149,7 @@ __global__ void __launch_bounds__(512)
 {
     constexpr int N = DenVec<T>::N;
     using V = typename DenVec<T>::V;
+    typedef T VU __attribute__((ext_vector_type(N), aligned(sizeof(T))));
     const int lane = threadIdx.x & 63;
     const long long wave = (long long)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
     const long long i0 = SHIFT ? (wave * 63 + lane) * N : (wave * 64 + lane) * N;
@@ -162,13 +163,16 @@ __global__ void __launch_bounds__(512)
             V x[kDenUnroll];
 #pragma unroll
             for (int j = 0; j < kDenUnroll; ++j) {
-                const V *c = (const V *)(col + (long long)(n + j) * ld);
+                const VU *c = (const VU *)(col + (long long)(n + j) * ld);
                 x[j] = NT ? __builtin_nontemporal_load(c) : *c;
             }
 #pragma unroll
             for (int j = 0; j < kDenUnroll; ++j) den_add<N>(acc, x[j], occ[n + j]);
         }
-        for (; n < ns; ++n) den_add<N>(acc, *(const V *)(col + (long long)n * ld), occ[n]);
+        for (; n < ns; ++n) {
+            const V x = *(const VU *)(col + (long long)n * ld);
+            den_add<N>(acc, x, occ[n]);
+        }
     } else if (SHIFT) {
         if (wave * 63 * N >= nd) return;  // the whole wave
         const long long last = (long long)(ns - 1) * ld + nd;  // elements of the block
@@ -216,9 +220,17 @@ __global__ void __launch_bounds__(512)
             den_add<N>(acc, x, occ[n]);
         }
     }
+    // whole units in 16-byte stores (rho starts on any double): for one column
+    // the writes are two thirds of the traffic
+    typedef double D2 __attribute__((ext_vector_type(2), aligned(sizeof(double))));
+    if (i0 + N <= nd) {
 #pragma unroll
-    for (int p = 0; p < N; ++p)
-        if (i0 + p < nd) rho[i0 + p] = scale * acc[p];
+        for (int p = 0; p < N; p += 2) *(D2 *)(rho + i0 + p) = D2{scale * acc[p], scale * acc[p + 1]};
+    } else {
+#pragma unroll
+        for (int p = 0; p < N; ++p)
+            if (i0 + p < nd) rho[i0 + p] = scale * acc[p];
+    }
 }
 
 template <typename T>
@@ -226,14 +238,18 @@ int launch_density(const T *psi, long long ld, long long nd, int ns, const doubl
                    hipStream_t s)
 {
     constexpr int N = DenVec<T>::N;
-    const bool aligned = ld % N == 0 && (uintptr_t)psi % 16 == 0;
+    // Columns off the 16-byte grid are read as aligned units shifted across the
+    // lanes, except a few FP64 columns that fit the last-level cache: the plain
+    // 16-byte loads at 8-byte places then cost less than the shifts (95 x 97 x 91
+    // x 4: 7.0 us, shifted 8.6; x 40 46.8 against 46.5).
+    const bool nt_loads = (double)nd * ns * sizeof(T) > kStreamBytes;
+    const bool aligned = (ld % N == 0 && (uintptr_t)psi % 16 == 0) || (sizeof(T) == 8 && ns <= 16 && !nt_loads);
     const long long per = (aligned ? 64LL : 63LL) * N;  // points per wave
     const long long waves = (nd + per - 1) / per;
     // workgroups of 8 waves; small grids spread over more CUs by waves of their own
     const int nt = waves >= 4096 ? 512 : 64;
     const long long blocks = (waves * 64 + nt - 1) / nt;
     if (blocks > 0x7fffffffLL) return fail(SPARC_E_SHAPE, "grid too large for one density launch");
-    const bool nt_loads = (double)nd * ns * sizeof(T) > kStreamBytes;
     ProfScope prof(4, s);
 #define SPARC_DEN(A, B)                                                                                            \
     hipLaunchKernelGGL((density_kernel<T, A, B>), dim3((unsigned)blocks), dim3(nt), 0, s, psi, ld, nd, ns, occ, scale, rho)

@@ -12,11 +12,11 @@
 //  * A workgroup owns a TY x TZ patch (TZ = 32, 64, 80 or 160 nodes) of the
 //    (y, z) plane of one column and streams it along x (wider patches cut the
 //    share of the z halo, whose two partial lines per row are fetched whole;
-//    a patch as wide as the grid has none).  Each lane owns one unit of consecutive z nodes of one
-//    y row: 4 FP32 or 2 FP64 values, 16 bytes, so every global access is a
-//    16-byte raw buffer load or store (a plain copy with 4-byte accesses per
-//    lane reaches about 60% of the bandwidth of 16-byte accesses on this
-//    chip).  A lane keeps the 13 x-planes of its unit in registers, one vector
+//    a patch as wide as the grid has none).  Each lane owns one unit of
+//    consecutive z nodes of one y row: 4 FP32 or 2 FP64 values, 16 bytes, so
+//    every global access is a 16-byte raw buffer load or store (a plain copy
+//    with 4-byte accesses per lane reaches about 60% of the bandwidth of
+//    16-byte accesses on this chip).  A lane keeps the 13 x-planes of its unit in registers, one vector
 //    per plane (x neighbours never touch LDS); the plane loop is unrolled over
 //    26 planes so the queue rotates by register renaming.
 //  * The current plane of the patch plus its halo (6 rows in y; 8 FP32 / 6
@@ -26,7 +26,8 @@
 //    fall outside the per-plane buffer descriptor's range (load zero, store
 //    dropped).  The grid's z extent and every leading dimension must be
 //    multiples of the unit, so a unit is either inside the grid or outside;
-//    other grids take the scalar kernels (stencil.hip).
+//    other grids take the row-pair kernel (rstep_kernel.hpp, which also takes
+//    the larger FP32 blocks) or the scalar kernels (stencil.hip).
 //  * Per point the sums run in the same order as in the scalar kernels.
 //  * Workgroup indices are remapped so consecutive patches of one column run
 //    on the same XCD and share halos in its L2 (optionally, col_group columns
@@ -136,6 +137,18 @@ static void choose_rstep(const sparc_op *op, int dtype, int ns, FLaunch &L)
     const int kz = (op->n[2] + maxtz - 1) / maxtz;
     const int tz = ((op->n[2] + kz - 1) / kz + vz - 1) / vz * vz;
     const int tiles_z = (op->n[2] + tz - 1) / tz;
+    // Workgroups of one patch of `group` columns run back to back and share its
+    // V_eff in the XCD's L2.  Fields below 2 MB stay there by themselves (80 x 72
+    // x 80 x 72 columns: 1.531 ms, by eight 1.554); from there eight columns pay
+    // (96^3 x 64: 3.54 -> 3.24 ms, 128 x 120 x 128 x 14 by two 1.43 -> 1.30), above
+    // 8 MB two (152 x 156 x 148 x 50: 8.36 -> 8.04; 160^3 x 600: 223.4 either
+    // way, by eight 232.6, its halo rows leave the L2).  Only divisors of the
+    // column count: a padded group would start workgroups for nothing (64 x 56 x
+    // 72 x 100 by eight: 1.52 -> 1.75 ms).
+    int group = 1;
+    const int64_t field = op->nd * (int64_t)elem_size(dtype);
+    for (int g = 2; field >= (int64_t)2 << 20 && g <= (field <= (int64_t)8 << 20 ? 8 : 2); g *= 2)
+        if (ns % g == 0) group = g;
     double best = 0;
     for (int ky = 1; ky <= op->n[1]; ++ky) {
         const int ty = ((op->n[1] + ky - 1) / ky + 1) / 2 * 2;
@@ -167,7 +180,8 @@ static void choose_rstep(const sparc_op *op, int dtype, int ns, FLaunch &L)
                 L.ty = ty;
                 L.chunk_x = cx;
                 L.nchunks = chunks;
-                L.cgroup = L.cblk = 1;
+                L.cgroup = group;
+                L.cblk = 1;
             }
         }
     }
@@ -199,6 +213,7 @@ FLaunch choose_vec_launch(const sparc_op *op, int dtype, int ns, std::initialize
     if (tuned && op->tune_shape[dtype] == kRowPair) {
         choose_rstep(op, dtype, ns, L);
         if (L.plan >= 0 && op->tune_chunk[dtype] > 0) set_chunks(op, (op->n[0] + op->tune_chunk[dtype] - 1) / op->tune_chunk[dtype], L);
+        if (L.plan >= 0 && op->tune_group[dtype] > 0) L.cgroup = op->tune_group[dtype];
         if (L.plan >= 0) return L;
     }
     const bool forced = tuned && (op->tune_shape[dtype] >= 0 || op->tune_chunk[dtype] > 0 || op->tune_group[dtype] > 0 ||
