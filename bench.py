@@ -116,15 +116,11 @@ def copy_bandwidth(nbytes=4 << 30, reps=10):
 
 
 def alg_bytes_per_step_launch(case, cl, s):
-    """Algorithmic HBM bytes of one recurrence-step launch (the fused step with
-    Y_{k-1} and the projector gather of the same Y_k): read Y_k and Y_{k-1},
-    write Y_{k+1} (s bytes per orbital*gridpoint each), read V_eff once (s per
-    gridpoint), read the projector values once (s per cube point and
-    projector) and write the gather's 8 split partials (s per projector and
-    orbital each).  The gather's second read of Y_k at the cube points is
-    an implementation cost and is not counted."""
-    chi = sum(int(np.prod(a.ext)) * a.nproj for a in cl.atoms)
-    return 3 * s * cl.nd * case.ns + s * cl.nd + s * chi + s * 8 * cl.nproj_total * case.ns
+    """Algorithmic HBM bytes of one recurrence-step launch: read Y_k and
+    Y_{k-1}, write Y_{k+1} (s bytes per orbital*gridpoint each), read V_eff
+    once (s per gridpoint).  The projector gather of Y_k, which the vector
+    step's launch also holds, is not counted."""
+    return 3 * s * cl.nd * case.ns + s * cl.nd
 
 
 class Pass:
@@ -735,8 +731,8 @@ def main():
         "stages_ms": main_res["stages_ms"],
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": read_traffic(args.dtype, (tz, ty, cx, cg, cb)),
-                     "kernel": "fstep_kernel (vector stencil + local potential + recurrence with Y_{k-1}, with the "
-                               "projector gather of Y_k in its last workgroups)",
+                     "kernel": "recurrence step (stencil + local potential + Y_{k-1}): row-pair rstep_kernel or vector "
+                               "fstep_kernel, as configured",
                      "launches": n_launch, "avg_launch_us": avg_s * 1e6, "alg_bytes_per_launch": alg,
                      "copy_kernel_gbs": copy_gbs, "frac_of_copy": achieved / copy_gbs},
         "scatter_kernel": {"launches": n_sc, "avg_launch_us": ms_sc / max(n_sc, 1) * 1e3},

@@ -263,7 +263,8 @@ size_t sparc_force_workspace_bytes(const sparc_op *op, int32_t ns);
  * nd x ns block (column n at psi + n ld, dtype SPARC_F64 or SPARC_F32,
  * widened to FP64 as it is read); occ: device FP64 array of ns occupations;
  * force: device FP64 array of 3 natoms values, atom J's (x, y, z) at 3J
- * (overwritten); ws: device workspace of sparc_force_workspace_bytes bytes.
+ * (overwritten); ws: device workspace of sparc_force_workspace_bytes bytes (with
+ * as few as 128 nproj_total ns bytes the sums are taken in fewer parts).
  * All sums run in FP64 in a fixed order.  The first call on an operator
  * builds its gradient tables (FP64, about 4x the projector data) and is
  * synchronous; later calls are asynchronous on stream.  With no atoms
@@ -571,8 +572,8 @@ int sparc_op_set_launch(sparc_op *op, int32_t dtype, int32_t tile_z, int32_t til
                         int32_t col_group, int32_t col_block);
 
 /* Measure the patch heights, a few x splits, column groups and column blocks
- * (1 or 2) of the vector step kernels for this op (its grid, atoms and projectors), dtype and
- * column count on scratch blocks (allocated and freed here), timing the launch
+ * (1 or 2) of the vector step kernels, and the row-pair kernels, for this op
+ * (its grid, atoms and projectors), dtype and column count on scratch blocks (allocated and freed here), timing the launch
  * a filter step makes (projections in and out), apply the fastest to the op
  * for blocks of ns columns (other widths keep the library's choice), and
  * return it (out params may be NULL; best_us = microseconds per recurrence
@@ -587,10 +588,10 @@ int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *stream, int32_
                    int32_t *chunk_x, int32_t *col_group, int32_t *col_block, double *best_us);
 
 /* Launch configuration of the step kernels for a dtype and ns as chosen by
- * the library for the op (out parameters may be NULL).  For grids the vector
- * kernels take: tile_z, tile_y, chunk_x, col_group and col_block of the
- * vector launch; otherwise the scalar kernels' patch (32 x 16), x-chunk and
- * col_group = col_block = 1. */
+ * the library for the op (out parameters may be NULL).  For blocks the vector
+ * or row-pair kernels take: tile_z, tile_y, chunk_x, col_group and col_block of
+ * that launch (the row-pair kernels' patch is chosen for the grid); otherwise
+ * the scalar kernels' patch (32 x 16), x-chunk and col_group = col_block = 1. */
 int sparc_step_config(const sparc_op *op, int32_t dtype, int32_t ns, int32_t *tile_z, int32_t *tile_y,
                       int32_t *chunk_x, int32_t *col_group, int32_t *col_block);
 

@@ -377,7 +377,9 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
         }
         off.push_back((int)cover.size());
         // scatter blocks: at most kBlock nodes touching at most kScatterSlots atoms
-        std::vector<int> blk_pt{0}, blk_at{0}, blk_atoms, ent(4 * raw.size());
+        std::vector<int> blk_pt{0}, blk_at{0}, blk_atoms, ent(4 * raw.size()), entu;
+        const bool unit_ent = chiu_total <= 0x7fffffffLL;
+        if (unit_ent) entu.resize(ent.size());
         std::vector<int> slot_of(natoms, -1);
         std::vector<int> cur;
         auto close_block = [&](int end_pt) {
@@ -411,6 +413,12 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
                 ent[4 * e + 1] = nbox;
                 ent[4 * e + 2] = slot_of[J];
                 ent[4 * e + 3] = a.nproj;
+                if (unit_ent) {
+                    entu[4 * e + 0] = (int)(a.chiu0 + upos[a.box0 + raw[e].second]);
+                    entu[4 * e + 1] = 4 * a.nunits;
+                    entu[4 * e + 2] = slot_of[J];
+                    entu[4 * e + 3] = a.nproj;
+                }
             }
         }
         close_block((int)pts.size());
@@ -429,6 +437,7 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
             {&op->d_nl_off, &off},       {&op->d_nl_ent, &ent},        {&op->d_nl_blk_pt, &blk_pt},
             {&op->d_nl_blk_at, &blk_at}, {&op->d_nl_blk_atoms, &blk_atoms}, {&op->d_nl_proj, &proj},
             {&op->d_nl_seg, &seg}};
+        if (unit_ent) at.push_back({&op->d_nl_entu, &entu});
         size_t total = 0;
         for (auto &t : at) total += (t.second->size() + 63) / 64 * 64;
         if (hipMalloc(&op->d_tables, total * sizeof(int)) != hipSuccess)

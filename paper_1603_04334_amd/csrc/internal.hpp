@@ -86,6 +86,7 @@ struct sparc_op {
     int *d_nl_pts = nullptr;
     int *d_nl_off = nullptr;
     int *d_nl_ent = nullptr;  // int4 records
+    int *d_nl_entu = nullptr; // the same for chi in unit layout (null: past int indices)
     int *d_nl_blk_pt = nullptr;
     int *d_nl_blk_at = nullptr;
     int *d_nl_blk_atoms = nullptr;
