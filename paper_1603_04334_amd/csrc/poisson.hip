@@ -15,7 +15,7 @@
 //  * right-hand side c - d, with d from the slabs, and the partial sums of
 //    its square;
 //  * CG iteration, three launches: q = A p with the partial sums of p.q (the
-//    stencil kernel of poisson_step.hip on vectors without a potential; A =
+//    stencil kernel of vstep.hip on vectors without a potential; A =
 //    (1/2 pi) (-1/2 lap_h)); r -= alpha q, z = M^-1 r per block and the
 //    partials of r.z and r.r; x += alpha p, the convergence test and
 //    p = z + beta p.  Scalars never leave the device: every workgroup finishes
@@ -28,8 +28,8 @@
 //    by a dense symmetric inverse per shape, in bricks along z so that global
 //    accesses are coalesced rows (bj_kernel).
 //  What bounds it: 11 passes of 8 N_d bytes per iteration (14 with p.q and the
-//  x update in passes of their own): 160^3 138 -> 80 us per iteration, 361 MB at
-//  4.5 TB/s; 96^3 57 -> 33 us; 49 x 44 x 41 33 -> 27 us, launches and their
+//  x update in passes of their own): 160^3 138 -> 77 us per iteration, 361 MB at
+//  4.7 TB/s; 96^3 57 -> 30 us; 49 x 44 x 41 33 -> 27 us, launches and their
 //  latency.
 #include <algorithm>
 #include <cmath>
@@ -45,7 +45,11 @@ constexpr int kNM = (kLmax + 1) * (kLmax + 1);     // moments
 constexpr int kPT = 256;                           // threads per workgroup
 constexpr int kBjStage = 64;                       // largest block (nodes) whose inverse is staged in LDS
 constexpr int kRedMax = 1024;                      // workgroups of the reduction kernels
-constexpr int kChunk = 8;                          // CG iterations enqueued between convergence reads
+// CG iterations enqueued between convergence reads.  A read leaves the chip idle
+// for about 30 us, an iteration after the converged one costs three empty
+// launches.  8, 16, 24, 32: 24^3 1.68, 1.62, 1.43, 1.72 ms; 96^3 7.56, 7.06, 6.90,
+// 6.90 ms; 160^3 30.8, 29.9, 29.6, 29.5 ms.
+constexpr int kChunk = 24;
 constexpr double kFourPi = 12.566370614359172954;  // 4 pi
 
 struct HarmNorm {
