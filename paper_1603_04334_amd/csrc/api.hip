@@ -444,7 +444,7 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
             return cleanup(fail(SPARC_E_NOMEM, "device allocation of projector tables failed"));
         // small sets go over in one copy, large ones without a host copy of their own
         std::vector<int> all;
-        const bool joint = total <= (size_t)1 << 16;
+        const bool joint = total <= (size_t)1 << 18;
         if (joint) all.resize(total);
         size_t place = 0;
         for (auto &t : at) {
