@@ -459,6 +459,9 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
         if (joint && hipMemcpy(op->d_tables, all.data(), total * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
             return cleanup(fail(SPARC_E_HIP, "copy of projector tables failed"));
     }
+    // the copies ran on the null stream; streams that do not wait for it may use
+    // the operator next
+    if (hipStreamSynchronize(0) != hipSuccess) return cleanup(fail(SPARC_E_HIP, "copies of the operator's data failed"));
     *out = op;
     return SPARC_OK;
 }

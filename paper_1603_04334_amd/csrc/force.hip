@@ -170,6 +170,7 @@ int build_force_tables(const sparc_op *op)
     SPARC_HIP(hipMemcpy(op->d_funits, units.data(), units.size() * sizeof(int), hipMemcpyHostToDevice));
     SPARC_HIP(hipMemcpy(op->d_ffun, fun.data(), fun.size() * sizeof(double), hipMemcpyHostToDevice));
     SPARC_HIP(hipMemcpy(op->d_fgamma, gam.data(), gam.size() * sizeof(double), hipMemcpyHostToDevice));
+    SPARC_HIP(hipStreamSynchronize(0));  // the caller's stream need not wait for the null stream
     op->force_ready = true;
     return SPARC_OK;
 }
