@@ -116,6 +116,9 @@ int build_force_tables(const sparc_op *op)
             nfun += 4 * (size_t)B.nunits * B.nf;
         }
     }
+    // lanes past their share read their box's first unit: one more for an empty
+    // box at the end of the table
+    units.insert(units.end(), 2, 0);
     std::vector<double> fun(nfun, 0.0);
     for (int J = 0; J < natoms; ++J) {
         const AtomDev &A = op->atoms[J];
@@ -195,6 +198,7 @@ __device__ __forceinline__ void force_accum(const ForceBox &B, const int2 *__res
         f[t] = fun + B.fun0 + (long long)(j < B.nf ? j : 0) * B.nunits * kUnit;
     }
     const int nu = B.nunits, step = 4 * waves;
+    if (nu == 0) return;  // an arm cut off by the walls
     int u = 4 * wave + k;
     int2 qn = un[u < nu ? u : 0];
 #pragma unroll 1
