@@ -820,7 +820,8 @@ static void launch_rotate_small(const T *Y, long long ldy, const double *Q, T *o
 // leases a handle from a per-device pool: one last used on the same stream
 // (stream order protects its workspace) or one whose completion event has
 // fired; otherwise a new handle is made.  Returning a lease records the event
-// on the call's stream.  Handles are kept until the process ends.
+// on the call's stream.  Handles are kept until the process ends, except one
+// that a call was thrown out of: its state is unknown, it is left behind.
 namespace {
 struct PooledBlas {
     rocblas_handle h = nullptr;
@@ -835,6 +836,7 @@ struct BlasLease {
     hipStream_t stream;
     PooledBlas e;
     rocblas_handle h = nullptr;
+    bool thrown = false;
     explicit BlasLease(hipStream_t s) : stream(s)
     {
         (void)hipGetDevice(&dev);
@@ -879,7 +881,7 @@ struct BlasLease {
     }
     ~BlasLease()
     {
-        if (!h) return;
+        if (!h || thrown) return;
         (void)hipEventRecord(e.done, stream);
         e.last = stream;
         std::lock_guard<std::mutex> lk(g_blas_mu);
@@ -887,6 +889,26 @@ struct BlasLease {
     }
     BlasLease(const BlasLease &) = delete;
     BlasLease &operator=(const BlasLease &) = delete;
+
+    // One library call, its status in rs.  The libraries are C++ inside and do
+    // not all catch their own exceptions (std::bad_variant_access has been seen
+    // to leave one): they end here, with the call, not in the caller's thread.
+    template <typename F>
+    int call(const char *what, rocblas_status &rs, F &&f)
+    {
+        try {
+            rs = f();
+            return SPARC_OK;
+        } catch (const std::exception &x) {
+            thrown = true;
+            (void)hipGetLastError();
+            return fail(SPARC_E_HIP, std::string(what) + " threw: " + x.what());
+        } catch (...) {
+            thrown = true;
+            (void)hipGetLastError();
+            return fail(SPARC_E_HIP, std::string(what) + " threw an unknown exception");
+        }
+    }
 };
 // A HIP error state left behind by a library call that itself reported
 // success.  The one code seen so far (hipErrorStreamCaptureUnsupported, after
@@ -1185,7 +1207,9 @@ int sparc_rayleigh_ritz(const sparc_op *op, int32_t dtype, const void *Y, int64_
         // blocked triangular solves (rocBLAS trsm); C z = theta z by rocSOLVER's
         // divide-and-conquer symmetric eigensolver.  (rocsolver_dsygvd's own
         // reduction issues ~600 matrix-vector solves per call at N_s = 600.)
-        auto lib_call = [&](const char *what, rocblas_status rs) -> int {
+        auto lib_call = [&](const char *what, auto &&f) -> int {
+            rocblas_status rs;
+            if (int threw = lease.call(what, rs, f)) return threw;
             const hipError_t after = hipGetLastError();
             if (rs != rocblas_status_success)
                 return fail(SPARC_E_HIP, std::string(what) + " failed: " + rocblas_status_to_string(rs) +
@@ -1193,7 +1217,8 @@ int sparc_rayleigh_ritz(const sparc_op *op, int32_t dtype, const void *Y, int64_
             if (after != hipSuccess) return note_library_error(what, after);
             return SPARC_OK;
         };
-        if ((st = lib_call("rocsolver_dpotrf", rocsolver_dpotrf(hb, rocblas_fill_upper, ns, Ms, ns, info)))) return st;
+        if ((st = lib_call("rocsolver_dpotrf", [&] { return rocsolver_dpotrf(hb, rocblas_fill_upper, ns, Ms, ns, info); })))
+            return st;
         int pinfo = 0;
         SPARC_HIP(hipMemcpyAsync(&pinfo, info, sizeof(int), hipMemcpyDeviceToHost, s));
         SPARC_HIP(hipStreamSynchronize(s));
@@ -1202,23 +1227,22 @@ int sparc_rayleigh_ritz(const sparc_op *op, int32_t dtype, const void *Y, int64_
             return fail(SPARC_E_BREAKDOWN, "Cholesky of M_s failed (info=" + std::to_string(pinfo) +
                                                "): the filtered block is numerically rank deficient");
         }
-        const double one = 1.0;
-        if ((st = lib_call("rocblas_dtrsm", rocblas_dtrsm(hb, rocblas_side_left, rocblas_fill_upper,
-                                                          rocblas_operation_transpose, rocblas_diagonal_non_unit, ns,
-                                                          ns, &one, Ms, ns, Hs, ns))))
+        // Hs = op(U)^-1 Hs (left) or Hs op(U)^-1 (right)
+        auto solve = [&](rocblas_side side, rocblas_operation op_u) -> int {
+            const double one = 1.0;
+            return lib_call("rocblas_dtrsm", [&] {
+                return rocblas_dtrsm(hb, side, rocblas_fill_upper, op_u, rocblas_diagonal_non_unit, ns, ns, &one, Ms, ns,
+                                     Hs, ns);
+            });
+        };
+        if ((st = solve(rocblas_side_left, rocblas_operation_transpose))) return st;
+        if ((st = solve(rocblas_side_right, rocblas_operation_none))) return st;
+        if ((st = lib_call("rocsolver_dsyevd", [&] {
+                 return rocsolver_dsyevd(hb, evec ? rocblas_evect_original : rocblas_evect_none, rocblas_fill_upper, ns,
+                                         Hs, ns, D, E, info);
+             })))
             return st;
-        if ((st = lib_call("rocblas_dtrsm", rocblas_dtrsm(hb, rocblas_side_right, rocblas_fill_upper,
-                                                          rocblas_operation_none, rocblas_diagonal_non_unit, ns, ns,
-                                                          &one, Ms, ns, Hs, ns))))
-            return st;
-        if ((st = lib_call("rocsolver_dsyevd",
-                           rocsolver_dsyevd(hb, evec ? rocblas_evect_original : rocblas_evect_none, rocblas_fill_upper,
-                                            ns, Hs, ns, D, E, info))))
-            return st;
-        if (evec && (st = lib_call("rocblas_dtrsm", rocblas_dtrsm(hb, rocblas_side_left, rocblas_fill_upper,
-                                                                 rocblas_operation_none, rocblas_diagonal_non_unit, ns,
-                                                                 ns, &one, Ms, ns, Hs, ns))))
-            return st;
+        if (evec && (st = solve(rocblas_side_left, rocblas_operation_none))) return st;
     }
     // Ritz values and the solver's status in one copy
     std::vector<double> host((size_t)ns + 1);
@@ -1286,21 +1310,27 @@ int sparc_rotate(int32_t dtype, const void *Y, int64_t ldy, int64_t nd, int32_t 
         BlasLease lease(s);
         if (!lease.h) return fail(SPARC_E_HIP, "rocblas_create_handle failed");
         rocblas_status rs;
+        int st;
         if (dtype == SPARC_F64) {
             hipLaunchKernelGGL(pad_rotation<double>, stream_grid((long long)ldq * ns), dim3(256), 0, s, Q, ns,
                                (double *)ws, ldq, ns);
             const double one = 1.0, zero = 0.0;
-            rs = rocblas_dgemm(lease.h, rocblas_operation_none, rocblas_operation_none, (rocblas_int)nd, ns, ns, &one,
-                               (const double *)Y, (rocblas_int)ldy, (const double *)ws, ldq, &zero, (double *)out,
-                               (rocblas_int)ldo);
+            st = lease.call("rocblas_dgemm", rs, [&] {
+                return rocblas_dgemm(lease.h, rocblas_operation_none, rocblas_operation_none, (rocblas_int)nd, ns, ns, &one,
+                                     (const double *)Y, (rocblas_int)ldy, (const double *)ws, ldq, &zero, (double *)out,
+                                     (rocblas_int)ldo);
+            });
         } else {
             hipLaunchKernelGGL(pad_rotation<float>, stream_grid((long long)ldq * ns), dim3(256), 0, s, Q, ns,
                                (float *)ws, ldq, ns);
             const float one = 1.0f, zero = 0.0f;
-            rs = rocblas_sgemm(lease.h, rocblas_operation_none, rocblas_operation_none, (rocblas_int)nd, ns, ns, &one,
-                               (const float *)Y, (rocblas_int)ldy, (const float *)ws, ldq, &zero, (float *)out,
-                               (rocblas_int)ldo);
+            st = lease.call("rocblas_sgemm", rs, [&] {
+                return rocblas_sgemm(lease.h, rocblas_operation_none, rocblas_operation_none, (rocblas_int)nd, ns, ns, &one,
+                                     (const float *)Y, (rocblas_int)ldy, (const float *)ws, ldq, &zero, (float *)out,
+                                     (rocblas_int)ldo);
+            });
         }
+        if (st) return st;
         const hipError_t after = hipGetLastError();
         if (rs != rocblas_status_success)
             return fail(SPARC_E_HIP, std::string("rocBLAS GEMM of the rotation failed: ") + rocblas_status_to_string(rs));

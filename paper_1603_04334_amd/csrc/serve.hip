@@ -63,6 +63,7 @@ struct Cluster {
     // device state
     sparc_op *op = nullptr;
     void *X = nullptr, *Y = nullptr, *ws = nullptr, *rr = nullptr, *evec = nullptr, *rot = nullptr;
+    void *lanczos = nullptr;  // workspace of the first request's bounds
     size_t ws_bytes = 0, rr_bytes = 0, rot_bytes = 0;
     double a0 = 0, a = 0, b = 0;
 };
@@ -148,7 +149,7 @@ size_t estimate_footprint(const Cluster &c, int lanczos_k)
 // work on the device.
 void free_device(Cluster &c, hipStream_t s)
 {
-    for (void **p : {&c.X, &c.Y, &c.ws, &c.rr, &c.evec, &c.rot}) {
+    for (void **p : {&c.X, &c.Y, &c.ws, &c.rr, &c.evec, &c.rot, &c.lanczos}) {
         if (*p) (void)hipFreeAsync(*p, s);
         *p = nullptr;
     }
@@ -182,11 +183,12 @@ int execute(sparc_server *srv, Cluster &c, const Request &r, hipStream_t s, spar
         c.resident = true;
         // bounds from the device Lanczos; later requests keep a0 and b
         const size_t lb = sparc_lanczos_workspace_bytes(c.op, srv->lanczos_k);
-        void *lw = nullptr;
-        if (hipMallocAsync(&lw, lb, s) != hipSuccess) return fail(SPARC_E_NOMEM, "Lanczos workspace allocation failed");
+        if (hipMallocAsync(&c.lanczos, lb, s) != hipSuccess)
+            return fail(SPARC_E_NOMEM, "Lanczos workspace allocation failed");
         std::vector<double> lt(srv->lanczos_k);
-        st = sparc_lanczos(c.op, srv->lanczos_k, c.v0, nullptr, nullptr, lt.data(), lw, lb, s);
-        (void)hipFreeAsync(lw, s);
+        st = sparc_lanczos(c.op, srv->lanczos_k, c.v0, nullptr, nullptr, lt.data(), c.lanczos, lb, s);
+        (void)hipFreeAsync(c.lanczos, s);
+        c.lanczos = nullptr;
         if (st) return st;
         double ub = 0;
         sparc_upper_bound(c.op, &ub);
@@ -218,6 +220,21 @@ int execute(sparc_server *srv, Cluster &c, const Request &r, hipStream_t s, spar
     for (int p = 0; p < passes; ++p) degsum += deg[p];
     res.updates = c.nd * (int64_t)c.ns * degsum;
     return SPARC_OK;
+}
+
+// execute, with every exception turned into a status: one that left the worker
+// would end the process, and with it every client's request
+int execute_guarded(sparc_server *srv, Cluster &c, const Request &r, hipStream_t s, sparc_job_result &res)
+{
+    try {
+        return execute(srv, c, r, s, res);
+    } catch (const std::bad_alloc &) {
+        return fail(SPARC_E_NOMEM, "host allocation failed");
+    } catch (const std::exception &x) {
+        return fail(SPARC_E_HIP, std::string("a library call of the request threw: ") + x.what());
+    } catch (...) {
+        return fail(SPARC_E_HIP, "a library call of the request threw an unknown exception");
+    }
 }
 
 // first pending request that may start now (FIFO order, skipping blocked ones)
@@ -259,7 +276,7 @@ void worker_main(sparc_server *srv)
         res.step = r.step;
         res.t_submit = r.t_submit;
         res.t_start = now_s();
-        res.status = execute(srv, c, r, s, res);
+        res.status = execute_guarded(srv, c, r, s, res);
         if (res.status != SPARC_OK) {
             (void)hipStreamSynchronize(s);
             std::strncpy(res.error, sparc_last_error(), sizeof(res.error) - 1);
