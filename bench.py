@@ -18,6 +18,7 @@ import argparse
 import hashlib
 import json
 import os
+import subprocess
 import sys
 import time
 
@@ -442,6 +443,20 @@ def serve_measure(rates, nrequests, workers):
     return out
 
 
+def serve_in_child(args):
+    """The serving measurement in a process of its own: if it dies, the numbers
+    measured before it are still printed, and its end is recorded."""
+    cmd = [sys.executable, os.path.abspath(__file__), "--serve-only", "--serve-rates", args.serve_rates,
+           "--serve-requests", str(args.serve_requests), "--serve-workers", str(args.serve_workers)]
+    try:
+        r = subprocess.run(cmd, stdout=subprocess.PIPE, text=True, timeout=1200)
+    except subprocess.TimeoutExpired:
+        return {"error": "the serving run did not end within 1200 s"}
+    if r.returncode != 0:
+        return {"error": f"the serving run ended with status {r.returncode}"}
+    return json.loads(r.stdout.strip().splitlines()[-1])
+
+
 def secondary(args):
     """Filter throughput of the medium cluster (96^3, 64 orbitals, m = 24) in
     FP32 and FP64 and the latency of one whole pass and of one filter on the
@@ -767,7 +782,7 @@ def main():
     if not args.no_serve:
         print("bench: serving", file=sys.stderr, flush=True)
         torch.cuda.empty_cache()
-        out["serving"] = serve_measure(rates, args.serve_requests, args.serve_workers)
+        out["serving"] = serve_in_child(args)
     if not args.no_cpu_baseline:
         print("bench: CPU oracle baseline", file=sys.stderr, flush=True)
         out["cpu_baseline"] = cpu_baseline(case, cl, op, main_res["bounds"],
