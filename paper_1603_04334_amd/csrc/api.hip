@@ -334,7 +334,7 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
             hipMemcpy(op->d_hg32, hg32.data(), op->nproj_total * sizeof(float), hipMemcpyHostToDevice))
             return cleanup(fail(SPARC_E_HIP, "copy of projector data failed"));
         int st;
-        if ((st = build_unit_chi(op, upos, chiu_total))) return cleanup(st);
+        if ((st = build_unit_chi(op, chiu_total))) return cleanup(st);
     }
 
     // cube-node grid offsets and the unique covered nodes with their (atom, cube index) entries

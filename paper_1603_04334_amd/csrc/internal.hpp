@@ -189,9 +189,8 @@ int append_units(const int n[3], int64_t nd, const int lo[3], const int ext[3], 
                  std::vector<int> &pos);
 
 // chi in unit layout (op->d_chiu64, d_chiu32: total values) and in FP32
-// (op->d_chi32) from op->d_chi64 and the places of the cube nodes, atoms back to
-// back.  Synchronous.
-int build_unit_chi(sparc_op *op, const std::vector<int> &pos, int64_t total);
+// (op->d_chi32) from op->d_chi64, enqueued on the null stream.
+int build_unit_chi(sparc_op *op, int64_t total);
 
 // out = Y Q on the matrix cores (rotate.hip); false: not a size it takes
 bool launch_rotate_mfma(int dtype, const void *Y, int64_t ldy, const double *Q, void *out, int64_t ldo, int64_t nd,

@@ -62,14 +62,19 @@ __global__ void __launch_bounds__(256) scatter_kernel(const ScatterArgs<T> s, in
     scatter_item<T, NC, NP>(s, blockIdx.x, blockIdx.y, (T *)scatter_lds, npm);
 }
 
-// blockIdx.x: atom; its nodes' places from pos + box0.  Also chi in FP32.
-__global__ void __launch_bounds__(256) unit_chi_kernel(const AtomDev *atoms, const double *chi, float *chi32,
-                                                       const int *pos, double *chiu64, float *chiu32)
+// blockIdx.x: atom.  chi at the places append_units gives the cube's nodes, and
+// chi in FP32.
+__global__ void __launch_bounds__(256) unit_chi_kernel(const AtomDev *atoms, const double *chi, float *chi32, int n2,
+                                                       int n3, long long nd, double *chiu64, float *chiu32)
 {
     const AtomDev A = atoms[blockIdx.x];
     const int nbox = A.ext[0] * A.ext[1] * A.ext[2];
+    const int s0 = A.lo[2] / kUnit, per_row = (A.lo[2] + A.ext[2] - 1) / kUnit - s0 + 1;
     for (int t = blockIdx.y * 256 + threadIdx.x; t < nbox; t += gridDim.y * 256) {
-        const int d = pos[A.box0 + t];
+        const int r = t / A.ext[2], z = A.lo[2] + t % A.ext[2], s = z / kUnit;
+        const long long row = (long long)n3 * ((A.lo[1] + r % A.ext[1]) + (long long)n2 * (A.lo[0] + r / A.ext[1]));
+        const long long first = max(0LL, min(row + kUnit * s, nd - kUnit));
+        const int d = kUnit * (r * per_row + s - s0) + (int)(row + z - first);
         for (int p = 0; p < A.nproj; ++p) {
             const double v = chi[A.chi0 + (long long)p * nbox + t];
             const long long o = A.chiu0 + (long long)p * A.nunits * kUnit + d;
@@ -80,21 +85,15 @@ __global__ void __launch_bounds__(256) unit_chi_kernel(const AtomDev *atoms, con
     }
 }
 
-int build_unit_chi(sparc_op *op, const std::vector<int> &pos, int64_t total)
+int build_unit_chi(sparc_op *op, int64_t total)
 {
-    int *d_pos = nullptr;
-    if (hipMalloc(&d_pos, pos.size() * sizeof(int)) != hipSuccess)
-        return fail(SPARC_E_NOMEM, "device allocation of projector tables failed");
-    hipError_t e = hipMemcpy(d_pos, pos.data(), pos.size() * sizeof(int), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(op->d_chiu64, 0, total * sizeof(double));
+    hipError_t e = hipMemset(op->d_chiu64, 0, total * sizeof(double));
     if (e == hipSuccess) e = hipMemset(op->d_chiu32, 0, total * sizeof(float));
     if (e == hipSuccess) {
         hipLaunchKernelGGL(unit_chi_kernel, dim3(op->natoms, 4), dim3(256), 0, 0, op->d_atoms, op->d_chi64,
-                           op->d_chi32, d_pos, op->d_chiu64, op->d_chiu32);
+                           op->d_chi32, op->n[1], op->n[2], op->nd, op->d_chiu64, op->d_chiu32);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(0);
-    (void)hipFree(d_pos);
     return e == hipSuccess ? SPARC_OK : fail(SPARC_E_HIP, std::string("projector tables: ") + hipGetErrorString(e));
 }
 
