@@ -459,8 +459,11 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
         if (joint && hipMemcpy(op->d_tables, all.data(), total * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
             return cleanup(fail(SPARC_E_HIP, "copy of projector tables failed"));
     }
-    // the copies ran on the null stream; streams that do not wait for it may use
-    // the operator next
+    // The copies and fills run on the null stream.  A copy from pageable memory
+    // may return once the data is staged, a fill as soon as it is enqueued (the
+    // API synchronisation rules of the CUDA runtime, which HIP follows), and a
+    // non-blocking stream, which may use the operator next, does not wait for the
+    // null stream.
     if (hipStreamSynchronize(0) != hipSuccess) return cleanup(fail(SPARC_E_HIP, "copies of the operator's data failed"));
     *out = op;
     return SPARC_OK;

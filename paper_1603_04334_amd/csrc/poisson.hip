@@ -971,6 +971,11 @@ extern "C" int sparc_poisson_create(const sparc_grid *grid, int32_t lmax, const 
         sparc_poisson_destroy(P);
         return fail(SPARC_E_HIP, "copy of the block inverses failed");
     }
+    // see sparc_op_create: a solve may run on a stream that does not wait for the null stream
+    if (hipStreamSynchronize(0) != hipSuccess) {
+        sparc_poisson_destroy(P);
+        return fail(SPARC_E_HIP, "copies of the solver's data failed");
+    }
     P->nmom = (int)std::max<long long>(1, std::min<long long>(256, (nd + kPT - 1) / kPT));
     P->nred = (int)std::max<long long>(1, std::min<long long>(kRedMax, (nd + 4 * kPT - 1) / (4 * kPT)));
     if (P->diag) {

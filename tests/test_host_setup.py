@@ -1,7 +1,11 @@
 """What operator setup asks of the HIP runtime."""
+import ctypes
+
+import numpy as np
 import pytest
 
 import host_library
+from paper_1603_04334_amd import binding
 
 pytestmark = pytest.mark.skipif(not host_library.available(), reason="needs hipcc")
 
@@ -15,3 +19,44 @@ def test_operator_setup_frees_nothing():
     assert st == 0
     assert not host_library.calls("hipFree", "hipFreeAsync")
     L.sparc_op_destroy(op)
+
+
+def _waits_last(names, L, make):
+    """make() -> (status, destroy); its last null-stream copy or fill is followed by a wait for that stream."""
+    L.stub_reset()
+    st, destroy = make()
+    assert st == 0
+    log = [c for c in host_library.calls() if c[0] in names or c[0] == "hipStreamSynchronize"]
+    copies = [i for i, c in enumerate(log) if c[0] in names]
+    waits = [i for i, c in enumerate(log) if c[0] == "hipStreamSynchronize" and c[1]["stream"] == 0]
+    assert copies and waits and waits[-1] > copies[-1]
+    destroy()
+
+
+NULL_STREAM = ("hipMemcpy", "hipMemset")
+
+
+def test_operator_setup_waits_for_its_copies():
+    L = host_library.load()
+
+    def make():
+        st, op = host_library.create(host_library.cluster((12, 11, 10), [((0, 3, 2), (5, 4, 7))]))
+        return st, lambda: L.sparc_op_destroy(op)
+
+    _waits_last(NULL_STREAM, L, make)
+
+
+@pytest.mark.parametrize("block", [(4, 4, 4), (2, 2, 2)])
+def test_poisson_setup_waits_for_its_copies(block):
+    L = host_library.load()
+
+    def make():
+        g = binding.sparc_grid()
+        g.n[:] = [9, 10, 11]
+        g.h, g.radius = 0.5, 6
+        b = (ctypes.c_int32 * 3)(*block)
+        h = ctypes.c_void_p()
+        st = L.sparc_poisson_create(ctypes.byref(g), 6, ctypes.cast(b, ctypes.c_void_p), ctypes.byref(h))
+        return st, lambda: L.sparc_poisson_destroy(h)
+
+    _waits_last(NULL_STREAM, L, make)
