@@ -587,6 +587,9 @@ int sparc_batch_create(const sparc_batch_job *jobs, int32_t njobs, int32_t mode,
         hipMemcpy(b->d_seg, b->segs.data(), b->segs.size() * sizeof(BatchSegment), hipMemcpyHostToDevice) ||
         hipMemcpy(b->d_coef, coef.data(), ncoef * sizeof(double), hipMemcpyHostToDevice))
         return cleanup(fail(SPARC_E_HIP, "copy of the batch schedule failed"));
+    // see sparc_op_create: the batch may run on a stream that does not wait for the null stream
+    if (hipStreamSynchronize(0) != hipSuccess)
+        return cleanup(fail(SPARC_E_HIP, "copies of the batch schedule failed"));
     // persistent grid: the resident workgroups of the whole device
     int cus = 0, per_cu = 0;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device);

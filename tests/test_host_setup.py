@@ -60,3 +60,19 @@ def test_poisson_setup_waits_for_its_copies(block):
         return st, lambda: L.sparc_poisson_destroy(h)
 
     _waits_last(NULL_STREAM, L, make)
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2, 3, 4, 5])
+def test_batch_setup_waits_for_its_copies(mode):
+    L = host_library.load()
+    st, op = host_library.create(host_library.cluster((12, 12, 12), [((3, 3, 3), (5, 5, 5))]))
+    assert st == 0
+    X, Y = np.zeros((3, 1728)), np.zeros((3, 1728))
+
+    def make():
+        job = binding.sparc_batch_job(op, 0, X.ctypes.data, 1728, Y.ctypes.data, 1728, 3, 4, -1.0, 1.0, 2.0)
+        h = ctypes.c_void_p()
+        return L.sparc_batch_create(ctypes.byref(job), 1, mode, ctypes.byref(h)), lambda: L.sparc_batch_destroy(h)
+
+    _waits_last(NULL_STREAM, L, make)
+    L.sparc_op_destroy(op)
