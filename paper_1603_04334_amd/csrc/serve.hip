@@ -128,18 +128,25 @@ int launch_copy(const void *src, long long lds, void *dst, long long ldd, long l
 size_t estimate_footprint(const Cluster &c, int lanczos_k)
 {
     const size_t s = c.dtype == SPARC_F64 ? 8 : 4;
-    size_t chi = 0, box = 0, nproj = 0;
+    size_t chi = 0, box = 0, nproj = 0, chiu = 0, units = 0;
     for (auto &a : c.atoms) {
         const size_t nb = (size_t)a.a.ext[0] * a.a.ext[1] * a.a.ext[2];
+        // the cube's rows in units of four nodes (append_units)
+        const size_t nu = (size_t)a.a.ext[0] * a.a.ext[1] * ((a.a.lo[2] + a.a.ext[2] - 1) / 4 - a.a.lo[2] / 4 + 1);
         chi += nb * a.a.nproj;
         box += nb;
         nproj += a.a.nproj;
+        chiu += 4 * nu * a.a.nproj;
+        units += nu;
     }
-    const size_t nd = (size_t)c.nd, ns = (size_t)c.ns;
-    size_t f = nd * 12 + chi * 12 + box * 28 + 4096;                 // operator
-    f += 3 * nd * ns * s + 4 * std::max<size_t>(1, nproj) * ns * s;  // X, Y, filter workspace
-    f += nd * ns * 8;                                                 // Rayleigh-Ritz H Y
-    f += 4 * std::max<size_t>(1, nproj) * ns * 8 + 1024 * 2 * ns * ns * 8 + 4 * (ns + 64) * (ns + 64) * 8 + 4096;
+    const size_t nd = (size_t)c.nd, ns = (size_t)c.ns, part = kGatherSplit * std::max<size_t>(1, nproj) * ns;
+    // operator: V_eff; chi node by node and in units, FP64 and FP32 each; per
+    // cube node its grid index, two scatter entries, its projector and its share
+    // of the node and block lists (at most 15 integers); two integers per unit
+    size_t f = nd * 12 + (chi + chiu) * 12 + box * 60 + units * 8 + c.atoms.size() * sizeof(AtomDev) + nproj * 12 + 16384;
+    f += 3 * nd * ns * s + part * s;  // X, Y, filter workspace
+    f += nd * ns * 8;                 // Rayleigh-Ritz H Y
+    f += part * 8 + 1024 * 2 * ns * ns * 8 + 4 * (ns + 64) * (ns + 64) * 8 + 4096;
     // first request only: the Lanczos basis and workspace
     return f + nd * (lanczos_k + 1) * 8 + 4096 * (lanczos_k + 2) * 8;
 }

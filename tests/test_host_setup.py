@@ -76,3 +76,26 @@ def test_batch_setup_waits_for_its_copies(mode):
 
     _waits_last(NULL_STREAM, L, make)
     L.sparc_op_destroy(op)
+
+
+@pytest.mark.parametrize("ns,natoms,edge", [(1, 60, 12), (4, 8, 9), (70, 3, 7)])
+@pytest.mark.parametrize("dtype", [binding.SPARC_F64, binding.SPARC_F32])
+def test_admission_estimate_covers_a_cluster(ns, natoms, edge, dtype):
+    """What the server reserves for a cluster against what its first request allocates."""
+    L = host_library.load()
+    rng = np.random.default_rng(3)
+    n = 40
+    cl = host_library.cluster((n, n, n), [(rng.integers(0, n - edge + 1, 3).tolist(), (edge,) * 3)
+                                          for _ in range(natoms)], nproj=9)
+    g, atoms, veff, keep = binding._cluster_arrays(cl)
+    d = binding.sparc_cluster_desc(g, veff.ctypes.data_as(binding._dp), natoms, atoms, dtype, ns, 4, None, cl.nd, None, 1.0)
+    L.stub_reset()
+    st, op = host_library.create(cl)
+    assert st == 0
+    used = sum(c["bytes"] for _, c in host_library.calls("hipMalloc"))
+    block = cl.nd * ns * (8 if dtype == binding.SPARC_F64 else 4)
+    used += 2 * block + L.sparc_workspace_bytes(op, dtype, ns, 1) + L.sparc_rr_workspace_bytes(op, dtype, ns)
+    used += 8 * ns * ns + L.sparc_rotate_workspace_bytes(dtype, ns) + L.sparc_lanczos_workspace_bytes(op, 40)
+    reserved = L.sparc_cluster_footprint(ctypes.byref(d), 40)
+    assert used <= reserved
+    L.sparc_op_destroy(op)
