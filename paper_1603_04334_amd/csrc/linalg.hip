@@ -350,46 +350,55 @@ __global__ void __launch_bounds__(256) omega_dots_kernel(const double *alpha, do
     }
 }
 
+constexpr int kOrthPanel = 1024;  // coefficients in LDS at a time: the step count has no limit
+
 // where the decision (run) asks for it: c_i = u_i^T w / nu_i^2 from the
 // partials (every workgroup in the same fixed order, one wave per c_i), w -=
-// sum_i c_i u_i, and partial[b] = sum over block b's nodes of the new w^2
+// sum_i c_i u_i by panels of kOrthPanel vectors, and partial[b] = sum over
+// block b's nodes of the new w^2
 __global__ void __launch_bounds__(256) orth_apply_norm(double *w, const double *__restrict__ V, long long ldv, int nv,
                                                        const double *__restrict__ dots, const double *__restrict__ nu,
                                                        long long n, double *__restrict__ partial, const int *run)
 {
-    extern __shared__ double coeff[];
+    __shared__ double coeff[kOrthPanel];
     if (!*run) return;
     __shared__ double red[4];
-    for (int i = threadIdx.x >> 6; i < nv; i += 4) {
-        double v = 0.0;
-#pragma unroll
-        for (int u = 0; u < kDotBlocks / 64; ++u) v += dots[(long long)i * kDotBlocks + 64 * u + (threadIdx.x & 63)];
-        v = wave_sum(v);
-        if ((threadIdx.x & 63) == 0) coeff[i] = v / (nu[i] * nu[i]);
-    }
-    __syncthreads();
     long long beg, end;
     block_segment(n, beg, end);
     double nrm = 0.0;
-    for (long long x0 = beg + threadIdx.x; x0 < end; x0 += 256 * kUnroll) {
-        double s[kUnroll];
+    for (int p0 = 0; p0 < nv; p0 += kOrthPanel) {
+        const int np = min(kOrthPanel, nv - p0);
+        const bool last = p0 + np == nv;
+        if (p0 > 0) __syncthreads();
+        for (int i = threadIdx.x >> 6; i < np; i += 4) {
+            double v = 0.0;
 #pragma unroll
-        for (int r = 0; r < kUnroll; ++r) s[r] = 0.0;
-        for (int i = 0; i < nv; ++i) {
-            const double c = coeff[i];
+            for (int u = 0; u < kDotBlocks / 64; ++u)
+                v += dots[(long long)(p0 + i) * kDotBlocks + 64 * u + (threadIdx.x & 63)];
+            v = wave_sum(v);
+            if ((threadIdx.x & 63) == 0) coeff[i] = v / (nu[p0 + i] * nu[p0 + i]);
+        }
+        __syncthreads();
+        for (long long x0 = beg + threadIdx.x; x0 < end; x0 += 256 * kUnroll) {
+            double s[kUnroll];
+#pragma unroll
+            for (int r = 0; r < kUnroll; ++r) s[r] = 0.0;
+            for (int i = 0; i < np; ++i) {
+                const double c = coeff[i];
+#pragma unroll
+                for (int r = 0; r < kUnroll; ++r) {
+                    const long long x = x0 + 256 * r;
+                    s[r] += c * (x < end ? V[(long long)(p0 + i) * ldv + x] : 0.0);
+                }
+            }
 #pragma unroll
             for (int r = 0; r < kUnroll; ++r) {
                 const long long x = x0 + 256 * r;
-                s[r] += c * (x < end ? V[(long long)i * ldv + x] : 0.0);
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < kUnroll; ++r) {
-            const long long x = x0 + 256 * r;
-            if (x < end) {
-                const double v = w[x] - s[r];
-                w[x] = v;
-                nrm += v * v;
+                if (x < end) {
+                    const double v = w[x] - s[r];
+                    w[x] = v;
+                    if (last) nrm += v * v;
+                }
             }
         }
     }
@@ -1069,7 +1078,7 @@ int sparc_lanczos(const sparc_op *op, int32_t k, const double *v0, double *alpha
         hipLaunchKernelGGL(omega_dots_kernel, rg, tb, 0, s, (const double *)d_alpha, d_nu + 1, j, eps1, Wp, Wc, Wn,
                            d_owed, d_full, d_anorm, (const double *)npart[j & 1], (const double *)V, (long long)n,
                            (const double *)w, n, partial);
-        hipLaunchKernelGGL(orth_apply_norm, rg, tb, nv * sizeof(double), s, w, (const double *)V, (long long)n, nv,
+        hipLaunchKernelGGL(orth_apply_norm, rg, tb, 0, s, w, (const double *)V, (long long)n, nv,
                            (const double *)partial, (const double *)d_nu, n, npart[j & 1], (const int *)(d_full + j));
         SPARC_HIP(hipGetLastError());
     }
