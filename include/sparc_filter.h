@@ -555,8 +555,10 @@ int sparc_profile_reset(void);
  * gathered in its last workgroups) for one dtype: patch extent along z and y
  * (FP32: tile_z = 32 with tile_y 16, 32 or 64; tile_z = 64 with tile_y 16 or
  * 32; tile_z = 80 with tile_y 32; tile_z = 160 with tile_y 24.  FP64: tile_z
- * = 32 with tile_y 8, 16 or 32; tile_z = 64 with tile_y 8, 16 or 24), the
- * number of x-planes per workgroup (chunk_x <= 0: library choice; the x
+ * = 32 with tile_y 8, 16 or 32; tile_z = 64 with tile_y 8, 16 or 24; also a
+ * row-pair patch of the grid, as sparc_step_config and sparc_autotune report
+ * it; where both kinds of kernels have the patch, a block goes to the one it
+ * takes without an override), the number of x-planes per workgroup (chunk_x <= 0: library choice; the x
  * extent is split into equal chunks of at most chunk_x planes) and the column
  * group (col_group <= 0: library choice; that many column blocks of one patch
  * go to consecutive workgroups, so they share V_eff in the L2 cache) and the
@@ -567,7 +569,7 @@ int sparc_profile_reset(void);
  * block never change results; another patch may change the last bits.  Not
  * thread-safe against calls that use the op.
  * Errors: SPARC_E_ARG (null op, bad dtype, unsupported tile, col_block
- * outside 0..2, or 2 on a patch of more than 512 threads). */
+ * outside 0..2, or 2 on a patch of more than 512 threads or a row-pair patch). */
 int sparc_op_set_launch(sparc_op *op, int32_t dtype, int32_t tile_z, int32_t tile_y, int32_t chunk_x,
                         int32_t col_group, int32_t col_block);
 

@@ -508,15 +508,19 @@ int sparc_op_set_launch(sparc_op *op, int32_t dtype, int32_t tile_z, int32_t til
     if (col_block < 0 || col_block > 2) return fail(SPARC_E_ARG, "col_block must be 0, 1 or 2");
     if (tile_z <= 0 && tile_y <= 0) {
         op->tune_shape[dtype] = -1;
+        op->tune_ty[dtype] = 0;
     } else {
-        // patches of TY x TZ nodes offered for the dtype
+        // patches of TY x TZ nodes offered for the dtype, and the row-pair
+        // kernels' own for the grid
         int found = -1;
         for (int p = 0; p < kNumPlans; ++p)
             if (kPlanTZ[p] == tile_z && kPlanTY[p] == tile_y && vec_plan_valid(dtype, p)) found = p;
+        if (found < 0 && rstep_patch(op, dtype, tile_z, tile_y)) found = kRowPair;
         if (found < 0) return fail(SPARC_E_ARG, "unsupported tile shape");
-        if (col_block == 2 && vec_max_cblk(dtype, found) < 2)
+        if (col_block == 2 && (found == kRowPair || vec_max_cblk(dtype, found) < 2))
             return fail(SPARC_E_ARG, "this tile shape takes one column per workgroup");
         op->tune_shape[dtype] = found;
+        op->tune_ty[dtype] = tile_y;
     }
     op->tune_chunk[dtype] = chunk_x > 0 ? chunk_x : 0;
     op->tune_group[dtype] = col_group > 0 ? col_group : 0;

@@ -106,6 +106,14 @@ static int rstep_pitch(int dtype, int tz)
     return need <= 112 ? 112 : need <= 176 ? 176 : 0;
 }
 
+// patch extent along z: whole rows or equal parts of them
+static int rstep_tz(const sparc_op *op, int dtype)
+{
+    const int vz = vec_width(dtype), maxtz = dtype == SPARC_F64 ? 96 : 160;
+    const int kz = (op->n[2] + maxtz - 1) / maxtz;
+    return ((op->n[2] + kz - 1) / kz + vz - 1) / vz * vz;
+}
+
 // threads of a patch (whole waves; 0: the patch does not fit a workgroup)
 static int rstep_threads(const sparc_op *op, int dtype, int tz, int ty, int &nh)
 {
@@ -131,11 +139,11 @@ static int rstep_threads(const sparc_op *op, int dtype, int tz, int ty, int &nh)
 // us; 96^3 x 64 in 1, 4, 8 chunks 137, 138, 160 us.  Patches are as wide as the
 // grid row where it fits (no z halo): 160^3 x 600 24 x 160 5.81 ms, 24 x 80
 // 6.76 ms.
-static void choose_rstep(const sparc_op *op, int dtype, int ns, FLaunch &L)
+// only_ty: the patch's rows, set by hand (0: chosen here).
+static void choose_rstep(const sparc_op *op, int dtype, int ns, FLaunch &L, int only_ty = 0)
 {
-    const int vz = vec_width(dtype), maxtz = dtype == SPARC_F64 ? 96 : 160;
-    const int kz = (op->n[2] + maxtz - 1) / maxtz;
-    const int tz = ((op->n[2] + kz - 1) / kz + vz - 1) / vz * vz;
+    if (op->n[2] < vec_width(dtype)) return;  // a cut row is read as its last whole unit
+    const int tz = rstep_tz(op, dtype);
     const int tiles_z = (op->n[2] + tz - 1) / tz;
     // Workgroups of one patch of `group` columns run back to back and share its
     // V_eff in the XCD's L2.  Fields below 2 MB stay there by themselves (80 x 72
@@ -153,6 +161,7 @@ static void choose_rstep(const sparc_op *op, int dtype, int ns, FLaunch &L)
     for (int ky = 1; ky <= op->n[1]; ++ky) {
         const int ty = ((op->n[1] + ky - 1) / ky + 1) / 2 * 2;
         if (ty < 12 && ky > 1) break;
+        if (only_ty > 0 && ty != only_ty) continue;
         int nh = 0;
         const int nt = rstep_threads(op, dtype, tz, ty, nh);
         // patches below 256 threads cannot host gather items (40 x 32 x 32 x
@@ -162,7 +171,7 @@ static void choose_rstep(const sparc_op *op, int dtype, int ns, FLaunch &L)
         const int w = nt / 64;
         // workgroups of about 10 planes: too few leave CUs idle (118 x 149 x 129
         // x 3: 177 of them, 40 us per step against the scalar kernels' 37.6 us)
-        if ((double)ns * ky * tiles_z * op->n[0] < 4000.0) continue;
+        if (only_ty == 0 && (double)ns * ky * tiles_z * op->n[0] < 4000.0) continue;
         const size_t lds = 2 * (size_t)(ty + 2 * kMaxRadius) * rstep_pitch(dtype, tz) * elem_size(dtype);
         const int percu = std::max(1, std::min(8 / w, (int)(163840 / lds)));
         const int full = std::max(6, percu * w);  // fewer waves than that leave a CU waiting
@@ -205,13 +214,26 @@ static bool take_rstep(const sparc_op *op, int dtype, int ns, bool aligned)
     return pad >= 1.15 * op->n[1] * op->n[2];
 }
 
+bool rstep_patch(const sparc_op *op, int dtype, int tz, int ty)
+{
+    FLaunch L;
+    if (tz == rstep_tz(op, dtype) && ty > 0) choose_rstep(op, dtype, 1, L, ty);
+    return L.plan >= 0;
+}
+
 FLaunch choose_vec_launch(const sparc_op *op, int dtype, int ns, std::initializer_list<int64_t> lds)
 {
     FLaunch L;
     const bool aligned = vec_grid(op, dtype, lds);
     const bool tuned = tune_applies(op, dtype, ns);
-    if (tuned && op->tune_shape[dtype] == kRowPair) {
-        choose_rstep(op, dtype, ns, L);
+    // a patch set by hand that both kinds of kernels offer goes to the one the
+    // library takes for the block itself
+    const int ty = op->tune_ty[dtype];
+    const bool both = ty > 0 && op->tune_shape[dtype] >= 0 && op->tune_shape[dtype] != kRowPair &&
+                      op->tune_cblk[dtype] != 2 && take_rstep(op, dtype, ns, aligned) &&
+                      rstep_patch(op, dtype, kPlanTZ[op->tune_shape[dtype]], ty);
+    if (tuned && (op->tune_shape[dtype] == kRowPair || both)) {
+        choose_rstep(op, dtype, ns, L, ty);
         if (L.plan >= 0 && op->tune_chunk[dtype] > 0) set_chunks(op, (op->n[0] + op->tune_chunk[dtype] - 1) / op->tune_chunk[dtype], L);
         if (L.plan >= 0 && op->tune_group[dtype] > 0) L.cgroup = op->tune_group[dtype];
         if (L.plan >= 0) return L;
@@ -287,28 +309,23 @@ static int launch_rstep_t(const sparc_op *op, const FLaunch &L, const void *yk, 
     int ncb = 0, nitems = 0, ngb = 0;
     if (part && op->natoms > 0) {
         if ((long long)(ns + 15) / 16 > 65535) return fail(SPARC_E_SHAPE, "too many columns for one gather launch");
-        if (nt < 256) {
-            // the patch is too small to host gather items: a launch of its own
-            int st;
-            if ((st = launch_gather(op, dtype, yk, ldk, ns, part, kGatherSplit, stream))) return st;
-        } else {
-            g.Y = (const T *)yk;
-            g.ldy = ldk;
-            g.ns = ns;
-            g.nproj_total = op->nproj_total;
-            g.atoms = op->d_atoms;
-            g.small = op->nd < kUnit;
-            g.units = (const int2 *)op->d_units;
-            g.chiu = std::is_same<T, double>::value ? (const T *)op->d_chiu64 : (const T *)op->d_chiu32;
-            g.box_off = op->d_box_off;
-            g.chi = std::is_same<T, double>::value ? (const T *)op->d_chi64 : (const T *)op->d_chi32;
-            g.part = (T *)part;
-            ncb = (ns + 15) / 16;
-            nitems = op->natoms * ncb * kGatherSplit;
-            const int per = nt / 256;
-            ngb = (nitems + per - 1) / per;
-            if ((long long)a.nblocks + ngb > 0x7fffffffLL) return fail(SPARC_E_SHAPE, "too many workgroups for one launch");
-        }
+        if (nt < 256) return fail(SPARC_E_ARG, "row-pair patch too small to gather projections");
+        g.Y = (const T *)yk;
+        g.ldy = ldk;
+        g.ns = ns;
+        g.nproj_total = op->nproj_total;
+        g.atoms = op->d_atoms;
+        g.small = op->nd < kUnit;
+        g.units = (const int2 *)op->d_units;
+        g.chiu = std::is_same<T, double>::value ? (const T *)op->d_chiu64 : (const T *)op->d_chiu32;
+        g.box_off = op->d_box_off;
+        g.chi = std::is_same<T, double>::value ? (const T *)op->d_chi64 : (const T *)op->d_chi32;
+        g.part = (T *)part;
+        ncb = (ns + 15) / 16;
+        nitems = op->natoms * ncb * kGatherSplit;
+        const int per = nt / 256;
+        ngb = (nitems + per - 1) / per;
+        if ((long long)a.nblocks + ngb > 0x7fffffffLL) return fail(SPARC_E_SHAPE, "too many workgroups for one launch");
     }
     ProfScope prof(prev ? 0 : 3, stream);
     const int natoms = std::max(op->natoms, 1);

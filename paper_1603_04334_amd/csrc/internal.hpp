@@ -100,6 +100,7 @@ struct sparc_op {
     int tune_ns[2] = {-1, -1};  // block width the launch choice was tuned for; -1: every width
     int tune_group[2] = {0, 0};  // column group of the vector step (0 = library choice)
     int tune_cblk[2] = {0, 0};   // columns per workgroup of the vector step (0 = library choice)
+    int tune_ty[2] = {0, 0};     // patch rows set by sparc_op_set_launch (0 = none)
     // nonlocal-force tables, built on the first sparc_nonlocal_force call
     // (force.hip): per atom the boxes its functions live on, their units and
     // function values (FP64), and gamma per projector
@@ -170,6 +171,8 @@ constexpr int kMaxChunks = 16;  // most x-chunks of a vector step launch
 
 // is plan a patch height offered for dtype
 bool vec_plan_valid(int dtype, int plan);
+// can the row-pair kernels step patches of tz x ty on the op's grid
+bool rstep_patch(const sparc_op *op, int dtype, int tz, int ty);
 int vec_max_cblk(int dtype, int plan);  // columns per workgroup the plan's patch can hold (1 or 2)
 // rows and columns of whole 16-byte units (what the kernels of fstep.hip need)
 bool vec_grid(const sparc_op *op, int dtype, std::initializer_list<int64_t> lds);

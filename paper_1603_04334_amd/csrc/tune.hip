@@ -76,6 +76,25 @@ void fill_scratch(int dtype, void *p, size_t bytes, unsigned salt, hipStream_t s
         hipLaunchKernelGGL(fill_hash<float>, dim3(4096), dim3(256), 0, s, (float *)p, (long long)(bytes / 4), salt);
 }
 
+// the op's launch override of one dtype
+struct Override {
+    int shape, chunk, ns, group, cblk, ty;
+};
+Override get_override(const sparc_op *op, int d)
+{
+    return {op->tune_shape[d], op->tune_chunk[d], op->tune_ns[d], op->tune_group[d], op->tune_cblk[d], op->tune_ty[d]};
+}
+void set_override(sparc_op *op, int d, const Override &o)
+{
+    op->tune_shape[d] = o.shape;
+    op->tune_chunk[d] = o.chunk;
+    op->tune_ns[d] = o.ns;
+    op->tune_group[d] = o.group;
+    op->tune_cblk[d] = o.cblk;
+    op->tune_ty[d] = o.ty;
+}
+Override choice_override(const Choice &c, int ns) { return {c.plan, c.chunk, ns, c.group, c.cblk, 0}; }
+
 }  // namespace
 }  // namespace sparc
 
@@ -90,6 +109,7 @@ extern "C" int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *str
         return fail(SPARC_E_SHAPE, "the vector step kernels cannot take this grid (nothing to tune)");
     const Key key(op->n[0], op->n[1], op->n[2], op->natoms, op->nproj_total, ns, dtype);
     Choice best{-1, 0, 1, 1, 1e30};
+    const Override saved = get_override(op, dtype);
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         load_cache();
@@ -99,9 +119,6 @@ extern "C" int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *str
     if (best.plan < 0) {
         const size_t es = elem_size(dtype);
         const size_t blk = (size_t)op->nd * ns * es;
-        const int saved_shape = op->tune_shape[dtype], saved_chunk = op->tune_chunk[dtype];
-        const int saved_ns = op->tune_ns[dtype], saved_group = op->tune_group[dtype];
-        const int saved_cblk = op->tune_cblk[dtype];
         const int n1 = op->n[0];
         const int chunks[] = {0, n1, (n1 + 1) / 2, (n1 + 3) / 4, (n1 + 7) / 8};
         const size_t pb = std::max<size_t>(gather_bytes(op, dtype, ns), 256);
@@ -114,9 +131,7 @@ extern "C" int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *str
             (void)hipFree(G);
             return fail(SPARC_E_NOMEM, "autotune scratch allocation failed");
         }
-        op->tune_shape[dtype] = -1;
-        op->tune_chunk[dtype] = op->tune_group[dtype] = op->tune_cblk[dtype] = 0;
-        op->tune_ns[dtype] = ns;
+        set_override(op, dtype, {-1, 0, ns, 0, 0, 0});
         fill_scratch(dtype, X, blk, 0x9e3779b9u, s);
         fill_scratch(dtype, Pv, blk, 0x7f4a7c15u, s);
         (void)hipMemsetAsync(G, 0, pb, s);
@@ -138,10 +153,7 @@ extern "C" int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *str
                 for (int gi = 0; gi < 4 && st == SPARC_OK; ++gi) {
                     if (groups[gi] * cb > ns && gi > 0) continue;
                     if (cb == 2 && (ns < 2 || p == kRowPair || vec_max_cblk(dtype, p) < 2)) continue;
-                    op->tune_shape[dtype] = p;
-                    op->tune_chunk[dtype] = chunks[ci];
-                    op->tune_group[dtype] = groups[gi];
-                    op->tune_cblk[dtype] = cb;
+                    set_override(op, dtype, {p, chunks[ci], ns, groups[gi], cb, 0});
                     const FLaunch L = choose_vec_launch(op, dtype, ns, {});
                     if (L.plan != p) continue;
                     // a filter step as the filter runs it: the step with the
@@ -161,11 +173,7 @@ extern "C" int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *str
                 }
             }
         }
-        op->tune_shape[dtype] = saved_shape;
-        op->tune_chunk[dtype] = saved_chunk;
-        op->tune_ns[dtype] = saved_ns;
-        op->tune_group[dtype] = saved_group;
-        op->tune_cblk[dtype] = saved_cblk;
+        set_override(op, dtype, saved);
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         (void)hipFree(X);
@@ -178,14 +186,10 @@ extern "C" int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *str
         g_tune[key] = best;
         store_cache(key, best);
     }
-    op->tune_shape[dtype] = best.plan;
-    op->tune_chunk[dtype] = best.chunk;
-    op->tune_group[dtype] = best.group;
-    op->tune_cblk[dtype] = best.cblk;
-    op->tune_ns[dtype] = ns;  // the choice holds for this block width only
+    set_override(op, dtype, choice_override(best, ns));  // the choice holds for this block width only
     const FLaunch L = choose_vec_launch(op, dtype, ns, {});
-    if (tile_z) *tile_z = L.plan == kRowPair ? L.tz : kPlanTZ[best.plan];
-    if (tile_y) *tile_y = L.plan == kRowPair ? L.ty : kPlanTY[best.plan];
+    if (tile_z) *tile_z = L.plan == kRowPair ? L.tz : kPlanTZ[L.plan];
+    if (tile_y) *tile_y = L.plan == kRowPair ? L.ty : kPlanTY[L.plan];
     if (chunk_x) *chunk_x = best.chunk;
     if (col_group) *col_group = best.group;
     if (col_block) *col_block = best.cblk;
