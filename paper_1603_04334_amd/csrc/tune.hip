@@ -39,7 +39,7 @@ void load_cache()
     double us;
     while (std::fscanf(f, "%d %d %d %d %d %d %d %d %d %d %d %lf", &n1, &n2, &n3, &na, &np, &ns, &dt, &pl, &ch, &gr, &cb,
                        &us) == 12)
-        if (pl >= 0 && pl <= kRowPair && ch > 0 && gr > 0 && (cb == 1 || cb == 2))
+        if (ns > 0 && (pl == kRowPair || vec_plan_valid(dt, pl)) && ch > 0 && gr > 0 && (cb == 1 || cb == 2))
             g_tune[Key(n1, n2, n3, na, np, ns, dt)] = {pl, ch, gr, cb, us};
     std::fclose(f);
 }
@@ -115,6 +115,13 @@ extern "C" int sparc_autotune(sparc_op *op, int32_t dtype, int32_t ns, void *str
         load_cache();
         auto it = g_tune.find(key);
         if (it != g_tune.end()) best = it->second;
+    }
+    if (best.plan >= 0) {
+        // an entry that the grid does not take is measured anew
+        set_override(op, dtype, choice_override(best, ns));
+        const bool taken = choose_vec_launch(op, dtype, ns, {}).plan == best.plan;
+        set_override(op, dtype, saved);
+        if (!taken) best = {-1, 0, 1, 1, 1e30};
     }
     if (best.plan < 0) {
         const size_t es = elem_size(dtype);

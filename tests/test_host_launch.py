@@ -1,11 +1,18 @@
 """Launch choices of the step kernels: what sparc_step_config reports can be
-set again with sparc_op_set_launch."""
+set again with sparc_op_set_launch, and entries of a tuning file that a grid
+does not take are measured anew."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import pytest
 
-import host_library
-from paper_1603_04334_amd import binding
+HERE = os.path.dirname(os.path.abspath(__file__))
+sys.path[:0] = [os.path.dirname(HERE), HERE]
+
+import host_library  # noqa: E402
+from paper_1603_04334_amd import binding  # noqa: E402
 
 pytestmark = pytest.mark.skipif(not host_library.available(), reason="needs hipcc")
 
@@ -43,3 +50,37 @@ def test_row_pair_patch_needs_a_whole_unit():
     assert st == 0
     assert L.sparc_op_set_launch(op, binding.SPARC_F32, 4, 40, 0, 0, 0) == binding.SPARC_E_ARG
     L.sparc_op_destroy(op)
+
+
+def _child():
+    L = host_library.load()
+    for n in ((8, 8, 8), (24, 24, 24)):
+        st, op = host_library.create(host_library.cluster(n, [((2, 2, 2), (3, 3, 3))]))
+        assert st == 0
+        v = [ctypes.c_int32() for _ in range(5)]
+        us = ctypes.c_double()
+        for dtype in (binding.SPARC_F32, binding.SPARC_F64):
+            assert L.sparc_autotune(op, dtype, 8, None, *[ctypes.byref(x) for x in v], ctypes.byref(us)) == 0
+            got = tuple(x.value for x in v)
+            assert got[:2] in [(32, 8), (32, 16), (32, 32), (32, 64), (64, 8), (64, 16), (64, 24), (64, 32), (80, 32),
+                               (160, 24)], got
+            assert us.value != 1.0  # not the file's entry
+            assert _config(L, op, dtype, 8)[:2] == got[:2]
+        L.sparc_op_destroy(op)
+    print("child ok", flush=True)
+
+
+def test_entries_the_grid_does_not_take(tmp_path):
+    host_library.load()
+    # n1 n2 n3 natoms nproj ns dtype plan chunk group block microseconds: the
+    # row-pair kernels on grids too small for them, and a patch of the other type
+    f = tmp_path / "tune.txt"
+    f.write_text("8 8 8 1 2 8 1 10 8 1 1 1.0\n8 8 8 1 2 8 0 10 8 1 1 1.0\n24 24 24 1 2 8 1 0 8 1 1 1.0\n"
+                 "24 24 24 1 2 8 0 7 8 1 1 1.0\n")
+    env = dict(os.environ, SPARC_TUNE_CACHE=str(f))
+    r = subprocess.run([sys.executable, os.path.abspath(__file__)], capture_output=True, text=True, timeout=120, env=env)
+    assert r.returncode == 0 and "child ok" in r.stdout, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    _child()
