@@ -125,7 +125,11 @@ static int launch_gather_t(const sparc_op *op, const void *Y, int64_t ldy, int n
     ProfScope prof(1, stream);
     if constexpr (sizeof(TI) == 4) {
         if (nparts == 1) {
-            hipLaunchKernelGGL((gather_whole_kernel<T, TI>), dim3(ncb, op->natoms), dim3(256), 0, stream, a);
+            for (int J = 0; J < op->natoms; J += 65535) {  // rows of a grid
+                a.atoms = op->d_atoms + J;
+                hipLaunchKernelGGL((gather_whole_kernel<T, TI>), dim3(ncb, std::min(op->natoms - J, 65535)), dim3(256), 0,
+                                   stream, a);
+            }
             SPARC_HIP(hipGetLastError());
             return SPARC_OK;
         }

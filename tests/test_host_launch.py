@@ -6,6 +6,7 @@ import os
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -49,6 +50,29 @@ def test_row_pair_patch_needs_a_whole_unit():
     st, op = host_library.create(host_library.cluster((40, 40, 3), []))
     assert st == 0
     assert L.sparc_op_set_launch(op, binding.SPARC_F32, 4, 40, 0, 0, 0) == binding.SPARC_E_ARG
+    L.sparc_op_destroy(op)
+
+
+def test_grids_stay_within_the_limits():
+    """More atoms than a launch has rows (65535): every kernel of H, in both types."""
+    L = host_library.load()
+    n = 42
+    boxes = [((i // n // n, i // n % n, i % n), (1, 1, 1)) for i in range(65536 + 100)]
+    st, op = host_library.create(host_library.cluster((n, n, n), boxes, nproj=1))
+    assert st == 0
+    ns = 3
+    for dtype in (binding.SPARC_F64, binding.SPARC_F32):
+        x, y = np.zeros((ns, n ** 3)), np.zeros((ns, n ** 3))
+        ws = np.zeros(L.sparc_workspace_bytes(op, dtype, ns, 0), dtype=np.uint8)
+        L.stub_reset()
+        assert L.sparc_h_apply(op, dtype, x.ctypes.data, n ** 3, y.ctypes.data, n ** 3, ns, ws.ctypes.data, ws.nbytes,
+                               None) == 0
+        rr = np.zeros(L.sparc_rr_workspace_bytes(op, dtype, ns), dtype=np.uint8)
+        theta = np.zeros(ns)
+        assert L.sparc_rayleigh_ritz(op, dtype, x.ctypes.data, n ** 3, ns, theta.ctypes.data_as(binding._dp), None,
+                                     rr.ctypes.data, rr.nbytes, None) == 0
+        launches = host_library.calls("hipLaunchKernel")
+        assert launches and all(c["grid"][1] <= 65535 and c["grid"][2] <= 65535 for _, c in launches)
     L.sparc_op_destroy(op)
 
 
