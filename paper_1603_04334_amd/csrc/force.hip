@@ -107,6 +107,11 @@ int build_force_tables(const sparc_op *op)
             };
             if (k == 0) {
                 part(2, A.lo[2] - R, A.lo[2] + A.ext[2] + R);
+                const Part &P = parts[3 * J].back();
+                for (size_t t = 0; t < P.at.size(); ++t) {
+                    const int z = P.lo[2] + (int)(t % P.ext[2]) - A.lo[2];
+                    if (z < 0 || z >= A.ext[2]) units[2 * (B.unit0 + P.at[t] / 4) + 1] |= 16 << P.at[t] % 4;
+                }
             } else {
                 const int d = k - 1;
                 part(d, A.lo[d] - R, A.lo[d]);
@@ -180,27 +185,24 @@ int build_force_tables(const sparc_op *op)
 
 // acc[s][t] += contraction of orbital block s (16 columns) with functions 16 t
 // .. 16 t + 15 of the box, over this wave's share of its units (groups of 4
-// units dealt round-robin to all the waves; lane (i, k) as in gather_accum)
-template <typename TI, int NT, int NS>
-__device__ __forceinline__ void force_accum(const ForceBox &B, const int2 *__restrict__ units,
-                                            const double *__restrict__ fun, const TI *const (&y)[NS],
-                                            const bool (&ok)[NS], bool small, int waves, int wave, int lane,
-                                            double (&acc)[NS][NT][4])
+// units dealt round-robin to all the waves; lane (i, k) as in gather_accum).
+// ROWS: the box of widened rows.  Bits 4 to 7 of a unit's mask are then its
+// nodes on the arms, where only F_z (functions fz and up) is not zero by
+// definition.  A value there that is not finite must not reach the others
+// through a product with their zeros: FAST passes watch for values that are not
+// finite (returned), a pass that met one is done again without FAST.
+template <typename TI, int NT, int NS, bool ROWS, bool FAST>
+__device__ __forceinline__ bool force_pass(const ForceBox &B, const int2 *__restrict__ un,
+                                           const double *__restrict__ const (&f)[NT], const TI *const (&y)[NS],
+                                           const bool (&ok)[NS], bool small, int step, int wave, int lane,
+                                           double (&acc)[NS][NT][4])
 {
     typedef TI VY __attribute__((ext_vector_type(kUnit), aligned(sizeof(TI))));
     typedef double VC __attribute__((ext_vector_type(kUnit)));
-    const int i = lane & 15, k = lane >> 4;
-    const int2 *un = units + B.unit0;
-    const double *f[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int j = 16 * t + i;
-        f[t] = fun + B.fun0 + (long long)(j < B.nf ? j : 0) * B.nunits * kUnit;
-    }
-    const int nu = B.nunits, step = 4 * waves;
-    if (nu == 0) return;  // an arm cut off by the walls
+    const int k = lane >> 4, nu = B.nunits;
     int u = 4 * wave + k;
     int2 qn = un[u < nu ? u : 0];
+    TI watch = TI(0);
 #pragma unroll 1
     for (int u0 = 4 * wave; u0 < nu; u0 += step) {
         const int2 q = qn;
@@ -224,14 +226,65 @@ __device__ __forceinline__ void force_accum(const ForceBox &B, const int2 *__res
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int mask = in && ok[s] ? q.y : 0;
+            if (ROWS && FAST) watch += TI(0) * ((yv[s][0] + yv[s][1]) + (yv[s][2] + yv[s][3]));
 #pragma unroll
             for (int j = 0; j < kUnit; ++j) {
-                const double v = (mask >> j) & 1 ? (double)yv[s][j] : 0.0;
+                double v = (mask >> j) & 1 ? (double)yv[s][j] : 0.0;
+                if (ROWS && !FAST && (mask >> (4 + j) & 1) && !__builtin_isfinite(v)) v = 0.0;
 #pragma unroll
                 for (int t = 0; t < NT; ++t) mfma_16x16x4(v, cv[t][j], acc[s][t]);
             }
         }
     }
+    return watch != TI(0);  // 0 times a sum that is not finite is NaN
+}
+
+template <typename TI, int NT, int NS, bool ROWS>
+__device__ __forceinline__ void force_accum(const ForceBox &B, const int2 *__restrict__ units,
+                                            const double *__restrict__ fun, const TI *const (&y)[NS],
+                                            const bool (&ok)[NS], bool small, int waves, int wave, int lane, int fz,
+                                            double (&acc)[NS][NT][4])
+{
+    const int i = lane & 15, k = lane >> 4;
+    const int2 *un = units + B.unit0;
+    const double *f[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int j = 16 * t + i;
+        f[t] = fun + B.fun0 + (long long)(j < B.nf ? j : 0) * B.nunits * kUnit;
+    }
+    const int nu = B.nunits, step = 4 * waves;
+    if (nu == 0) return;  // an arm cut off by the walls
+    const bool odd = force_pass<TI, NT, NS, ROWS, true>(B, un, f, y, ok, small, step, wave, lane, acc);
+    if (!ROWS || !__any(odd)) return;
+    // again without the arms' values that are not finite
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[s][t][r] = 0.0;
+    (void)force_pass<TI, NT, NS, ROWS, false>(B, un, f, y, ok, small, step, wave, lane, acc);
+    // then those values for F_z alone, one tile of sums at a time (few registers)
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            double z[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+            for (int u0 = 4 * wave; u0 < nu; u0 += step) {
+                const int e = u0 + k, ec = e < nu ? e : 0;
+                const int2 q = un[ec];
+                const int arm = e < nu && ok[s] ? q.y >> 4 : 0;
+#pragma unroll 1
+                for (int j = 0; j < kUnit; ++j) {
+                    const double v = arm >> j & 1 ? (double)y[s][q.x + j] : 0.0;
+                    mfma_16x16x4(__builtin_isfinite(v) ? 0.0 : v, f[t][(long long)kUnit * ec + j], z);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[s][t][r] += 16 * t + i >= fz ? z[r] : 0.0;
+        }
 }
 
 // S_rp(n) below is the contraction of orbital n with function r of projector p.
@@ -282,9 +335,11 @@ __global__ void __launch_bounds__(64 * NW)
         const int box = wave < NB ? 0 : 1 + (wave - NB) / NA, w = box ? wave % NA : wave, parts = gridDim.z;
         double acc[NS][NT][4] = {}, arm[NS][1][4] = {};
         if (box == 0)
-            force_accum<TI, NT, NS>(F.box[0], units, fun, y, ok, small != 0, NB * parts, NB * blockIdx.z + w, lane, acc);
+            force_accum<TI, NT, NS, true>(F.box[0], units, fun, y, ok, small != 0, NB * parts, NB * blockIdx.z + w, lane,
+                                          3 * np, acc);
         else
-            force_accum<TI, 1, NS>(F.box[box], units, fun, y, ok, small != 0, NA * parts, NA * blockIdx.z + w, lane, arm);
+            force_accum<TI, 1, NS, false>(F.box[box], units, fun, y, ok, small != 0, NA * parts, NA * blockIdx.z + w, lane,
+                                          0, arm);
         for (int r = 0; r < NA; ++r) {
             if (box == 0 && w / 2 == r) put(S[w & 1], acc, 16 * NT, r == 0);
             if (box != 0 && w == r) put(S[1 + box] + box * np, arm, np, r == 0);
@@ -300,7 +355,7 @@ __global__ void __launch_bounds__(64 * NW)
     }
     {
         double acc[NS][NT][4] = {};
-        force_accum<TI, NT, NS>(F.box[0], units, fun, y, ok, small != 0, NW, wave, lane, acc);
+        force_accum<TI, NT, NS, true>(F.box[0], units, fun, y, ok, small != 0, NW, wave, lane, 3 * np, acc);
         for (int w = 0; w < NW; ++w) {
             if (wave == w) put(S[0], acc, 16 * NT, w == 0);
             __syncthreads();
@@ -309,7 +364,7 @@ __global__ void __launch_bounds__(64 * NW)
 #pragma unroll 1
     for (int k = 1; k < 3; ++k) {
         double acc[NS][1][4] = {};
-        force_accum<TI, 1, NS>(F.box[k], units, fun, y, ok, small != 0, NW, wave, lane, acc);
+        force_accum<TI, 1, NS, false>(F.box[k], units, fun, y, ok, small != 0, NW, wave, lane, 0, acc);
         for (int w = 0; w < NW; ++w) {
             if (wave == w) put(S[0] + k * np, acc, np, false);
             __syncthreads();
