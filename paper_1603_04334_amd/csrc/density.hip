@@ -141,7 +141,7 @@ __device__ __forceinline__ void den_add(double (&acc)[N], const V &x, double g)
 // NT: blocks the last-level cache cannot hold are read non-temporally.
 // Measured (blocks not in cache): 127 x 119 x 131 x 256 FP32 546 us by scalar
 // loads, 463 us by unaligned ones, 364 to 388 us now (5.6 TB/s); 99 x 101 x 103
-// x 128 FP64 193 -> 184 us; aligned 160^3 x 600 FP32 1.82 -> 1.68 ms (5.9 TB/s).
+// x 128 FP64 193 -> 173 us (by units shifted like the FP32 ones 184); aligned 160^3 x 600 FP32 1.82 -> 1.68 ms (5.9 TB/s).
 template <typename T, bool NT, bool SHIFT>
 __global__ void __launch_bounds__(512)
     density_kernel(const T *__restrict__ psi, long long ld, long long nd, int ns, const double *__restrict__ occ,
@@ -233,34 +233,92 @@ __global__ void __launch_bounds__(512)
     }
 }
 
+// FP64 columns off the 16-byte grid: a lane owns the points l and l + 64 of its
+// wave's 128, so that its 8-byte loads are whole lines of the wave wherever a
+// column starts.  U columns in flight; WHOLE: groups of U columns first (few
+// waves need all their loads at once, 45 x 47 x 43 x 100 13.3 us, without 32;
+// blocks from memory are faster without, 127 x 119 x 131 x 256 597 us, 697).
+template <bool NT, bool WHOLE, int U>
+__global__ void __launch_bounds__(512)
+    density_split_kernel(const double *__restrict__ psi, long long ld, long long nd, int ns,
+                         const double *__restrict__ occ, double scale, double *__restrict__ rho)
+{
+    const long long wave = (long long)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
+    const long long i0 = wave * 128 + (threadIdx.x & 63), i1 = i0 + 64;
+    if (i0 >= nd) return;
+    const double *c0 = psi + i0, *c1 = psi + (i1 < nd ? i1 : i0);
+    double acc[2] = {0.0, 0.0};
+    typedef double V __attribute__((ext_vector_type(2)));
+    int n0 = 0;
+    if (WHOLE)
+        for (; n0 + U <= ns; n0 += U) {
+            V x[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) x[j] = V{c0[(long long)(n0 + j) * ld], c1[(long long)(n0 + j) * ld]};
+#pragma unroll
+            for (int j = 0; j < U; ++j) den_add<2>(acc, x[j], occ[n0 + j]);
+        }
+    for (; n0 < ns; n0 += U) {
+        V x[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const long long o = (long long)min(n0 + j, ns - 1) * ld;
+            x[j][0] = NT ? __builtin_nontemporal_load(c0 + o) : c0[o];
+            x[j][1] = NT ? __builtin_nontemporal_load(c1 + o) : c1[o];
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            if (n0 + j >= ns) break;
+            den_add<2>(acc, x[j], occ[n0 + j]);
+        }
+    }
+    rho[i0] = scale * acc[0];
+    if (i1 < nd) rho[i1] = scale * acc[1];
+}
+
 template <typename T>
 int launch_density(const T *psi, long long ld, long long nd, int ns, const double *occ, double scale, double *rho,
                    hipStream_t s)
 {
     constexpr int N = DenVec<T>::N;
-    // Columns off the 16-byte grid are read as aligned units shifted across the
-    // lanes, except a few FP64 columns that fit the last-level cache: the plain
-    // 16-byte loads at 8-byte places then cost less than the shifts (95 x 97 x 91
-    // x 4: 7.0 us, shifted 8.6; x 40 46.8 against 46.5).
+    // Columns off the 16-byte grid: FP32 as aligned units shifted across the lanes,
+    // FP64 point by point (density_split_kernel).
     const bool nt_loads = (double)nd * ns * sizeof(T) > kStreamBytes;
-    const bool aligned = (ld % N == 0 && (uintptr_t)psi % 16 == 0) || (sizeof(T) == 8 && ns <= 16 && !nt_loads);
-    const long long per = (aligned ? 64LL : 63LL) * N;  // points per wave
+    const bool aligned = ld % N == 0 && (uintptr_t)psi % 16 == 0;
+    const bool split = sizeof(T) == 8 && !aligned;
+    const long long per = (aligned || split ? 64LL : 63LL) * N;  // points per wave
     const long long waves = (nd + per - 1) / per;
     // workgroups of 8 waves; small grids spread over more CUs by waves of their own
-    const int nt = waves >= 4096 ? 512 : 64;
+    const int nt = waves >= 4096 ? 512 : split ? 256 : 64;
     const long long blocks = (waves * 64 + nt - 1) / nt;
     if (blocks > 0x7fffffffLL) return fail(SPARC_E_SHAPE, "grid too large for one density launch");
     ProfScope prof(4, s);
 #define SPARC_DEN(A, B)                                                                                            \
     hipLaunchKernelGGL((density_kernel<T, A, B>), dim3((unsigned)blocks), dim3(nt), 0, s, psi, ld, nd, ns, occ, scale, rho)
-    if (aligned && nt_loads)
+    if (aligned && nt_loads) {
         SPARC_DEN(true, false);
-    else if (aligned)
+    } else if (aligned) {
         SPARC_DEN(false, false);
-    else if (nt_loads)
-        SPARC_DEN(true, true);
-    else
-        SPARC_DEN(false, true);
+    } else if constexpr (sizeof(T) == 4) {
+        if (nt_loads)
+            SPARC_DEN(true, true);
+        else
+            SPARC_DEN(false, true);
+    } else {
+        // in the last-level cache a full chip needs few loads per lane: 95 x 97 x
+        // 91 x 40 columns 42.6 us by two, 44.5 by eight; 45 x 47 x 43 x 100 19.7
+        // and 13.3; from memory 127 x 119 x 131 x 20 57.9 and 51.6
+#define SPARC_DEN_SPLIT(A, W, U)                                                                                  \
+    hipLaunchKernelGGL((density_split_kernel<A, W, U>), dim3((unsigned)blocks), dim3(nt), 0, s, psi, ld, nd, ns, occ, \
+                       scale, rho)
+        if (nt_loads)
+            SPARC_DEN_SPLIT(true, false, 8);
+        else if (waves >= 4096)
+            SPARC_DEN_SPLIT(false, false, 2);
+        else
+            SPARC_DEN_SPLIT(false, true, 8);
+#undef SPARC_DEN_SPLIT
+    }
 #undef SPARC_DEN
     SPARC_HIP(hipGetLastError());
     return SPARC_OK;
