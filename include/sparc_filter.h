@@ -307,7 +307,7 @@ size_t sparc_poisson_workspace_bytes(const sparc_poisson *p);
  * rel_resid: host outputs (may be NULL); moments: NULL or a host array of
  * (lmax+1)^2 values receiving Q_lm (index l*l + l + m).  All sums FP64 in a
  * fixed order (reproducible bit for bit).  Synchronous on stream (it reads a
- * convergence flag every 24 iterations).  Errors: SPARC_E_ARG (tol <= 0,
+ * convergence flag every 24 iterations, with a guess also after 12).  Errors: SPARC_E_ARG (tol <= 0,
  * max_iter < 0), SPARC_E_WORKSPACE, SPARC_E_ALIAS, SPARC_E_SHAPE, SPARC_E_HIP. */
 int sparc_poisson_solve(sparc_poisson *p, const double *charge, double *phi, int32_t use_guess, double tol,
                         int32_t max_iter, int32_t *iters, double *rel_resid, double *moments, void *ws,

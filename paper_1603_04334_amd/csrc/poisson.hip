@@ -47,9 +47,12 @@ constexpr int kBjStage = 64;                       // largest block (nodes) whos
 constexpr int kRedMax = 1024;                      // workgroups of the reduction kernels
 // CG iterations enqueued between convergence reads.  A read leaves the chip idle
 // for about 30 us, an iteration after the converged one costs three empty
-// launches.  8, 16, 24, 32: 24^3 1.68, 1.62, 1.43, 1.72 ms; 96^3 7.56, 7.06, 6.90,
-// 6.90 ms; 160^3 30.8, 29.9, 29.6, 29.5 ms.
+// launches.  From zero 24 (8, 16, 24, 32: 24^3 1.68, 1.62, 1.43, 1.72 ms; 96^3
+// 7.56, 7.06, 6.90, 6.90 ms; 160^3 30.8, 29.9, 29.6, 29.5 ms; a small grid's time
+// also depends on where its last iteration falls in a chunk).  A solve from a good
+// guess may need few: twice half a chunk first.
 constexpr int kChunk = 24;
+inline int chunk_from(int it, bool guess) { return guess && it < kChunk ? kChunk / 2 : kChunk; }
 constexpr double kFourPi = 12.566370614359172954;  // 4 pi
 
 struct HarmNorm {
@@ -1071,7 +1074,7 @@ extern "C" int sparc_poisson_solve(sparc_poisson *P, const double *charge, doubl
     SPARC_HIP(hipStreamSynchronize(s));
     int it = 0;
     while (hs.done == kNotDone && it < max_iter) {
-        const int chunk = std::min(kChunk, max_iter - it);
+        const int chunk = std::min(chunk_from(it, use_guess != 0), max_iter - it);
         for (int c = 0; c < chunk; ++c, ++it) {
             if (P->npq > 0) {
                 if ((st = launch_vstep(P->op0, W.p, W.q, cA.alpha, false, W.pq, &W.state->done, it, s))) return st;
