@@ -225,16 +225,16 @@ int launch_gather_f32_to_f64(const sparc_op *op, const float *Y, int64_t ldy, in
 int launch_step_f32_to_f64(const sparc_op *op, const float *yk, int64_t ldk, double *out, int64_t ldo, int ns,
                            const StepCoef &c, const StepLaunch &L, hipStream_t stream);
 
-// out = alpha (-1/2 lap_h + V_eff (pot only)) v for one FP64 vector of N_d
-// values, dot[b] = sum over workgroup b's nodes of v(x) out(x), b <
-// vstep_blocks(op); skipped on the device when done is given and *done < iter.
-// vstep_takes: the grid has rows of at least two nodes and a bounded number of
-// workgroups.
+// out = alpha (-1/2 lap_h) v for one FP64 vector of N_d values, dot[b] = sum over
+// workgroup b's nodes of v(x) out(x), b < vstep_blocks(op); skipped on the device
+// when *done < iter.  launch_vstep_gather: out = H_loc v, alike, with the
+// projector gather of v into part (as launch_gather with ns = 1).  vstep_takes:
+// the grid has rows of at least two nodes and a bounded number of workgroups.
 bool vstep_takes(const sparc_op *op);
 long long vstep_blocks(const sparc_op *op);
 int launch_vstep_gather(const sparc_op *op, const double *v, double *out, double *dot, double *part, hipStream_t stream);
-int launch_vstep(const sparc_op *op, const double *v, double *out, double alpha, bool pot, double *dot, const int *done,
-                 int iter, hipStream_t stream);
+int launch_vstep(const sparc_op *op, const double *v, double *out, double alpha, double *dot, const int *done, int iter,
+                 hipStream_t stream);
 
 // One launch for one FP64 vector v (N_d values, contiguous): out = H_loc v,
 // dot[b] = sum over workgroup b's points of v(x) (H_loc v)(x) for

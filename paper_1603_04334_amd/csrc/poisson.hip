@@ -1077,7 +1077,7 @@ extern "C" int sparc_poisson_solve(sparc_poisson *P, const double *charge, doubl
         const int chunk = std::min(chunk_from(it, use_guess != 0), max_iter - it);
         for (int c = 0; c < chunk; ++c, ++it) {
             if (P->npq > 0) {
-                if ((st = launch_vstep(P->op0, W.p, W.q, cA.alpha, false, W.pq, &W.state->done, it, s))) return st;
+                if ((st = launch_vstep(P->op0, W.p, W.q, cA.alpha, W.pq, &W.state->done, it, s))) return st;
             } else {
                 if ((st = launch_h_step(P->op0, SPARC_F64, W.p, nd, nullptr, 0, W.q, nd, 1, nullptr, cA, L, s, &V)))
                     return st;

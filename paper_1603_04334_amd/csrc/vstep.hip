@@ -58,14 +58,14 @@ __global__ void __launch_bounds__(kVThreads)
     store_partial(k.dacc, dot, b);
 }
 
-// done: the launch is skipped when *done < iter (null: never)
-template <bool POT, int RAG>
+// A p without a potential; skipped when *done < iter
+template <int RAG>
 __global__ void __launch_bounds__(kVThreads)
     vstep_kernel(const FStepArgs<double> a, double *dot, const int *done, int iter)
 {
-    using K = FStep<double, kVTY, false, false, 1, kVTZ, POT, true, RAG>;
+    using K = FStep<double, kVTY, false, false, 1, kVTZ, false, true, RAG>;
     __shared__ __align__(16) typename K::Shared sh;
-    if (done && *done < iter) return;
+    if (*done < iter) return;
     K k(a);
     k.run(blockIdx.x, sh);
     store_partial(k.dacc, dot, blockIdx.x);
@@ -143,20 +143,15 @@ int launch_vstep_gather(const sparc_op *op, const double *v, double *out, double
     return SPARC_OK;
 }
 
-int launch_vstep(const sparc_op *op, const double *v, double *out, double alpha, bool pot, double *dot, const int *done,
-                 int iter, hipStream_t stream)
+int launch_vstep(const sparc_op *op, const double *v, double *out, double alpha, double *dot, const int *done, int iter,
+                 hipStream_t stream)
 {
     const FStepArgs<double> a = vstep_args(op, v, out, alpha);
     const dim3 grid((unsigned)a.nblocks), blk(kVThreads);
-    const bool rag = op->n[2] & 1;
-    if (pot && rag)
-        hipLaunchKernelGGL((vstep_kernel<true, 1>), grid, blk, 0, stream, a, dot, done, iter);
-    else if (pot)
-        hipLaunchKernelGGL((vstep_kernel<true, 0>), grid, blk, 0, stream, a, dot, done, iter);
-    else if (rag)
-        hipLaunchKernelGGL((vstep_kernel<false, 1>), grid, blk, 0, stream, a, dot, done, iter);
+    if (op->n[2] & 1)
+        hipLaunchKernelGGL(vstep_kernel<1>, grid, blk, 0, stream, a, dot, done, iter);
     else
-        hipLaunchKernelGGL((vstep_kernel<false, 0>), grid, blk, 0, stream, a, dot, done, iter);
+        hipLaunchKernelGGL(vstep_kernel<0>, grid, blk, 0, stream, a, dot, done, iter);
     SPARC_HIP(hipGetLastError());
     return SPARC_OK;
 }
