@@ -99,10 +99,12 @@ int build_unit_chi(sparc_op *op, int64_t total)
 
 bool gather_wide(const sparc_op *op, int ns)
 {
-    // measured (FP32 filters): 128 atoms x 600 columns (4864 pairs) 1.3 %
-    // faster per step on its own than in the step's tail, 40 atoms x 128
-    // columns (320 pairs) 0.5 % slower
-    return (long long)op->natoms * ((ns + 15) / 16) >= 2048;
+    // FP32 filters, per step with a workgroup per pair against the step's tail:
+    // 64 pairs (96^3, 16 atoms x 64 columns) 168 and 148 us, 400 (40^3, 40 x 160)
+    // 99 and 94, 512 (64^3, 32 x 256) 239 and 237; 1024 (128^3, 64 x 256) 1402 and
+    // 1459, 1178 (120^3, 31 x 600) 2770 and 2862, 2048 (160^3, 128 x 256) 3127 and
+    // 3377, 4864 (160^3, 128 x 600) 7182 and 7306
+    return (long long)op->natoms * ((ns + 15) / 16) >= 1024;
 }
 
 template <typename T, typename TI = T>
