@@ -304,7 +304,7 @@ __global__ void __launch_bounds__(64 * NW)
     constexpr int G = SPLIT ? 4 : 1;
     __shared__ double S[G][16 * NT][NC];
     __shared__ double red[3][NW];
-        const int J = blockIdx.y, cb = blockIdx.x;
+    const int J = blockIdx.y, cb = blockIdx.x;
     const ForceAtom &F = atoms[J];
     const int c0 = cb * NC, np = F.nproj;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15;

@@ -16,9 +16,10 @@
 //    consecutive z nodes of one y row: 4 FP32 or 2 FP64 values, 16 bytes, so
 //    every global access is a 16-byte raw buffer load or store (a plain copy
 //    with 4-byte accesses per lane reaches about 60% of the bandwidth of
-//    16-byte accesses on this chip).  A lane keeps the 13 x-planes of its unit in registers, one vector
-//    per plane (x neighbours never touch LDS); the plane loop is unrolled over
-//    26 planes so the queue rotates by register renaming.
+//    16-byte accesses on this chip).  A lane keeps the 13 x-planes of its unit
+//    in registers, one vector per plane (x neighbours never touch LDS); the
+//    plane loop is unrolled over 26 planes so the queue rotates by register
+//    renaming.
 //  * The current plane of the patch plus its halo (6 rows in y; 8 FP32 / 6
 //    FP64 nodes in z, whole units) is staged in LDS, double-buffered with one
 //    barrier per plane; y and z neighbours are read there as 16-byte units.
@@ -138,7 +139,9 @@ static int rstep_threads(const sparc_op *op, int dtype, int tz, int ty, int &nh)
 // x-chunks 733, 666, 688 us; 75 x 83 x 91 x 64 in 2, 4, 5 chunks 95, 101, 113
 // us; 96^3 x 64 in 1, 4, 8 chunks 137, 138, 160 us.  Patches are as wide as the
 // grid row where it fits (no z halo): 160^3 x 600 24 x 160 5.81 ms, 24 x 80
-// 6.76 ms.
+// 6.76 ms.  The estimate knows nothing of the L2: 160^3 x 600 in 4 x-chunks and
+// groups of 4 columns takes 5.71 ms, its own choice (no x split, groups of 2)
+// 5.85 ms; the autotuner finds the former.
 // only_ty: the patch's rows, set by hand (0: chosen here).
 static void choose_rstep(const sparc_op *op, int dtype, int ns, FLaunch &L, int only_ty = 0)
 {
@@ -199,8 +202,9 @@ static void choose_rstep(const sparc_op *op, int dtype, int ns, FLaunch &L, int 
 // Whether the library's own choice is the row-pair kernels.  aligned: the
 // 16-byte-unit kernels of this file take the grid too.
 //  * FP32 from 4e6 values per block: 160^3 x 600 7.75 -> 6.84 ms per step
-//    launch, 128^3 x 128 827 -> 666 us, 96^3 x 64 178 -> 137 us, 64^3 x 64 49 ->
-//    44 us; below (32^3 x 64) 12 -> 15 us.
+//    launch with the projections in its tail (without, as it runs beside
+//    gather_whole_kernel, 5.85 ms), 128^3 x 128 827 -> 666 us, 96^3 x 64 178 ->
+//    137 us, 64^3 x 64 49 -> 44 us; below (32^3 x 64) 12 -> 15 us.
 //  * FP64, whose step is bound by memory already: only where the 16 x 32 patches
 //    of the other kernels reach 15 % past the grid (75 x 83 x 92 x 37 151 -> 131
 //    us; 96^3 x 64, no overhang, 300 -> 322 us).

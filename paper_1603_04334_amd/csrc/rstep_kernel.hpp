@@ -13,7 +13,8 @@
 // longer than a memory access.
 //
 // What bounds it now: at 160^3 x 600 FP32 the launch without projectors takes
-// 5.80 ms (6.96 ms before, 32 x 32 patches), 29.5 GB at 5.09 TB/s; a kernel that
+// 5.80 to 5.85 ms (6.96 ms before, 32 x 32 patches; 5.71 ms with x in 4 chunks
+// and groups of 4 columns), 29.5 GB at 5.09 TB/s; a kernel that
 // only walks the same three arrays in the same order of planes takes 5.78 ms
 // (a linear walk of them 4.61 ms), and leaving out V_eff, the halo and the LDS
 // reads together gains 4 %.  The order of the walk is what is left.
