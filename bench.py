@@ -572,11 +572,11 @@ def next_rows(case, cl, op, dtype):
             hi = min(cl.n[d], at.lo[d] + at.ext[d] + R)
             ee = list(e)
             ee[d] = hi - lo
-            pts += int(np.prod(ee))
+            pts += int(np.prod(ee)) - int(np.prod(e))
     byt = s * pts * ns
     out["nonlocal_force"] = {"ms": ms, "first_call_ms_with_tables": first, "orbital_bytes_read": byt,
                              "gbs": byt / (ms * 1e-3) / 1e9, "atoms": len(cl.atoms),
-                             "bytes": "s N_s per point of each atom's cube and its three widened gradient boxes"}
+                             "bytes": "s N_s per point of each atom's cube and its arms along the three axes, each once"}
     del fws, X, rho
     torch.cuda.empty_cache()
     # electrostatic potential of a neutral synthetic charge on the same grid
@@ -601,7 +601,7 @@ def next_rows(case, cl, op, dtype):
     _, it, res, _ = P.solve(charge, phi=phi, tol=1e-10, ws=pws)
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) * 1e3
-    per_it = 14 * 8 * nd  # matvec 2, p.q 2, x/r/z update 7, p update 3 vector passes
+    per_it = 11 * 8 * nd  # A p with p.q 2, block Jacobi with the r update 4, x and p update 5 vector passes
     out["poisson"] = {"grid": list(n), "tol": 1e-10, "iterations": it, "rel_resid": res, "ms": ms,
                       "ms_per_iteration": ms / max(it, 1), "bytes_per_iteration": per_it,
                       "gbs": per_it * it / (ms * 1e-3) / 1e9, "lmax": 6, "block": [4, 4, 4]}
