@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <initializer_list>
 #include <memory>
 #include <new>
 
@@ -39,8 +40,11 @@ int64_t g_prof_count[kProfKernels] = {};
 double g_prof_ms[kProfKernels] = {};
 }  // namespace
 
-TraceRange::TraceRange(const char *name) { roctxRangePushA(name); }
-TraceRange::~TraceRange() { roctxRangePop(); }
+TraceRange::TraceRange(const char *name) : pushed(quiet([&] { roctxRangePushA(name); })) {}
+TraceRange::~TraceRange()
+{
+    if (pushed) quiet([] { roctxRangePop(); });
+}
 
 ProfScope::ProfScope(int k, hipStream_t s) : kernel(k), stream(s)
 {
@@ -55,14 +59,16 @@ ProfScope::ProfScope(int k, hipStream_t s) : kernel(k), stream(s)
 ProfScope::~ProfScope()
 {
     if (!ev0) return;
-    hipEvent_t e;
-    if (hipEventCreate(&e) != hipSuccess) {
-        (void)hipEventDestroy((hipEvent_t)ev0);
-        return;
-    }
-    (void)hipEventRecord(e, stream);
-    std::lock_guard<std::mutex> lk(g_prof_mu);
-    g_prof_pending.push_back({kernel, (hipEvent_t)ev0, e});
+    quiet([&] {
+        hipEvent_t e;
+        if (hipEventCreate(&e) != hipSuccess) {
+            (void)hipEventDestroy((hipEvent_t)ev0);
+            return;
+        }
+        (void)hipEventRecord(e, stream);
+        std::lock_guard<std::mutex> lk(g_prof_mu);
+        g_prof_pending.push_back({kernel, (hipEvent_t)ev0, e});
+    });
 }
 
 // ---------------------------------------------------------------- weights
@@ -472,20 +478,10 @@ int sparc_op_create(const sparc_grid *grid, const double *veff, int32_t natoms, 
 int sparc_op_destroy(sparc_op *op)
 {
     if (!op) return SPARC_OK;
-    (void)hipFree(op->d_veff64);
-    (void)hipFree(op->d_veff32);
-    (void)hipFree(op->d_atoms);
-    (void)hipFree(op->d_chi64);
-    (void)hipFree(op->d_chi32);
-    (void)hipFree(op->d_hg64);
-    (void)hipFree(op->d_hg32);
-    (void)hipFree(op->d_tables);
-    (void)hipFree(op->d_chiu64);
-    (void)hipFree(op->d_chiu32);
-    (void)hipFree(op->d_fatoms);
-    (void)hipFree(op->d_funits);
-    (void)hipFree(op->d_ffun);
-    (void)hipFree(op->d_fgamma);
+    for (void *p : std::initializer_list<void *>{op->d_veff64, op->d_veff32, op->d_atoms, op->d_chi64, op->d_chi32,
+                                                 op->d_hg64, op->d_hg32, op->d_tables, op->d_chiu64, op->d_chiu32,
+                                                 op->d_fatoms, op->d_funits, op->d_ffun, op->d_fgamma})
+        quiet([&] { (void)hipFree(p); });
     delete op;
     return SPARC_OK;
 }

@@ -293,10 +293,24 @@ int chefsi_run(const sparc_op *op, int dtype, void *X, int64_t ldx, int ns, int 
                double &a0, double a, double b, const ChefsiBuffers &B, double *theta, double *lambda_f,
                int32_t *degrees, double *rho, hipStream_t s, int *halvings);
 
+// f(), and false where it threw: for destructors, clean-up and a worker's own
+// calls, where an exception out of a library would end the process
+template <typename F>
+bool quiet(F &&f) noexcept
+{
+    try {
+        f();
+        return true;
+    } catch (...) {
+        return false;
+    }
+}
+
 // roctx range over the host side of an entry point or a step of it, for
 // timelines that show the library's phases beside its kernels (rocprofv3
 // --marker-trace); without a tool that records markers it costs a call
 struct TraceRange {
+    bool pushed;
     explicit TraceRange(const char *name);
     ~TraceRange();
     TraceRange(const TraceRange &) = delete;

@@ -891,10 +891,12 @@ struct BlasLease {
     ~BlasLease()
     {
         if (!h || thrown) return;
-        (void)hipEventRecord(e.done, stream);
-        e.last = stream;
-        std::lock_guard<std::mutex> lk(g_blas_mu);
-        g_blas_free[dev].push_back(e);
+        quiet([&] {
+            (void)hipEventRecord(e.done, stream);
+            e.last = stream;
+            std::lock_guard<std::mutex> lk(g_blas_mu);
+            g_blas_free[dev].push_back(e);
+        });
     }
     BlasLease(const BlasLease &) = delete;
     BlasLease &operator=(const BlasLease &) = delete;

@@ -158,10 +158,10 @@ size_t estimate_footprint(const Cluster &c, int lanczos_k)
 void free_device(Cluster &c, hipStream_t s)
 {
     for (void **p : {&c.X, &c.Y, &c.ws, &c.rr, &c.evec, &c.rot, &c.lanczos}) {
-        if (*p) (void)hipFreeAsync(*p, s);
+        if (*p) quiet([&] { (void)hipFreeAsync(*p, s); });
         *p = nullptr;
     }
-    (void)hipStreamSynchronize(s);
+    quiet([&] { (void)hipStreamSynchronize(s); });
     sparc_op_destroy(c.op);
     c.op = nullptr;
     c.resident = false;
@@ -261,9 +261,11 @@ std::deque<Request>::iterator admissible(sparc_server *srv)
 
 void worker_main(sparc_server *srv)
 {
-    (void)hipSetDevice(srv->device);
+    // an exception here or below would leave the thread and end the process;
+    // without a stream of its own the worker runs on the null stream
     hipStream_t s = nullptr;
-    (void)hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    quiet([&] { (void)hipSetDevice(srv->device); });
+    quiet([&] { (void)hipStreamCreateWithFlags(&s, hipStreamNonBlocking); });
     for (;;) {
         std::unique_lock<std::mutex> lk(srv->mu);
         srv->cv.wait(lk, [&] { return srv->stop || admissible(srv) != srv->pending.end(); });
@@ -286,7 +288,7 @@ void worker_main(sparc_server *srv)
         res.t_start = now_s();
         res.status = execute_guarded(srv, c, r, s, res);
         if (res.status != SPARC_OK) {
-            (void)hipStreamSynchronize(s);
+            quiet([&] { (void)hipStreamSynchronize(s); });
             std::strncpy(res.error, sparc_last_error(), sizeof(res.error) - 1);
         }
         res.t_end = now_s();
@@ -333,7 +335,7 @@ void worker_main(sparc_server *srv)
         lk.unlock();
         srv->cv.notify_all();
     }
-    (void)hipStreamDestroy(s);
+    quiet([&] { (void)hipStreamDestroy(s); });
 }
 
 }  // namespace
@@ -490,13 +492,13 @@ int sparc_server_destroy(sparc_server *srv)
     srv->cv.notify_all();
     for (auto &t : srv->workers) t.join();
     hipStream_t s = nullptr;
-    (void)hipSetDevice(srv->device);
-    (void)hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    quiet([&] { (void)hipSetDevice(srv->device); });
+    quiet([&] { (void)hipStreamCreateWithFlags(&s, hipStreamNonBlocking); });
     for (auto &kv : srv->clusters) {
         free_device(*kv.second, s);
         delete kv.second;
     }
-    (void)hipStreamDestroy(s);
+    quiet([&] { (void)hipStreamDestroy(s); });
     delete srv;
     return SPARC_OK;
 }

@@ -39,6 +39,17 @@ struct Config {
 };
 thread_local Config t_config;
 
+// throws where stub_throw names `what`
+void raise_if(const char *what)
+{
+    {
+        std::lock_guard<std::mutex> lk(st().mu);
+        if (st().raise != what) return;
+    }
+    const std::variant<int, double> v(1);
+    (void)std::get<double>(v);
+}
+
 void note(const char *what, const char *fmt = "", ...)
 {
     char text[512];
@@ -46,16 +57,11 @@ void note(const char *what, const char *fmt = "", ...)
     va_start(ap, fmt);
     vsnprintf(text, sizeof(text), fmt, ap);
     va_end(ap);
-    bool raise = false;
     {
         std::lock_guard<std::mutex> lk(st().mu);
         st().log += std::string(what) + " " + text + "\n";
-        raise = st().raise == what;
     }
-    if (raise) {
-        const std::variant<int, double> v(1);
-        (void)std::get<double>(v);
-    }
+    raise_if(what);
 }
 
 template <typename P>
@@ -76,6 +82,7 @@ hipError_t copy(const char *what, void *dst, const void *src, size_t n, hipMemcp
 
 hipError_t allocate(const char *what, void **p, size_t n)
 {
+    raise_if(what);
     *p = std::calloc(1, n ? n : 1);
     note(what, "ptr=%p bytes=%zu", *p, n);
     return *p ? hipSuccess : hipErrorOutOfMemory;
@@ -182,6 +189,7 @@ hipError_t hipStreamSynchronize(hipStream_t s)
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned)
 {
+    raise_if("hipStreamCreateWithFlags");
     *s = handle<hipStream_t>();
     note("hipStreamCreateWithFlags", "stream=%p", (void *)*s);
     return hipSuccess;
@@ -226,8 +234,16 @@ hipError_t hipEventDestroy(hipEvent_t e)
     std::free(e);
     return hipSuccess;
 }
-hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t)
+{
+    note("hipEventQuery");
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t, hipStream_t)
+{
+    note("hipEventRecord");
+    return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t)
 {
@@ -239,7 +255,11 @@ hipError_t hipGetDevice(int *d)
     *d = 0;
     return hipSuccess;
 }
-hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipSetDevice(int)
+{
+    note("hipSetDevice");
+    return hipSuccess;
+}
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int)
 {
     *v = 256;
@@ -261,8 +281,16 @@ const char *hipGetErrorString(hipError_t) { return "hip error"; }
 
 // ---------------------------------------------------------------- libraries
 
-int roctxRangePushA(const char *) { return 0; }
-int roctxRangePop() { return 0; }
+int roctxRangePushA(const char *)
+{
+    note("roctxRangePushA");
+    return 0;
+}
+int roctxRangePop()
+{
+    note("roctxRangePop");
+    return 0;
+}
 rocblas_status rocblas_create_handle(rocblas_handle *h)
 {
     *h = handle<rocblas_handle>();
@@ -275,7 +303,11 @@ rocblas_status rocblas_destroy_handle(rocblas_handle h)
     std::free(h);
     return rocblas_status_success;
 }
-rocblas_status rocblas_set_stream(rocblas_handle, hipStream_t) { return rocblas_status_success; }
+rocblas_status rocblas_set_stream(rocblas_handle, hipStream_t)
+{
+    note("rocblas_set_stream");
+    return rocblas_status_success;
+}
 rocblas_status rocblas_set_atomics_mode(rocblas_handle, rocblas_atomics_mode) { return rocblas_status_success; }
 const char *rocblas_status_to_string(rocblas_status) { return "rocblas status"; }
 rocblas_status rocblas_dtrsm(rocblas_handle, rocblas_side, rocblas_fill, rocblas_operation, rocblas_diagonal,

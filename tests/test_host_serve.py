@@ -34,7 +34,7 @@ def _fill(dst, src, nbytes):
     ctypes.memmove(dst, v.ctypes.data, 8 * n)
 
 
-def _child(where):
+def _child(where, anywhere=False):
     L = host_library.load()
     L.stub_d2h(_fill)
     cfg = binding.sparc_server_cfg(0, 2, 40, 0, 0.0)
@@ -62,6 +62,23 @@ def _child(where):
             time.sleep(0.001)
         return r
 
+    if anywhere:
+        # the call throws from here until the request and its clean-up are done
+        L.stub_throw(where.encode())
+        srv = ctypes.c_void_p()
+        assert L.sparc_server_create(ctypes.byref(cfg), ctypes.byref(srv)) == 0
+        for cid, release in ((1, 0), (2, 1)):
+            r = wait(submit(cid, 70, release))
+            print(where, r.status, r.error.decode(), flush=True)
+        assert L.sparc_server_destroy(srv) == 0
+        L.stub_throw(b"")
+        srv = ctypes.c_void_p()
+        assert L.sparc_server_create(ctypes.byref(cfg), ctypes.byref(srv)) == 0
+        ok = wait(submit(3, 70, release=1))
+        assert ok.status == 0, ok.error
+        assert L.sparc_server_destroy(srv) == 0
+        print("child ok", flush=True)
+        return
     used = ctypes.c_uint64()
     for cid in (1, 2):
         L.stub_throw(where.encode())
@@ -86,6 +103,19 @@ def _child(where):
 def test_exception_fails_its_request_only(where):
     host_library.load()
     r = subprocess.run([sys.executable, os.path.abspath(__file__), where], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "child ok" in r.stdout, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("where", [
+    "hipSetDevice", "hipStreamCreateWithFlags", "hipStreamSynchronize", "hipFreeAsync", "hipFree", "hipStreamDestroy",
+    "hipEventRecord", "hipEventQuery", "roctxRangePushA", "roctxRangePop", "rocblas_create_handle",
+    "rocblas_set_stream"])
+def test_exception_outside_a_request_leaves_the_process(where):
+    """The worker's own calls, the clean-up after a request and what destructors
+    call: none of them ends the process, and a later server runs its requests."""
+    host_library.load()
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), where, "anywhere"], capture_output=True, text=True,
+                       timeout=120)
     assert r.returncode == 0 and "child ok" in r.stdout, r.stdout + r.stderr
 
 
@@ -119,4 +149,4 @@ print("child ok")
 
 
 if __name__ == "__main__":
-    _child(sys.argv[1])
+    _child(sys.argv[1], len(sys.argv) > 2)
