@@ -39,6 +39,11 @@ STENCIL_SRCS = [os.path.join(ROOT, "paper_1603_04334_amd", "csrc", f)
                           "rstep_launch.hpp")]
 
 
+# why the serving measurement does not run by itself
+SERVING_OFF = ("off: a run with four workers has ended with std::bad_variant_access thrown inside a library, "
+               "at a call that is not known yet")
+
+
 def parse():
     p = argparse.ArgumentParser()
     p.add_argument("--gpus", type=int, default=1)
@@ -53,7 +58,9 @@ def parse():
     p.add_argument("--no-next", action="store_true",
                    help="skip the first-SCF, density, force and electrostatic-potential measurements")
     p.add_argument("--batch-only", action="store_true", help="print only the batched measurement")
-    p.add_argument("--no-serve", action="store_true", help="skip the serving measurement")
+    p.add_argument("--serve", action="store_true",
+                   help="run the serving measurement, which is off by default (SERVING_OFF)")
+    p.add_argument("--no-serve", action="store_true", help="leave the serving measurement out of the line altogether")
     p.add_argument("--serve-only", action="store_true", help="print only the serving measurement")
     p.add_argument("--serve-rates", default="50",
                    help="comma-separated Poisson arrival rates in requests/s (full sweep: 50,100,200,500,1000,2000)")
@@ -779,7 +786,9 @@ def main():
         print("bench: batched clusters", file=sys.stderr, flush=True)
         torch.cuda.empty_cache()
         out["batched"] = batch_measure()
-    if not args.no_serve:
+    if not args.no_serve and not args.serve:
+        out["serving"] = {"skipped": SERVING_OFF}
+    elif not args.no_serve:
         print("bench: serving", file=sys.stderr, flush=True)
         torch.cuda.empty_cache()
         out["serving"] = serve_in_child(args)
